@@ -552,27 +552,47 @@ struct MgParams {
     rbgs_sweep_opts sweep;
 };
 
-// Enqueues one V-cycle from level l down; *states collects the persistent
-// kernels' state blocks whose error words must be checked.
+// The smoothing runs in the fused legs (multigrid_fused.hip) when the
+// library chooses the kernel and would smooth with plain half-sweeps (fewer
+// than 8 sweeps a call); without sweeps on a leg there is nothing to fuse.
+// Of more than two sweeps a leg the legs take the two next to the transfer.
+bool mg_fused(const MgParams& mp) {
+    return mp.sweep.kernel == RBGS_KERNEL_AUTO && mp.nu1 >= 1 && mp.nu1 < 8 && mp.nu2 >= 1 &&
+           mp.nu2 < 8;
+}
+
+bool mg_coarse_end(const MgPlan& p, int l) {
+    return p.g[l].n <= kMgCoarseN && p.levels - l <= kMgMaxCoarseLevels;
+}
+
+// The cycle's last launch leaves the finest level's residual norm in sums[0].
+bool mg_norm_in_cycle(const MgPlan& p, const MgParams& mp) {
+    return mg_fused(mp) && mp.nu2 <= 2 && p.levels > 1 && !mg_coarse_end(p, 0);
+}
+
 // Launches one V-cycle enqueues (an upper bound: the plain smoother's two
 // per sweep), for the decision to capture the cycles as a graph.
 int64_t mg_launches_per_cycle(const MgPlan& p, const MgParams& mp) {
     int64_t total = 0;
     for (int l = 0; l < p.levels; ++l) {
-        if (p.g[l].n <= kMgCoarseN && p.levels - l <= kMgMaxCoarseLevels) return total + 1;
+        if (mg_coarse_end(p, l)) return total + 1;
         if (l == p.levels - 1) return total + 2 * int64_t(mp.coarse_sweeps);
         total += 2 * (int64_t(mp.nu1) + mp.nu2) + 2;
     }
     return total;
 }
 
+// Enqueues one V-cycle from level l down; *states collects the persistent
+// kernels' state blocks whose error words must be checked.
 int mg_cycle(const MgPlan& p, int l, const MgParams& mp, hipStream_t s, const int* stop,
              std::vector<void*>* states) {
     const Workspace& a = p.w[l];
-    if (p.g[l].n <= kMgCoarseN && p.levels - l <= kMgMaxCoarseLevels) {
+    const bool fused = mg_fused(mp);
+    if (mg_coarse_end(p, l)) {
         // this level and all below: one workgroup, one launch
         MgCoarseLevels lv;
         lv.count = p.levels - l;
+        lv.zero_top = fused && l > 0;  // a fused leg above leaves u as it was
         for (int k = 0; k < lv.count; ++k) {
             const Workspace& wk = p.w[l + k];
             const double h = p.g[l + k].h;
@@ -596,11 +616,56 @@ int mg_cycle(const MgPlan& p, int l, const MgParams& mp, hipStream_t s, const in
             states->push_back(es);
         return RBGS_OK;
     };
-    if (l == p.levels - 1) return smooth(mp.coarse_sweeps);
-    int rc = smooth(mp.nu1);
-    if (rc) return rc;
+    auto clear = [&]() -> int {  // a zero iterate, ring included
+        const size_t colour = align256(size_t(p.g[l].n + 2) * size_t(a.pitch) * 8);
+        HIP_TRY(launch_zero(a.u_red, colour, s), "zero coarse iterate");
+        HIP_TRY(launch_zero(a.u_black, colour, s), "zero coarse iterate");
+        return RBGS_OK;
+    };
+    int rc = RBGS_OK;
+    if (l == p.levels - 1) {
+        if (fused && l > 0 && (rc = clear())) return rc;
+        return smooth(mp.coarse_sweeps);
+    }
     const Workspace& c = p.w[l + 1];
     const double hl = p.g[l].h;
+    if (fused) {
+        const int before = mp.nu1 > 2 ? mp.nu1 - 2 : 0, after = mp.nu2 > 2 ? mp.nu2 - 2 : 0;
+        if (before > 0) {
+            if (l > 0 && (rc = clear())) return rc;
+            if ((rc = smooth(before))) return rc;
+        }
+        MgLegArgs leg{};
+        leg.b_in = static_cast<const double*>(a.u_black);
+        leg.r_in = static_cast<const double*>(a.u_red);
+        leg.b_out = static_cast<double*>(a.u2_black);
+        leg.f_red = static_cast<const double*>(a.f_red);
+        leg.f_black = static_cast<const double*>(a.f_black);
+        leg.pitch = a.pitch;
+        leg.n = p.g[l].n;
+        leg.nc = p.g[l + 1].n;
+        leg.h2 = hl * hl;
+        leg.inv_h2 = 1.0 / (hl * hl);
+        leg.fc_red = static_cast<double*>(c.f_red);
+        leg.fc_black = static_cast<double*>(c.f_black);
+        leg.cpitch = c.pitch;
+        leg.stop = stop;
+        HIP_TRY(launch_mg_leg(leg, mp.nu1 - before, false, l > 0 && before == 0, false, s),
+                "multigrid leg down");
+        if ((rc = mg_cycle(p, l + 1, mp, s, stop, states))) return rc;
+        leg.b_in = static_cast<const double*>(a.u2_black);
+        leg.r_in = static_cast<const double*>(a.u2_red);
+        leg.b_out = static_cast<double*>(a.u_black);
+        leg.r_out = static_cast<double*>(a.u_red);
+        leg.e_red = static_cast<const double*>(c.u_red);
+        leg.e_black = static_cast<const double*>(c.u_black);
+        leg.partials = a.partials;
+        leg.sums = a.sums;
+        HIP_TRY(launch_mg_leg(leg, mp.nu2 - after, true, false, l == 0 && after == 0, s),
+                "multigrid leg up");
+        return smooth(after);
+    }
+    if ((rc = smooth(mp.nu1))) return rc;
     HIP_TRY(launch_mg_restrict(static_cast<const double*>(a.u_red),
                                static_cast<const double*>(a.u_black),
                                static_cast<const double*>(a.f_red),
@@ -1444,35 +1509,50 @@ int rbgs_mg_solve(const rbgs_grid* g, rbgs_dtype dt, void* u, const void* f,
     mp.sweep = o->sweep;
     HIP_TRY(launch_pack(u, g->ld, w0.u_red, w0.u_black, g->n, w0.pitch, 8, s), "pack u");
     HIP_TRY(launch_pack(f, g->ld, w0.f_red, w0.f_black, g->n, w0.pitch, 8, s), "pack f");
+    // coarse iterates: a zero ring (interiors are rewritten every cycle);
+    // persistent smoothers' error words start clear once per solve
+    MgInit init{};
+    init.count = p.levels;
     for (int l = 0; l < p.levels; ++l) {
         const Workspace& wl = p.w[l];
-        if (l > 0) {  // coarse iterates: zero ring (and interior, rewritten per cycle)
-            const size_t colour = align256(size_t(p.g[l].n + 2) * size_t(wl.pitch) * 8);
-            HIP_TRY(launch_zero(wl.u_red, colour, s), "zero coarse iterate");
-            HIP_TRY(launch_zero(wl.u_black, colour, s), "zero coarse iterate");
-        }
-        // persistent smoothers' error words start clear once per solve
-        HIP_TRY(launch_zero(static_cast<char*>(wl.blocked) + 64, 4, s), "clear error word");
-        if (wl.resident)
-            HIP_TRY(launch_zero(static_cast<char*>(wl.resident) + 64, 4, s), "clear error word");
+        MgInitLevel& il = init.level[l];
+        il.u[0] = static_cast<double*>(wl.u_red);
+        il.u[1] = static_cast<double*>(wl.u_black);
+        il.u[2] = static_cast<double*>(wl.u2_red);
+        il.u[3] = static_cast<double*>(wl.u2_black);
+        il.pitch = wl.pitch;
+        il.n = l > 0 ? p.g[l].n : 0;
+        il.error[0] = reinterpret_cast<int*>(static_cast<char*>(wl.blocked) + 64);
+        il.error[1] = wl.resident ? reinterpret_cast<int*>(static_cast<char*>(wl.resident) + 64)
+                                  : nullptr;
     }
+    HIP_TRY(launch_mg_init(init, s), "multigrid rings");
+    if (mg_fused(mp))  // the legs alternate between both buffers
+        HIP_TRY(launch_copy_ring(w0.u2_red, w0.u2_black, w0.u_red, w0.u_black, g->n, w0.pitch, 8, s),
+                "ring copy");
 
     rbgs_mg_info out{0, p.levels, nL, mp.coarse_sweeps, 0.0, 0.0, 0, RBGS_OK};
     std::vector<void*> states;
     double rel = 0.0, ab = 0.0;
     int32_t cycles = 0;
     const bool fixed = o->rel_tol <= 0.0;  // exactly max_cycles cycles
-    if (!fixed) {
+    // a cycle that ends with its own residual norm leaves sum b^2 (which
+    // depends on f and the ring alone) as the residual of the start forms it
+    const bool own_norm = mg_norm_in_cycle(p, mp);
+    if (!fixed || (own_norm && o->max_cycles > 0)) {
         if ((rc = split_residual<double>(&p.g[0], w0, s, nullptr, nullptr, 0))) return rc;
-        if ((rc = fetch_norms(w0, s, &ab, &rel))) return rc;
+        if (!fixed && (rc = fetch_norms(w0, s, &ab, &rel))) return rc;
     }
+    auto cycle_norm = [&](hipStream_t cs) -> int {
+        return own_norm ? RBGS_OK : split_residual<double>(&p.g[0], w0, cs, nullptr, nullptr, 0);
+    };
     if ((fixed || (!(rel <= o->rel_tol) && std::isfinite(rel))) && o->max_cycles > 0) {
         RoundBody body = [&](hipStream_t cs, const int* stop, void** es) -> int {
             states.clear();
             int r = mg_cycle(p, 0, mp, cs, stop, &states);
             if (r) return r;
             *es = states.empty() ? nullptr : states[0];
-            return split_residual<double>(&p.g[0], w0, cs, nullptr, nullptr, 0);
+            return cycle_norm(cs);
         };
         int rounds = 0;
         bool used = false;
@@ -1490,8 +1570,7 @@ int rbgs_mg_solve(const rbgs_grid* g, rbgs_dtype dt, void* u, const void* f,
                 if ((rc = mg_cycle(p, 0, mp, s, nullptr, &states))) return rc;
                 ++cycles;
                 if (!fixed || cycles == o->max_cycles) {
-                    if ((rc = split_residual<double>(&p.g[0], w0, s, nullptr, nullptr, 0)))
-                        return rc;
+                    if ((rc = cycle_norm(s))) return rc;
                     if ((rc = fetch_norms(w0, s, &ab, &rel))) return rc;
                 }
             }

@@ -345,6 +345,16 @@ __global__ __launch_bounds__(kCoarseThreads) void k_mg_coarse_vcycle(MgCoarseLev
                                                                     const int* stop) {
     if (stop && *stop) return;
     const int m = lv.count;
+    if (lv.zero_top) {
+        const MgCoarseLevel& t = lv.level[0];
+        const int W = (t.n >> 1) + 1;
+        for (int idx = threadIdx.x; idx < t.n * W; idx += kCoarseThreads) {
+            const int64_t at = int64_t(idx / W + 1) * t.pitch + idx % W;
+            t.u_red[at] = 0.0;
+            t.u_black[at] = 0.0;
+        }
+        __syncthreads();
+    }
     for (int l = 0; l + 1 < m; ++l) {
         cw_sweeps(lv.level[l], nu1);
         cw_restrict(lv.level[l], lv.level[l + 1]);
@@ -358,7 +368,32 @@ __global__ __launch_bounds__(kCoarseThreads) void k_mg_coarse_vcycle(MgCoarseLev
     }
 }
 
+// One workgroup row (blockIdx.y) per level, its threads over the rows.
+__global__ __launch_bounds__(kMgThreads) void k_mg_init(MgInit init) {
+    const MgInitLevel& lv = init.level[blockIdx.y];
+    if (blockIdx.x == 0 && threadIdx.x < 2 && lv.error[threadIdx.x]) *lv.error[threadIdx.x] = 0;
+    if (lv.n == 0) return;
+    const int n1 = lv.n + 1;
+    for (int i = int(blockIdx.x); i <= n1; i += int(gridDim.x)) {
+        const bool whole = i == 0 || i == n1;
+        // the ring columns 0 and n + 1 of either colour sit at q = 0 and
+        // (n + 1) >> 1; a row of the ring is cleared whole
+        for (int64_t q = threadIdx.x; q < lv.pitch; q += kMgThreads) {
+            for (int k = 0; k < 4; ++k) {
+                const int64_t j = 2 * q + ((i + k) & 1);  // k & 1 is the colour
+                if (whole || j == 0 || j >= n1) lv.u[k][int64_t(i) * lv.pitch + q] = 0.0;
+            }
+        }
+    }
+}
+
 }  // namespace
+
+hipError_t launch_mg_init(const MgInit& init, hipStream_t s) {
+    if (init.count < 1 || init.count > kMgInitLevels) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mg_init, dim3(512, unsigned(init.count)), dim3(kMgThreads), 0, s, init);
+    return hipGetLastError();
+}
 
 hipError_t launch_mg_coarse_vcycle(const MgCoarseLevels& levels, int nu1, int nu2,
                                    int coarse_sweeps, const int* stop, hipStream_t s) {

@@ -19,6 +19,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace rbgs {
 
 constexpr int kWaveSize = 64;
@@ -147,6 +149,40 @@ hipError_t launch_mg_prolong_red(double* u_red, const double* u_black, const dou
                                  const double* e_black, int64_t cpitch, const int* stop,
                                  hipStream_t s);
 
+// A level's half of the cycle in one pass (multigrid_fused.hip; n odd, n >= 3).
+// down (up = false): `sweeps` (1 or 2) sweeps of the iterate whose black is
+// b_in (ring: b_in, r_in; zero = true: an all-zero iterate, nothing read), the
+// final black into b_out, the full-weighted residual into fc.  up: black b_in
+// plus the interpolant of e, `sweeps` sweeps, both colours into r_out/b_out;
+// norm: also the sum of squares of the residual into sums[0] through
+// mg_leg_geometry's bands x strips partial sums.  Outputs do not overlap
+// inputs.  Nothing when stop != nullptr and *stop != 0.
+struct MgLegGeometry {
+    int bands, rows, strips;
+};
+MgLegGeometry mg_leg_geometry(int n);
+struct MgLegArgs {
+    const double* b_in;
+    const double* r_in;
+    double* b_out;
+    double* r_out;
+    const double* f_red;
+    const double* f_black;
+    int64_t pitch;
+    double h2, inv_h2;
+    double* fc_red;
+    double* fc_black;
+    const double* e_red;
+    const double* e_black;
+    int64_t cpitch;
+    double* partials;
+    double* sums;
+    const int* stop;
+    int n, nc;
+    int bands, rows, strips;  // filled by launch_mg_leg
+};
+hipError_t launch_mg_leg(MgLegArgs a, int sweeps, bool up, bool zero, bool norm, hipStream_t s);
+
 // The coarse end of a multigrid cycle in one workgroup: levels[0] (at most
 // kMgCoarseN points per side) down to the coarsest, each with its split u
 // and f arrays; pre/post smoothing counts nu1/nu2 and the coarsest level's
@@ -166,7 +202,23 @@ struct MgCoarseLevel {
 struct MgCoarseLevels {
     MgCoarseLevel level[kMgMaxCoarseLevels];
     int count;
+    int zero_top;  // 1: level[0]'s iterate starts at zero, whatever u holds
 };
+// Before a solve's first cycle: the rings of both iterate buffers of the
+// levels below the finest <- 0 (interiors are written before they are read)
+// and every level's persistent-kernel error words <- 0, in one launch.
+constexpr int kMgInitLevels = 32;
+struct MgInitLevel {
+    double* u[4];   // red, black and the second red, black; unused when n == 0
+    int64_t pitch;
+    int n;          // 0: no ring to clear (the finest level)
+    int* error[2];  // error words or nullptr
+};
+struct MgInit {
+    MgInitLevel level[kMgInitLevels];
+    int count;
+};
+hipError_t launch_mg_init(const MgInit& init, hipStream_t s);
 hipError_t launch_mg_coarse_vcycle(const MgCoarseLevels& levels, int nu1, int nu2,
                                    int coarse_sweeps, const int* stop, hipStream_t s);
 
