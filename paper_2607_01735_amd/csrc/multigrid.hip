@@ -25,6 +25,10 @@ namespace rbgs {
 namespace {
 
 constexpr int kMgThreads = 256;
+
+// One colour of a level with its ring in LDS, (n + 2) rows of (n + 3) / 2.
+__host__ __device__ constexpr int mg_coarse_cells(int n) { return (n + 2) * ((n + 3) / 2); }
+
 constexpr int kRestrictRows = 4;  // coarse rows one thread marches down
 
 // Element k of a split row, 0 outside [0, pitch): only ever used for points
@@ -244,94 +248,53 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_prolong_red(
 }
 
 // ----- the coarse end of the cycle in one workgroup ------------------------
-// Levels of at most kMgCoarseN points per side cost little work but two
-// launches per sweep; below that size the rest of the V-cycle (its smoothing,
+// Levels of at most kMgCoarseN = 63 points per side cost little work but a
+// launch per step; below that size the rest of the V-cycle (its smoothing,
 // transfers and coarsest sweeps, in the order of the level-by-level cycle)
 // runs in one workgroup of kCoarseThreads threads with a barrier between
-// phases; the arrays stay in the level workspaces (L2-resident at these
-// sizes).  Every point's arithmetic is the kernels' above, so the iterate is
-// the same bit for bit.
+// phases, all levels' u and f in LDS (94 KB from 63^2 down, and 33 KB for the
+// residual of the level being restricted; a 127^2 level would need 270 KB).
+// Only the top level's f (and u, unless it starts at zero) is read and only
+// its u is written.  Every point's arithmetic is the kernels' above, so the
+// iterate is the same bit for bit.  It is bound by the LDS round trip and the
+// barrier of each phase: 127^2 down in global memory (L2) took 94 us a cycle.
 
 constexpr int kCoarseThreads = 1024;
+constexpr int kCoarseQ = 32;  // split columns of a phase: (kMgCoarseN + 1) / 2
+constexpr int kCoarseRows = kCoarseThreads / kCoarseQ;
 
-__device__ __forceinline__ double split_at(const double* red, const double* black, int64_t i,
-                                           int64_t j, int64_t pitch) {
-    return (((i + j) & 1) ? black : red)[i * pitch + (j >> 1)];
+// One level in LDS: split rows 0 .. n + 1 of `w` columns; u and f are element
+// offsets of their red arrays, black follows `cells` elements later.
+struct CwLevel {
+    int u, f, n, w, cells;
+    double h2, inv_h2;
+};
+
+extern __shared__ __align__(16) double cw_lds[];
+
+// Element of the array pair at `a` that holds point (i, j).
+__device__ __forceinline__ double cw_at(const CwLevel& L, int a, int i, int j) {
+    return cw_lds[a + ((i + j) & 1) * L.cells + i * L.w + (j >> 1)];
 }
 
-__device__ void cw_half_sweep(const MgCoarseLevel& L, int colour) {
-    double* self = colour ? L.u_black : L.u_red;
-    const double* other = colour ? L.u_red : L.u_black;
-    const double* f = colour ? L.f_black : L.f_red;
-    const int64_t pitch = L.pitch;
-    const int W = (L.n >> 1) + 1;
-    for (int idx = threadIdx.x; idx < L.n * W; idx += kCoarseThreads) {
-        const int64_t i = idx / W + 1, q = idx % W;
-        const int64_t p = (i + colour) & 1;
-        if (q < 1 - p || q > ((int64_t(L.n) - p) >> 1)) continue;
-        const double* orow = other + i * pitch;
-        double s = other[(i + 1) * pitch + q] + other[(i - 1) * pitch + q];
-        s = s + orow[q + p];
-        s = s + orow[q - 1 + p];
-        const double t = L.h2 * f[i * pitch + q];
+__device__ __forceinline__ void cw_half_sweep(const CwLevel& L, int colour) {
+    const int self = L.u + colour * L.cells, other = L.u + (1 - colour) * L.cells;
+    const int f = L.f + colour * L.cells;
+    const int q = threadIdx.x % kCoarseQ;
+    for (int i = int(threadIdx.x / kCoarseQ) + 1; i <= L.n; i += kCoarseRows) {
+        const int p = (i + colour) & 1;
+        if (q < 1 - p || q > ((L.n - p) >> 1)) continue;
+        const int at = i * L.w + q;
+        double s = cw_lds[other + at + L.w] + cw_lds[other + at - L.w];
+        s = s + cw_lds[other + at + p];
+        s = s + cw_lds[other + at - 1 + p];
+        const double t = L.h2 * cw_lds[f + at];
         s = s - t;
-        self[i * pitch + q] = 0.25 * s;
+        cw_lds[self + at] = 0.25 * s;
     }
 }
 
-__device__ __forceinline__ double cw_residual(const MgCoarseLevel& L, int64_t i, int64_t j) {
-    const int64_t pitch = L.pitch;
-    double s = split_at(L.u_red, L.u_black, i + 1, j, pitch) +
-               split_at(L.u_red, L.u_black, i - 1, j, pitch);
-    s = s + split_at(L.u_red, L.u_black, i, j + 1, pitch);
-    s = s + split_at(L.u_red, L.u_black, i, j - 1, pitch);
-    const double lap = (s - 4.0 * split_at(L.u_red, L.u_black, i, j, pitch)) * L.inv_h2;
-    return split_at(L.f_red, L.f_black, i, j, pitch) - lap;
-}
-
-__device__ void cw_restrict(const MgCoarseLevel& F, const MgCoarseLevel& C) {
-    const int nc = C.n;
-    for (int idx = threadIdx.x; idx < nc * nc; idx += kCoarseThreads) {
-        const int64_t I = idx / nc + 1, J = idx % nc + 1;
-        double row[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int64_t i = 2 * I - 1 + a;
-            row[a] = weight_row(cw_residual(F, i, 2 * J - 1), cw_residual(F, i, 2 * J),
-                                cw_residual(F, i, 2 * J + 1));
-        }
-        double* fdst = ((I + J) & 1) ? C.f_black : C.f_red;
-        double* udst = ((I + J) & 1) ? C.u_black : C.u_red;
-        fdst[I * C.pitch + (J >> 1)] = ((row[0] + 2.0 * row[1]) + row[2]) * 0.0625;
-        udst[I * C.pitch + (J >> 1)] = 0.0;
-    }
-}
-
-__device__ void cw_prolong_add(const MgCoarseLevel& C, const MgCoarseLevel& F) {
-    const int nf = F.n;
-    for (int idx = threadIdx.x; idx < nf * nf; idx += kCoarseThreads) {
-        const int64_t i = idx / nf + 1, j = idx % nf + 1;
-        const int64_t I = i >> 1, J = j >> 1;
-        const double e00 = split_at(C.u_red, C.u_black, I, J, C.pitch);
-        double v;
-        if ((i & 1) == 0 && (j & 1) == 0) {
-            v = e00;
-        } else if ((i & 1) == 1 && (j & 1) == 0) {
-            v = (e00 + split_at(C.u_red, C.u_black, I + 1, J, C.pitch)) * 0.5;
-        } else if ((i & 1) == 0) {
-            v = (e00 + split_at(C.u_red, C.u_black, I, J + 1, C.pitch)) * 0.5;
-        } else {
-            const double e01 = split_at(C.u_red, C.u_black, I, J + 1, C.pitch);
-            const double e10 = split_at(C.u_red, C.u_black, I + 1, J, C.pitch);
-            const double e11 = split_at(C.u_red, C.u_black, I + 1, J + 1, C.pitch);
-            v = ((e00 + e01) + (e10 + e11)) * 0.25;
-        }
-        double* dst = (((i + j) & 1) ? F.u_black : F.u_red) + i * F.pitch + (j >> 1);
-        *dst = *dst + v;
-    }
-}
-
-__device__ void cw_sweeps(const MgCoarseLevel& L, int count) {
+__device__ __forceinline__ void cw_sweeps(const CwLevel& L, int count) {
     for (int s = 0; s < count; ++s) {
         cw_half_sweep(L, 0);
         __syncthreads();
@@ -340,31 +303,120 @@ __device__ void cw_sweeps(const MgCoarseLevel& L, int count) {
     }
 }
 
+// The residual of every interior point into the natural array at r (pitch
+// n + 2).
+__device__ __forceinline__ void cw_residual(const CwLevel& L, int r) {
+    const int q = threadIdx.x % kCoarseQ;
+    for (int i = int(threadIdx.x / kCoarseQ) + 1; i <= L.n; i += kCoarseRows) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int j = 2 * q + e;
+            if (j < 1 || j > L.n) continue;
+            double s = cw_at(L, L.u, i + 1, j) + cw_at(L, L.u, i - 1, j);
+            s = s + cw_at(L, L.u, i, j + 1);
+            s = s + cw_at(L, L.u, i, j - 1);
+            const double lap = (s - 4.0 * cw_at(L, L.u, i, j)) * L.inv_h2;
+            cw_lds[r + i * (L.n + 2) + j] = cw_at(L, L.f, i, j) - lap;
+        }
+    }
+}
+
+__device__ __forceinline__ void cw_restrict(int r, int nf, const CwLevel& C) {
+    const int J = threadIdx.x % kCoarseQ + 1;
+    for (int I = int(threadIdx.x / kCoarseQ) + 1; I <= C.n && J <= C.n; I += kCoarseRows) {
+        double row[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int at = r + (2 * I - 1 + a) * (nf + 2) + 2 * J;
+            row[a] = weight_row(cw_lds[at - 1], cw_lds[at], cw_lds[at + 1]);
+        }
+        cw_lds[C.f + ((I + J) & 1) * C.cells + I * C.w + (J >> 1)] =
+            ((row[0] + 2.0 * row[1]) + row[2]) * 0.0625;
+    }
+}
+
+__device__ __forceinline__ void cw_prolong_add(const CwLevel& C, const CwLevel& F) {
+    const int q = threadIdx.x % kCoarseQ;
+    for (int i = int(threadIdx.x / kCoarseQ) + 1; i <= F.n && 2 * q <= F.n; i += kCoarseRows) {
+        const int I = i >> 1;
+        const double e00 = cw_at(C, C.u, I, q), e01 = cw_at(C, C.u, I, q + 1);
+        double v_even, v_odd;
+        if ((i & 1) == 0) {
+            v_even = e00;
+            v_odd = (e00 + e01) * 0.5;
+        } else {
+            const double e10 = cw_at(C, C.u, I + 1, q), e11 = cw_at(C, C.u, I + 1, q + 1);
+            v_even = (e00 + e10) * 0.5;
+            v_odd = ((e00 + e01) + (e10 + e11)) * 0.25;
+        }
+        const int at = F.u + i * F.w + q;
+        const int even = at + (i & 1) * F.cells, odd = at + (1 - (i & 1)) * F.cells;
+        if (q >= 1) cw_lds[even] = cw_lds[even] + v_even;
+        if (2 * q + 1 <= F.n) cw_lds[odd] = cw_lds[odd] + v_odd;
+    }
+}
+
+__device__ __forceinline__ CwLevel cw_level(const MgCoarseLevels& lv, int l) {
+    CwLevel L;
+    L.u = 0;
+    for (int k = 0; k < l; ++k) L.u += 4 * mg_coarse_cells(lv.level[k].n);
+    L.n = lv.level[l].n;
+    L.w = (L.n + 3) / 2;
+    L.cells = mg_coarse_cells(L.n);
+    L.f = L.u + 2 * L.cells;
+    L.h2 = lv.level[l].h2;
+    L.inv_h2 = lv.level[l].inv_h2;
+    return L;
+}
+
 __global__ __launch_bounds__(kCoarseThreads) void k_mg_coarse_vcycle(MgCoarseLevels lv, int nu1,
                                                                     int nu2, int coarse_sweeps,
                                                                     const int* stop) {
     if (stop && *stop) return;
     const int m = lv.count;
-    if (lv.zero_top) {
-        const MgCoarseLevel& t = lv.level[0];
-        const int W = (t.n >> 1) + 1;
-        for (int idx = threadIdx.x; idx < t.n * W; idx += kCoarseThreads) {
-            const int64_t at = int64_t(idx / W + 1) * t.pitch + idx % W;
-            t.u_red[at] = 0.0;
-            t.u_black[at] = 0.0;
+    const CwLevel last = cw_level(lv, m - 1);
+    const int total = last.u + 4 * last.cells;  // the residual's array follows
+    const MgCoarseLevel& g = lv.level[0];
+    const CwLevel top = cw_level(lv, 0);
+    for (int k = threadIdx.x; k < total; k += kCoarseThreads) cw_lds[k] = 0.0;
+    __syncthreads();
+    // rows of kCoarseQ columns, then the ring column's (w = 33 for n = 62, 63)
+    auto in = [&](int i, int q) {
+        const int64_t src = int64_t(i) * g.pitch + q;
+        const int at = i * top.w + q;
+        cw_lds[top.f + at] = g.f_red[src];
+        cw_lds[top.f + top.cells + at] = g.f_black[src];
+        if (!lv.zero_top) {
+            cw_lds[top.u + at] = g.u_red[src];
+            cw_lds[top.u + top.cells + at] = g.u_black[src];
         }
-        __syncthreads();
-    }
+    };
+    const int tq = threadIdx.x % kCoarseQ, ti = threadIdx.x / kCoarseQ;
+    for (int i = ti; i <= top.n + 1 && tq < top.w; i += kCoarseRows) in(i, tq);
+    if (top.w > kCoarseQ && int(threadIdx.x) <= top.n + 1) in(int(threadIdx.x), kCoarseQ);
+    __syncthreads();
     for (int l = 0; l + 1 < m; ++l) {
-        cw_sweeps(lv.level[l], nu1);
-        cw_restrict(lv.level[l], lv.level[l + 1]);
+        const CwLevel L = cw_level(lv, l);
+        cw_sweeps(L, nu1);
+        cw_residual(L, total);
+        __syncthreads();
+        cw_restrict(total, L.n, cw_level(lv, l + 1));
         __syncthreads();
     }
-    cw_sweeps(lv.level[m - 1], coarse_sweeps);
+    cw_sweeps(last, coarse_sweeps);
     for (int l = m - 2; l >= 0; --l) {
-        cw_prolong_add(lv.level[l + 1], lv.level[l]);
+        const CwLevel L = cw_level(lv, l);
+        cw_prolong_add(cw_level(lv, l + 1), L);
         __syncthreads();
-        cw_sweeps(lv.level[l], nu2);
+        cw_sweeps(L, nu2);
+    }
+    for (int i = ti + 1; i <= top.n; i += kCoarseRows) {
+        const int p = i & 1;  // red's column parity; black has the other
+        const int at = i * top.w + tq;
+        const int64_t dst = int64_t(i) * g.pitch + tq;
+        if (2 * tq + p >= 1 && 2 * tq + p <= top.n) g.u_red[dst] = cw_lds[top.u + at];
+        if (2 * tq + 1 - p >= 1 && 2 * tq + 1 - p <= top.n)
+            g.u_black[dst] = cw_lds[top.u + top.cells + at];
     }
 }
 
@@ -397,8 +449,15 @@ hipError_t launch_mg_init(const MgInit& init, hipStream_t s) {
 
 hipError_t launch_mg_coarse_vcycle(const MgCoarseLevels& levels, int nu1, int nu2,
                                    int coarse_sweeps, const int* stop, hipStream_t s) {
-    if (levels.count < 1 || levels.count > kMgMaxCoarseLevels) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mg_coarse_vcycle, dim3(1), dim3(kCoarseThreads), 0, s, levels, nu1, nu2,
+    if (levels.count < 1 || levels.count > kMgMaxCoarseLevels || levels.level[0].n > kMgCoarseN)
+        return hipErrorInvalidValue;
+    size_t cells = size_t(levels.level[0].n + 2) * size_t(levels.level[0].n + 2);  // the residual
+    for (int l = 0; l < levels.count; ++l) cells += 4 * size_t(mg_coarse_cells(levels.level[l].n));
+    const size_t lds = cells * sizeof(double);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mg_coarse_vcycle),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mg_coarse_vcycle, dim3(1), dim3(kCoarseThreads), lds, s, levels, nu1, nu2,
                        coarse_sweeps, stop);
     return hipGetLastError();
 }

@@ -187,7 +187,7 @@ hipError_t launch_mg_leg(MgLegArgs a, int sweeps, bool up, bool zero, bool norm,
 // kMgCoarseN points per side) down to the coarsest, each with its split u
 // and f arrays; pre/post smoothing counts nu1/nu2 and the coarsest level's
 // sweeps; nothing when stop != nullptr and *stop != 0.
-constexpr int kMgCoarseN = 127;
+constexpr int kMgCoarseN = 63;
 constexpr int kMgMaxCoarseLevels = 8;
 struct MgCoarseLevel {
     double* u_red;
