@@ -708,6 +708,8 @@ struct Mc9Workspace {
     double* sums = nullptr;  // sum r^2, sum b^2; the graph rounds' state at +64 bytes
     int* state = nullptr;    // flag-driven form: error word, ticket at +32 ints, block
                              // counters from +64 ints
+    size_t base = 0;         // bytes up to here: every form but the fused passes
+    double* u2[4] = {nullptr, nullptr, nullptr, nullptr};  // the fused passes' second buffer
     size_t total = 0;
 };
 
@@ -725,13 +727,15 @@ Mc9Workspace plan_mc9(const rbgs_grid* g, char* base) {
     w.partials = take(size_t(mc9_residual_blocks(g->n)) * 2 * sizeof(double));
     w.sums = take(256);
     w.state = reinterpret_cast<int*>(take(256 + size_t(kMc9MaxBlocks) * sizeof(int)));
+    w.base = off;
+    for (auto& c : w.u2) c = take(colour);
     w.total = off;
     return w;
 }
 
-// Four-colour kernel choice: AUTO or PLAIN (a launch per colour), RESIDENT
-// (the flag-driven form, one launch for all quarter-sweeps); no temporally
-// blocked form.
+// Four-colour kernel choice: AUTO (fused passes, several sweeps each), PLAIN
+// (a launch per colour), RESIDENT (the flag-driven form, one launch for all
+// quarter-sweeps); no flag-driven temporally blocked form.
 int mc9_check_kernel(int kernel) {
     if (kernel == RBGS_KERNEL_BLOCKED)
         return fail(RBGS_EUNSUPPORTED, "the 9-point sweep has no temporally blocked kernel: use "
@@ -781,15 +785,49 @@ int mc9_prepare(const rbgs_grid* g, const void* u, const void* f, void* ws, size
     if (!valid_grid(g, &why)) return fail(RBGS_EINVAL, why);
     Mc9Workspace plan = plan_mc9(g, nullptr);
     int rc;
-    if ((rc = check_workspace(ws, ws_bytes, plan.total))) return rc;
+    // a workspace without the second buffer still serves: AUTO then launches
+    // per colour
+    const bool second = ws_bytes >= plan.total;
+    if ((rc = check_workspace(ws, ws_bytes, second ? plan.total : plan.base))) return rc;
     if ((rc = check_device_range(u, grid_bytes(g, RBGS_F64), "u"))) return rc;
     if ((rc = check_device_range(f, grid_bytes(g, RBGS_F64), "f"))) return rc;
     *w = plan_mc9(g, static_cast<char*>(ws));
+    if (!second)
+        for (auto& c : w->u2) c = nullptr;
     return RBGS_OK;
 }
 
+// Passes of nsweeps sweeps at most mc9_fuse(n) deep (depths differ by at most
+// one); even: an even number, so that the result is where the start was, if
+// nsweeps allows one.
+int mc9_passes(int n, int nsweeps, bool even) {
+    const int depth = mc9_fuse(n);
+    int p = (nsweeps - 1) / depth + (nsweeps > 0 ? 1 : 0);
+    if (even && (p & 1) && nsweeps > p) ++p;
+    return p;
+}
+
+// The fused passes; the iterate starts in u2 (start = 1) or u (0).
+int mc9_sweeps_fused(const rbgs_grid* g, const Mc9Workspace& w, int nsweeps, int passes, int start,
+                     hipStream_t s, const int* stop) {
+    const double c6 = 6.0 * (g->h * g->h);
+    for (int p = 0; p < passes; ++p) {
+        const int k = nsweeps / passes + (p < nsweeps % passes ? 1 : 0);
+        const bool second = ((p + start) & 1) != 0;
+        HIP_TRY(launch_mc9_pass(second ? w.u2 : w.u, second ? w.u : w.u2, w.f, g->n, c6, k,
+                                p == passes - 1, stop, s),
+                "9-point pass");
+    }
+    return RBGS_OK;
+}
+
+// A launch per colour, or (fused; both buffers hold the ring) an even number
+// of passes; a single sweep is a launch per colour either way.
 int mc9_sweeps(const rbgs_grid* g, const Mc9Workspace& w, int nsweeps, hipStream_t s,
-               const int* stop) {
+               const int* stop, bool fused) {
+    const int passes = mc9_passes(g->n, nsweeps, true);
+    if (fused && passes > 0 && passes % 2 == 0)
+        return mc9_sweeps_fused(g, w, nsweeps, passes, 0, s, stop);
     const double c6 = 6.0 * (g->h * g->h);
     for (int it = 0; it < nsweeps; ++it)
         for (int colour = 0; colour < 4; ++colour)
@@ -1615,11 +1653,21 @@ int rbgs_mc9_sweep(const rbgs_grid* g, double* u, const double* f, int32_t nswee
     if (nsweeps == 0) return RBGS_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool flags = kernel == RBGS_KERNEL_RESIDENT;
+    const bool fused = kernel == RBGS_KERNEL_AUTO && w.u2[0] != nullptr;
     int capacity = 0;
     if (flags && (rc = mc9_flags_setup(w, s, &capacity))) return rc;
-    HIP_TRY(launch_mc9_pack(u, g->ld, w.u, g->n, s), "pack u");
+    // an odd number of passes starts in the second buffer
+    const int passes = mc9_passes(g->n, nsweeps, false), start = fused ? passes & 1 : 0;
+    HIP_TRY(launch_mc9_pack(u, g->ld, start ? w.u2 : w.u, g->n, s,
+                            fused ? (start ? w.u : w.u2) : nullptr),
+            "pack u");
     HIP_TRY(launch_mc9_pack(f, g->ld, w.f, g->n, s), "pack f");
-    rc = flags ? mc9_sweeps_flags(g, w, nsweeps, capacity, s) : mc9_sweeps(g, w, nsweeps, s, nullptr);
+    if (fused) {
+        rc = mc9_sweeps_fused(g, w, nsweeps, passes, start, s, nullptr);
+    } else {
+        rc = flags ? mc9_sweeps_flags(g, w, nsweeps, capacity, s)
+                   : mc9_sweeps(g, w, nsweeps, s, nullptr, false);
+    }
     if (rc) return rc;
     HIP_TRY(launch_mc9_unpack(u, g->ld, w.u, g->n, s), "unpack u");
     return flags ? mc9_flags_error(w, s) : RBGS_OK;
@@ -1655,14 +1703,15 @@ int rbgs_mc9_solve(const rbgs_grid* g, double* u, const double* f, int32_t max_s
     hipStream_t s = static_cast<hipStream_t>(stream);
     int capacity = 0;
     if (flags && (rc = mc9_flags_setup(w, s, &capacity))) return rc;
-    HIP_TRY(launch_mc9_pack(u, g->ld, w.u, g->n, s), "pack u");
+    const bool fused = kernel == RBGS_KERNEL_AUTO && w.u2[0] != nullptr;
+    HIP_TRY(launch_mc9_pack(u, g->ld, w.u, g->n, s, fused ? w.u2 : nullptr), "pack u");
     HIP_TRY(launch_mc9_pack(f, g->ld, w.f, g->n, s), "pack f");
     double rel = 0.0, ab = 0.0;
     int32_t done = 0;
     // k sweeps of the asked-for form; the flag-driven form checks its error
     // word after each group (one launch per group of sweeps)
     auto sweeps = [&](int k) -> int {
-        if (!flags) return mc9_sweeps(g, w, k, s, nullptr);
+        if (!flags) return mc9_sweeps(g, w, k, s, nullptr, fused);
         int r = mc9_sweeps_flags(g, w, k, capacity, s);
         return r ? r : mc9_flags_error(w, s);
     };
@@ -1680,7 +1729,7 @@ int rbgs_mc9_solve(const rbgs_grid* g, double* u, const double* f, int32_t max_s
             v.sums = w.sums;
             RoundBody body = [&](hipStream_t cs, const int* stop, void** es) -> int {
                 *es = nullptr;
-                int r = mc9_sweeps(g, w, check_every, cs, stop);
+                int r = mc9_sweeps(g, w, check_every, cs, stop, fused);
                 return r ? r : mc9_residual_sums(g, w, cs);
             };
             int rounds = 0;

@@ -43,9 +43,11 @@ struct ConstColours {
 
 // natural (n+2) x ld -> four colour arrays; the 2 x 2 block (2I .. 2I+1,
 // 2J .. 2J+1) holds one point of each colour.  Points beyond the grid get 0.
+// ring (optional arrays): the ring's points go there too (the fused passes'
+// other buffer; a launch of its own for them took 8 us at 4001^2).
 __global__ __launch_bounds__(kThreads) void k_mc9_pack(const double* __restrict__ nat, int64_t ld,
-                                                       Colours dst, int n, int64_t pitch,
-                                                       int rows) {
+                                                       Colours dst, Colours ring, int n,
+                                                       int64_t pitch, int rows) {
     const int64_t J = int64_t(blockIdx.x) * kThreads + threadIdx.x;
     const int64_t I = blockIdx.y;
     if (J >= pitch || I >= rows) return;
@@ -54,7 +56,10 @@ __global__ __launch_bounds__(kThreads) void k_mc9_pack(const double* __restrict_
         for (int pj = 0; pj < 2; ++pj) {
             const int64_t j = 2 * J + pj;
             const bool in = i <= n + 1 && j <= n + 1;
-            dst.c[pi + 2 * pj][I * pitch + J] = in ? nat[i * ld + j] : 0.0;
+            const double v = in ? nat[i * ld + j] : 0.0;
+            dst.c[pi + 2 * pj][I * pitch + J] = v;
+            if (ring.c[0] && in && (i == 0 || i == n + 1 || j == 0 || j == n + 1))
+                ring.c[pi + 2 * pj][I * pitch + J] = v;
         }
     }
 }
@@ -297,12 +302,14 @@ int64_t mc9_pitch(int n) {
 int mc9_residual_blocks(int n) { return mc9_rows(n) < kResidualBlocks ? mc9_rows(n) : kResidualBlocks; }
 
 hipError_t launch_mc9_pack(const double* nat, int64_t ld, double* const colours[4], int n,
-                           hipStream_t s) {
+                           hipStream_t s, double* const* ring) {
     const int64_t pitch = mc9_pitch(n);
     const int rows = mc9_rows(n);
     Colours d{{colours[0], colours[1], colours[2], colours[3]}};
+    Colours r{{nullptr, nullptr, nullptr, nullptr}};
+    if (ring) r = Colours{{ring[0], ring[1], ring[2], ring[3]}};
     hipLaunchKernelGGL(k_mc9_pack, dim3(unsigned((pitch + kThreads - 1) / kThreads), unsigned(rows)),
-                       dim3(kThreads), 0, s, nat, ld, d, n, pitch, rows);
+                       dim3(kThreads), 0, s, nat, ld, d, r, n, pitch, rows);
     return hipGetLastError();
 }
 

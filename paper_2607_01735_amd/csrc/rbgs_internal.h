@@ -231,13 +231,30 @@ int mc9_rows(int n);
 int64_t mc9_pitch(int n);
 int mc9_residual_blocks(int n);
 hipError_t launch_mc9_pack(const double* nat, int64_t ld, double* const colours[4], int n,
-                           hipStream_t s);
+                           hipStream_t s, double* const* ring = nullptr);
 hipError_t launch_mc9_unpack(double* nat, int64_t ld, double* const colours[4], int n,
                              hipStream_t s);
 hipError_t launch_mc9_quarter(double* const u[4], double* const f[4], int n, double c6,
                               int colour, const int* stop, hipStream_t s);
 hipError_t launch_mc9_residual(double* const u[4], double* const f[4], int n, double inv6h2,
                                double* partials, double* out, hipStream_t s);
+// pass: `sweeps` (1 .. kMc9MaxFuse) whole sweeps from buffer `in` to buffer
+// `out` (multicolour9_fused.hip); colour 0 is written only when last; the ring
+// of `out` holds the ring of `in` (launch_mc9_pack's `ring` puts it there).
+// in's colour 0 is read on the ring only.
+constexpr int kMc9MaxFuse = 3;
+struct Mc9PassArgs {
+    const double* in[4];
+    double* out[4];
+    const double* f[4];
+    const int* stop;
+    double c6;
+    int64_t pitch;
+    int n, rows, bands, pairs, last;
+};
+int mc9_fuse(int n);  // sweeps per pass for grids of size n
+hipError_t launch_mc9_pass(double* const in[4], double* const out[4], double* const f[4], int n,
+                           double c6, int sweeps, bool last, const int* stop, hipStream_t s);
 // The flag-driven 9-point form: `levels` quarter-sweeps (colour 0 first) in
 // one launch (levels x mc9_flags_blocks(n, capacity) < 2^31).  capacity:
 // resident workgroups of the kernel (mc9_flags_capacity()); ticket and
