@@ -642,11 +642,14 @@ int rbgs_mc9_solve(const rbgs_grid *g, double *u, const double *f,
  * residual is r = f - lap(u), b = r with the interior of u set to zero.
  * --------------------------------------------------------------------- */
 
-/* Workspace bytes (split u and f, reduction space); 0 for an invalid grid. */
+/* Workspace bytes (split u and f, a second black array for the fused passes,
+ * reduction space); 0 for an invalid grid.  A workspace without the second
+ * black array (a fifth of the arrays, at the end) is accepted too: the sweeps
+ * then run as one launch per half-sweep. */
 size_t rbgs_rb3_workspace_size(const rbgs_grid *g);
 
-/* nsweeps sweeps of u in place, one launch per half-sweep.  Asynchronous
- * on `stream`. */
+/* nsweeps sweeps of u in place, in passes of up to two sweeps, one launch
+ * each, over independent overlapping tiles.  Asynchronous on `stream`. */
 int rbgs_rb3_sweep(const rbgs_grid *g, double *u, const double *f,
                    int32_t nsweeps, void *workspace, size_t workspace_bytes,
                    void *stream);
@@ -665,8 +668,10 @@ int rbgs_rb3_solve(const rbgs_grid *g, double *u, const double *f,
                    size_t workspace_bytes, void *stream);
 
 /* Kernel choice for the 3D calls (zero-initialise; NULL = all zero).
- * kernel: RBGS_KERNEL_AUTO or RBGS_KERNEL_PLAIN = one launch per half-sweep
- * (a device-wide barrier between colours, Algorithm 1's structure);
+ * kernel: RBGS_KERNEL_AUTO or RBGS_KERNEL_PLAIN = passes of up to two sweeps,
+ * one launch each (a device-wide barrier between passes); a launch per
+ * half-sweep (Algorithm 1's structure) where there is no room for the passes'
+ * second black array, and for a round of a single sweep; the same bits.
  * RBGS_KERNEL_RESIDENT = the flag-driven form, the dependency rule of
  * Algorithm 2 (Section 2.3) carried to 3D: all half-sweeps of a call in one
  * cooperative launch of co-resident one-wave workgroups, the interior cut

@@ -861,6 +861,8 @@ struct Rb3Workspace {
     double* sums = nullptr;  // sum r^2, sum b^2; the graph rounds' state at +64 bytes
     int* state = nullptr;    // flag-driven form: error word, ticket at +32 ints, block
                              // counters from +64 ints
+    size_t base = 0;         // bytes up to here: every form but the fused passes
+    double* u2_black = nullptr;  // the fused passes' second black array
     size_t total = 0;
 };
 
@@ -893,6 +895,8 @@ Rb3Workspace plan_rb3(const rbgs_grid* g, char* base) {
     w.partials = take(size_t(rb3_residual_blocks(g->n)) * 2 * sizeof(double));
     w.sums = take(256);
     w.state = reinterpret_cast<int*>(take(256 + size_t(kRb3MaxBlocks) * sizeof(int)));
+    w.base = off;
+    w.u2_black = take(colour);
     w.total = off;
     return w;
 }
@@ -903,22 +907,58 @@ int rb3_prepare(const rbgs_grid* g, const void* u, const void* f, void* ws, size
     if (!valid_grid3(g, &why)) return fail(RBGS_EINVAL, why);
     Rb3Workspace plan = plan_rb3(g, nullptr);
     int rc;
-    if ((rc = check_workspace(ws, ws_bytes, plan.total))) return rc;
+    // a workspace without the second black array still serves: the sweeps
+    // then run as a launch per half-sweep
+    const bool second = ws_bytes >= plan.total;
+    if ((rc = check_workspace(ws, ws_bytes, second ? plan.total : plan.base))) return rc;
     if ((rc = check_device_range(u, grid3_bytes(g), "u"))) return rc;
     if ((rc = check_device_range(f, grid3_bytes(g), "f"))) return rc;
     *w = plan_rb3(g, static_cast<char*>(ws));
+    if (!second) w->u2_black = nullptr;
     return RBGS_OK;
 }
 
+// Packs u and f; start = 1: black goes into the second array (an odd number
+// of fused passes ends in the first).  The ring is in both black arrays.
 int rb3_pack_both(const rbgs_grid* g, const Rb3Workspace& w, const double* u, const double* f,
-                  hipStream_t s) {
-    HIP_TRY(launch_rb3_pack(u, g->ld, w.u_red, w.u_black, g->n, w.pitch, s), "pack u");
-    HIP_TRY(launch_rb3_pack(f, g->ld, w.f_red, w.f_black, g->n, w.pitch, s), "pack f");
+                  hipStream_t s, int start = 0) {
+    HIP_TRY(launch_rb3_pack(u, g->ld, w.u_red, start ? w.u2_black : w.u_black, g->n, w.pitch, s,
+                            start ? w.u_black : w.u2_black),
+            "pack u");
+    HIP_TRY(launch_rb3_pack(f, g->ld, w.f_red, w.f_black, g->n, w.pitch, s, nullptr, true),
+            "pack f");
     return RBGS_OK;
 }
 
+// Fused passes of nsweeps sweeps at most kRb3MaxFuse deep; even: an even
+// number, so that black ends where it started, if nsweeps allows one.
+int rb3_passes(int nsweeps, bool even) {
+    int p = nsweeps / kRb3MaxFuse + (nsweeps % kRb3MaxFuse ? 1 : 0);
+    if (even && (p & 1) && nsweeps > p) ++p;
+    return p;
+}
+
+// The passes; black starts in u2_black (start = 1) or u_black (0).
+int rb3_sweeps_fused(const rbgs_grid* g, const Rb3Workspace& w, int nsweeps, int passes, int start,
+                     hipStream_t s, const int* stop) {
+    for (int p = 0; p < passes; ++p) {
+        const int k = nsweeps / passes + (p < nsweeps % passes ? 1 : 0);
+        const bool second = ((p + start) & 1) != 0;
+        HIP_TRY(launch_rb3_pass(second ? w.u2_black : w.u_black, second ? w.u_black : w.u2_black,
+                                w.u_red, w.f_red, w.f_black, g->n, w.pitch, g->h * g->h, k,
+                                p == passes - 1, stop, s),
+                "3D pass");
+    }
+    return RBGS_OK;
+}
+
+// An even number of fused passes, or (no second array, a single sweep) a
+// launch per half-sweep.
 int rb3_sweeps(const rbgs_grid* g, const Rb3Workspace& w, int nsweeps, hipStream_t s,
                const int* stop) {
+    const int passes = rb3_passes(nsweeps, true);
+    if (w.u2_black && passes > 0 && passes % 2 == 0)
+        return rb3_sweeps_fused(g, w, nsweeps, passes, 0, s, stop);
     const double h2 = g->h * g->h;
     for (int it = 0; it < nsweeps; ++it) {
         HIP_TRY(launch_rb3_half(w.u_red, w.u_black, w.f_red, g->n, w.pitch, h2, 0, stop, s),
@@ -1788,9 +1828,13 @@ int rbgs_rb3_sweep_ex(const rbgs_grid* g, double* u, const double* f, int32_t ns
     const bool flags = rb3_flag_driven(opts);
     int capacity = 0;
     if (flags && (rc = rb3_flags_setup(g, opts, w, s, &capacity))) return rc;
-    if ((rc = rb3_pack_both(g, w, u, f, s))) return rc;
+    const bool fused = !flags && w.u2_black;
+    const int passes = rb3_passes(nsweeps, false), start = fused ? passes & 1 : 0;
+    if ((rc = rb3_pack_both(g, w, u, f, s, start))) return rc;
     if (flags)
         rc = rb3_sweeps_flags(g, w, nsweeps, opts, capacity, s);
+    else if (fused)
+        rc = rb3_sweeps_fused(g, w, nsweeps, passes, start, s, nullptr);
     else
         rc = rb3_sweeps(g, w, nsweeps, s, nullptr);
     if (rc) return rc;

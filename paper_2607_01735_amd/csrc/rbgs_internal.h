@@ -274,11 +274,30 @@ hipError_t launch_mc9_flags(double* const u[4], double* const f[4], int n, doubl
 // rb3_residual_blocks(n) partial pairs.
 int rb3_residual_blocks(int n);
 hipError_t launch_rb3_pack(const double* nat, int64_t ld, double* red, double* black, int n,
-                           int64_t pitch, hipStream_t s);
+                           int64_t pitch, hipStream_t s, double* ring = nullptr,
+                           bool zero_ring = false);
 hipError_t launch_rb3_unpack(double* nat, int64_t ld, const double* red, const double* black,
                              int n, int64_t pitch, hipStream_t s);
 hipError_t launch_rb3_half(double* self, const double* other, const double* f, int n,
                            int64_t pitch, double h2, int colour, const int* stop, hipStream_t s);
+// pass: `sweeps` (1 .. kRb3MaxFuse) whole sweeps of the iterate whose black is
+// b_in (sweep3d_fused.hip): black into b_out, which holds the ring of b_in,
+// and red, read on the ring only, into red when last.
+constexpr int kRb3MaxFuse = 2;
+struct Rb3PassArgs {
+    const double* b_in;
+    double* b_out;
+    double* red;
+    const double* f_red;
+    const double* f_black;
+    const int* stop;
+    int64_t pitch;
+    double h2;
+    int n, bands, qcore, jtiles, planes, last;
+};
+hipError_t launch_rb3_pass(const double* b_in, double* b_out, double* red, const double* f_red,
+                           const double* f_black, int n, int64_t pitch, double h2, int sweeps,
+                           bool last, const int* stop, hipStream_t s);
 // The flag-driven 3D form: `levels` half-sweeps (red first) of the split
 // iterate in one launch (levels x rb3_flags_blocks(n, capacity) < 2^31).
 // capacity: resident one-wave workgroups (rb3_flags_capacity(n)); ticket

@@ -32,10 +32,14 @@ constexpr int kThreads = 256;
 constexpr int kPlanes = 16;
 constexpr int kResidualBlocks = 2048;
 
+// ring (optional): black's points outside the interior go there too (the
+// fused passes' other black array).  zero_ring: the ring becomes 0 (f, whose
+// ring is not defined and not read).
 __global__ __launch_bounds__(kThreads) void k_rb3_pack(const double* __restrict__ nat, int64_t ld,
                                                        double* __restrict__ red,
-                                                       double* __restrict__ black, int n,
-                                                       int64_t pitch) {
+                                                       double* __restrict__ black,
+                                                       double* __restrict__ ring, int zero_ring,
+                                                       int n, int64_t pitch) {
     const int64_t q = int64_t(blockIdx.x) * kThreads + threadIdx.x;
     const int64_t j = blockIdx.y, i = blockIdx.z;
     if (q >= pitch) return;
@@ -45,8 +49,17 @@ __global__ __launch_bounds__(kThreads) void k_rb3_pack(const double* __restrict_
     double* odd_dst = ((i + j) & 1) ? red : black;
     const double* src = nat + row * ld;
     const int64_t k0 = 2 * q, k1 = 2 * q + 1;
-    even_dst[row * pitch + q] = k0 <= n + 1 ? src[k0] : 0.0;
-    odd_dst[row * pitch + q] = k1 <= n + 1 ? src[k1] : 0.0;
+    const bool row_in = !zero_ring || (i >= 1 && i <= n && j >= 1 && j <= n);
+    const int64_t lo = zero_ring ? 1 : 0, hi = zero_ring ? n : n + 1;
+    const double v0 = row_in && k0 >= lo && k0 <= hi ? src[k0] : 0.0;
+    const double v1 = row_in && k1 >= lo && k1 <= hi ? src[k1] : 0.0;
+    even_dst[row * pitch + q] = v0;
+    odd_dst[row * pitch + q] = v1;
+    if (ring) {
+        const int64_t k = ((i + j) & 1) ? k0 : k1;
+        if (i == 0 || i == n + 1 || j == 0 || j == n + 1 || k == 0 || k > n)
+            ring[row * pitch + q] = ((i + j) & 1) ? v0 : v1;
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void k_rb3_unpack(double* __restrict__ nat, int64_t ld,
@@ -416,9 +429,10 @@ int rb3_residual_blocks(int n) {
 }
 
 hipError_t launch_rb3_pack(const double* nat, int64_t ld, double* red, double* black, int n,
-                           int64_t pitch, hipStream_t s) {
+                           int64_t pitch, hipStream_t s, double* ring, bool zero_ring) {
     const dim3 grid(unsigned((pitch + kThreads - 1) / kThreads), unsigned(n + 2), unsigned(n + 2));
-    hipLaunchKernelGGL(k_rb3_pack, grid, dim3(kThreads), 0, s, nat, ld, red, black, n, pitch);
+    hipLaunchKernelGGL(k_rb3_pack, grid, dim3(kThreads), 0, s, nat, ld, red, black, ring,
+                       zero_ring ? 1 : 0, n, pitch);
     return hipGetLastError();
 }
 

@@ -451,8 +451,9 @@ def _kernel_code(kernel):
 
 def rbgs_mc9_sweep(u, f, nsweeps, h=None, kernel="auto", workspace=None, stream=None):
     """nsweeps four-colour sweeps of the 9-point system, in place (FP64);
-    kernel "auto" or "plain" (a launch per colour), or "resident" (the
-    flag-driven form: one launch, a counter per block; synchronises)."""
+    kernel "auto" (launches of two or three sweeps each), "plain" (a launch
+    per colour), or "resident" (the flag-driven form: one launch, a counter
+    per block; synchronises)."""
     grid, ws = _mc9_args(u, f, h, workspace)
     _check(_lib.rbgs_mc9_sweep(ctypes.byref(grid), _vp(u.data_ptr()), _vp(f.data_ptr()),
                                int(nsweeps), _kernel_code(kernel), _vp(ws.data_ptr()), ws.numel(),
@@ -522,8 +523,8 @@ def _rb3_opts(kernel="plain", debug_delay=0, debug_spin_limit=0, debug_stall_blo
 
 def rbgs_rb3_sweep(u, f, nsweeps, h=None, workspace=None, stream=None, kernel="plain", **debug):
     """nsweeps 3D red-black sweeps (7-point Laplacian), in place (FP64).
-    kernel "plain": one launch per half-sweep; "resident": the flag-driven
-    form (one launch, per-block progress counters; synchronises)."""
+    kernel "plain": launches of up to two sweeps each; "resident": the
+    flag-driven form (one launch, per-block progress counters; synchronises)."""
     grid, ws = _rb3_args(u, f, h, workspace)
     o = _rb3_opts(kernel, **debug)
     _check(_lib.rbgs_rb3_sweep_ex(ctypes.byref(grid), _vp(u.data_ptr()), _vp(f.data_ptr()),
