@@ -70,9 +70,13 @@ typedef enum {
 
 typedef enum {
     RBGS_KERNEL_AUTO = 0,    /* library choice, from measured time per sweep:
-                                PLAIN below 8 sweeps; else RESIDENT up to
-                                n = 384 (FP64) / 768 (FP32), PLAIN for FP32
-                                n < 1536, BLOCKED otherwise                    */
+                                launches of up to 4 - 6 sweeps over independent
+                                overlapping windows held in registers, up to
+                                n = 2300 (FP64) / 10000 (FP32) and for calls of
+                                few sweeps beyond; else BLOCKED.  With tuning or
+                                debug options set: PLAIN below 8 sweeps,
+                                RESIDENT up to n = 384 (FP64) / 768 (FP32),
+                                PLAIN for FP32 n < 1536, BLOCKED otherwise     */
     RBGS_KERNEL_PLAIN = 1,   /* one kernel launch per half-sweep (Algorithm 1's
                                 barrier after every colour)                     */
     RBGS_KERNEL_BLOCKED = 2, /* persistent, temporally blocked kernel: several

@@ -26,6 +26,35 @@ __global__ __launch_bounds__(kThreads) void k_pack(const W* __restrict__ nat, in
     odd_dst[i * pitch + q] = (j1 <= n + 1) ? row[j1] : W(0);
 }
 
+// k_pack of u (blockIdx.z 0; the ring's points go to the second buffer too)
+// and of f (blockIdx.z 1).
+template <typename W>
+__global__ __launch_bounds__(kThreads) void k_pack_grid(const W* __restrict__ u,
+                                                        const W* __restrict__ f, int64_t ld,
+                                                        W* __restrict__ red, W* __restrict__ black,
+                                                        W* __restrict__ ring_red,
+                                                        W* __restrict__ ring_black,
+                                                        W* __restrict__ f_red,
+                                                        W* __restrict__ f_black, int n,
+                                                        int64_t pitch) {
+    const int64_t q = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    const int64_t i = blockIdx.y;
+    if (q >= pitch) return;
+    const bool is_f = blockIdx.z != 0, odd = (i & 1) != 0;
+    const int64_t j0 = 2 * q, j1 = 2 * q + 1, at = i * pitch + q, n1 = int64_t(n) + 1;
+    const W* row = (is_f ? f : u) + i * ld;
+    const W v0 = j0 <= n1 ? row[j0] : W(0), v1 = j1 <= n1 ? row[j1] : W(0);
+    W* r = is_f ? f_red : red;
+    W* b = is_f ? f_black : black;
+    r[at] = odd ? v1 : v0;
+    b[at] = odd ? v0 : v1;
+    if (is_f) return;
+    const bool row_ring = i == 0 || i == n1;
+    const bool ring0 = row_ring || j0 == 0 || j0 >= n1, ring1 = row_ring || j1 >= n1;
+    if (odd ? ring1 : ring0) ring_red[at] = odd ? v1 : v0;
+    if (odd ? ring0 : ring1) ring_black[at] = odd ? v0 : v1;
+}
+
 // The Dirichlet ring of a split grid, both colours: rows 0 and n+1 whole,
 // and in every other row the q-columns 0 and (n+1)/2, which hold j = 0 and
 // j = n+1 in one of the two colours (the other colour's interior point at
@@ -121,6 +150,25 @@ hipError_t launch_pack(const void* nat, int64_t ld, void* red, void* black, int 
         hipLaunchKernelGGL(k_pack<uint32_t>, grid, dim3(kThreads), 0, s,
                            static_cast<const uint32_t*>(nat), ld, static_cast<uint32_t*>(red),
                            static_cast<uint32_t*>(black), n, pitch);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_grid(const void* u, const void* f, int64_t ld, void* red, void* black,
+                            void* ring_red, void* ring_black, void* f_red, void* f_black, int n,
+                            int64_t pitch, int elem_bytes, hipStream_t s) {
+    const dim3 grid(unsigned((pitch + kThreads - 1) / kThreads), unsigned(n + 2), 2);
+    auto go = [&](auto word) {
+        using W = decltype(word);
+        hipLaunchKernelGGL(k_pack_grid<W>, grid, dim3(kThreads), 0, s, static_cast<const W*>(u),
+                           static_cast<const W*>(f), ld, static_cast<W*>(red),
+                           static_cast<W*>(black), static_cast<W*>(ring_red),
+                           static_cast<W*>(ring_black), static_cast<W*>(f_red),
+                           static_cast<W*>(f_black), n, pitch);
+    };
+    if (elem_bytes == 8)
+        go(uint64_t());
+    else
+        go(uint32_t());
     return hipGetLastError();
 }
 

@@ -54,6 +54,11 @@ hipError_t launch_pack(const void* nat, int64_t ld, void* red, void* black, int 
                        int64_t pitch, int elem_bytes, hipStream_t s);
 hipError_t launch_unpack(void* nat, int64_t ld, const void* red, const void* black, int n,
                          int64_t pitch, int elem_bytes, hipStream_t s);
+// u into red/black, its ring also into ring_red/ring_black, and f into
+// f_red/f_black (all split, one pitch), in one launch.
+hipError_t launch_pack_grid(const void* u, const void* f, int64_t ld, void* red, void* black,
+                            void* ring_red, void* ring_black, void* f_red, void* f_black, int n,
+                            int64_t pitch, int elem_bytes, hipStream_t s);
 // Convert a natural FP64 array to split FP32 (round to nearest even).
 hipError_t launch_pack_f64_to_f32(const double* nat, int64_t ld, float* red, float* black,
                                   int n, int64_t pitch, hipStream_t s);
@@ -66,6 +71,27 @@ template <typename T>
 hipError_t launch_half_sweep(T* self, const T* other, const T* f_self, int n, int64_t pitch,
                              T h2, int colour, int rows_per_block, hipStream_t s,
                              const int* stop = nullptr, T omega = T(1));
+
+// `sweeps` (1 .. window_fuse) whole sweeps from buffer `in` to buffer `out`,
+// red then black (sweep_window.hip): black always, red when last; in's red is
+// read on the ring only; both buffers hold the ring.  Small and middle-sized
+// grids.
+template <typename T>
+struct WindowArgs {
+    const T* in[2];
+    T* out[2];
+    const T* f[2];
+    const int* stop;
+    int64_t pitch;
+    T h2;
+    T omega;  // != 1: red-black SOR (FP64), red read and written by every pass
+    int n, last;
+    int bands;  // filled by launch_window
+};
+bool window_takes(int n, size_t elem_bytes, int nsweeps);  // whether it is the choice
+int window_fuse(int n, size_t elem_bytes);  // most sweeps a launch
+template <typename T>
+hipError_t launch_window(const WindowArgs<T>& a, int sweeps, hipStream_t s);
 
 // Number of partial-sum slots the residual kernels need for grid size n.
 int residual_partial_slots(int n, int64_t pitch, size_t elem_bytes);
