@@ -6,18 +6,18 @@
 // grids N_l = (N_{l-1} + 1)/F - 1 (coarsening factor F = 2 or 4) with
 // 16/32/64/128 channels; each encoder level is conv3x3+ReLU twice, levels
 // are linked by the averaging restriction R; each decoder level
-// concatenates the bilinear prolongation P = F^2 R^T of the level below with
-// the encoder's output of its own level and applies conv3x3+ReLU twice; a
+// takes the bilinear prolongation P = F^2 R^T of the level below beside
+// the encoder's output of its own level (the concatenation) and applies conv3x3+ReLU twice; a
 // 1x1 head gives y, and u0 = y * rms(f).  With F = 4 the coarsest level's
 // 3x3 convolutions span the whole grid (N = 511: levels 511, 127, 31, 7).
 // The restriction/prolongation pair is the multigrid transfer pair, fixed
 // (no weights).  Loss: mean squared error against u*/rms(f).
 //
 // Tensors are NHWC (batch, row, column, channel) in bfloat16; a tensor view
-// has a pixel stride (channels per pixel of its buffer), so an encoder
-// output is written straight into the channel slice of the decoder's
-// concatenation buffer.  Convolutions are implicit GEMMs on the 16x16x16
-// BF16 MFMA: pixels x output channels, K = 9 taps x input channels.
+// has a pixel stride (channels per pixel of its buffer).  The two halves of
+// a decoder's concatenated input stay two tensors that the kernels read as
+// one.  Convolutions are implicit GEMMs on the BF16 MFMA: pixels x output
+// channels, K = 9 taps x input channels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,118 +47,316 @@ __device__ __forceinline__ bf16 f2bf(float x) {
 }
 
 // ---------------------------------------------------------------------------
-// 3x3 convolution, stride 1, zero padding 1, as an implicit GEMM.
-// One wave computes kConvGroups x 16 consecutive pixels of one row for all
-// output channels (NT tiles of 16), as D[co][pixel] = sum_k W[co][k]
-// X[k][pixel], K = 9 taps x input channels.  MFMA 16x16x16 lane layout
-// (checked on the device):
+// 3x3 convolution, stride 1, zero padding 1, as an implicit GEMM:
+// D[co][pixel] = sum_k W[co][k] X[k][pixel], K = 9 taps x input channels, on
+// 16 x 16 x 16 BF16 MFMAs.  Lane layout (checked on the device):
 //   A[m][k]: lane l holds m = l%16, k = 4(l/16)+j;  B[k][n]: n = l%16,
 //   k = 4(l/16)+j;  D[m][n]: lane l holds m = 4(l/16)+i, n = l%16.
 // So a lane loads four consecutive input channels of one pixel (B) and of
 // one output channel's weights (A), 8 bytes each, and stores four
-// consecutive output channels of one pixel, 8 bytes.  Each weight operand
-// is loaded once per wave and used for every pixel group.
+// consecutive output channels of one pixel.  Every kernel below adds to an
+// output in the same order (16-channel chunks, in each the kernel rows, in
+// each the columns, one MFMA each), so an activation has the same bits
+// whichever computes it; K is therefore neither split over waves nor taken
+// 32 at a time.
 // X may be masked: an input element counts as 0 where mask <= 0 (this is
-// how the backward pass applies the ReLU derivative of the layer output).
+// how the backward pass applies the ReLU derivative of the layer output; the
+// mask is a ReLU's output, so it holds no NaN).  Input and output channels
+// may lie in two tensors (a decoder level's input is the prolongation of the
+// level below beside the encoder's output; two tensors, so that each is read
+// and written in whole lines).
 // ---------------------------------------------------------------------------
+constexpr int kConvGroups = 2;  // 16-pixel groups of a k_conv_march wave
+
 struct ConvArgs {
-    const bf16* x;
-    int64_t xs;        // pixel stride of x (channels of its buffer)
+    const bf16* x;     // input channels [0, xsplit), pixel stride xs
+    int64_t xs;
+    const bf16* x2;    // input channels [xsplit, cin), pixel stride xs2
+    int64_t xs2;
     const bf16* mask;  // optional, same geometry as x, stride ms
     int64_t ms;
-    const bf16* w;     // [cout][9][cin]
+    const bf16* w;     // [cout / 16][cin / 16][9][64 lanes][4], as the A operands lie
     const float* bias; // optional
-    bf16* y;
+    bf16* y;           // output channels [0, ysplit), pixel stride ys
     int64_t ys;
-    int batch, h, wd, cin, cout, relu;
+    bf16* y2;          // output channels [ysplit, cout), pixel stride ys2
+    int64_t ys2;
+    int batch, h, wd, cin, cout, relu, xsplit, ysplit;
+    int rows;          // k_conv_march: rows of a wave
 };
 
-constexpr int kConvGroups = 2;  // 16-pixel groups per wave
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ bf16x4 load4(const bf16* p) {
-    // four consecutive channels: 8 bytes, 8-byte aligned (channel strides
-    // and offsets are multiples of 4)
-    return *reinterpret_cast<const bf16x4*>(p);
+__device__ __forceinline__ f32x4 mfma16(u32x2 a, u32x2 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, a),
+                                                     __builtin_bit_cast(bf16x4, b), c, 0, 0, 0);
 }
 
-template <int NT, bool MASK>
-__global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
+// all ones in the halves of m that are > 0 (as a BF16 that is no NaN)
+__device__ __forceinline__ uint32_t positive(uint32_t m) {
+    const s16x2 v = __builtin_bit_cast(s16x2, m);
+    const s16x2 one = {1, 1}, zero = {0, 0};
+    return __builtin_bit_cast(
+        uint32_t, s16x2(zero - __builtin_elementwise_min(__builtin_elementwise_max(v, zero), one)));
+}
+
+template <int CTRL>
+__device__ __forceinline__ u32x2 dpp(u32x2 old, u32x2 v) {
+    return u32x2{uint32_t(__builtin_amdgcn_update_dpp(int(old[0]), int(v[0]), CTRL, 0xf, 0xf, false)),
+                 uint32_t(__builtin_amdgcn_update_dpp(int(old[1]), int(v[1]), CTRL, 0xf, 0xf, false))};
+}
+
+__device__ __forceinline__ void store_pixel(const ConvArgs& a, int64_t pix, int co, f32x4 v,
+                                            f32x4 bias) {
+    bf16x4 out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float r = v[i] + bias[i];
+        if (a.relu) r = r > 0.f ? r : 0.f;
+        out[i] = short(f2bf(r));
+    }
+    bf16* p = co < a.ysplit ? a.y + pix * a.ys + co : a.y2 + pix * a.ys2 + (co - a.ysplit);
+    *reinterpret_cast<bf16x4*>(p) = out;
+}
+
+// Four channels of PG x 16 pixels of a row and of the two pixels beside
+// them, as loaded: of group g's pixels, then (lanes n < 8) the pixel before
+// the strip or (the others) the one after it.
+template <int PG>
+struct RowPixels {
+    u32x2 v[PG + 1];
+};
+
+// A wave's pixels in a row; outside the grid they read a pixel inside and
+// are zeroed.
+template <int PG>
+struct RowLanes {
+    int px[PG + 1];
+    uint32_t ok[PG + 1];
+    __device__ RowLanes(int x0, int n, int wd) {
+#pragma unroll
+        for (int g = 0; g <= PG; ++g) {
+            const int x = g < PG ? x0 + g * 16 + n : (n < 8 ? x0 - 1 : x0 + 16 * PG);
+            ok[g] = x >= 0 && x < wd ? ~0u : 0u;
+            px[g] = x < 0 ? 0 : x < wd ? x : wd - 1;
+        }
+    }
+    __device__ void load(RowPixels<PG>& r, const bf16* p, uint32_t stride, uint32_t ch) const {
+#pragma unroll
+        for (int g = 0; g <= PG; ++g)
+            r.v[g] = *reinterpret_cast<const u32x2*>(p + (uint32_t(px[g]) * stride + ch));
+    }
+    // The B operands of the three taps of a kernel row: the pixels shifted
+    // by a lane either way (DPP), op[column * step + group].
+    template <bool MASK>
+    __device__ void taps(const RowPixels<PG>& r, const RowPixels<PG>& m, uint32_t row_ok, u32x2* op,
+                         int step) const {
+        u32x2 v[PG + 1];
+#pragma unroll
+        for (int g = 0; g <= PG; ++g) {
+            v[g] = r.v[g] & (ok[g] & row_ok);
+            if (MASK) {
+                v[g][0] &= positive(m.v[g][0]);
+                v[g][1] &= positive(m.v[g][1]);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < PG; ++g) {
+            const u32x2 zero = {0u, 0u};
+            // row_ror:1 / row_ror:15 bring the neighbouring group's edge pixel
+            const u32x2 lo = g == 0 ? v[PG] : dpp<0x121>(zero, v[g ? g - 1 : 0]);
+            const u32x2 hi = g == PG - 1 ? v[PG] : dpp<0x12f>(zero, v[g + 1]);
+            op[g] = dpp<0x111>(lo, v[g]);             // row_shr:1
+            op[step + g] = v[g];
+            op[2 * step + g] = dpp<0x101>(hi, v[g]);  // row_shl:1
+        }
+    }
+};
+
+// Few channels, many pixels (cin = 16 or 48: the finest level, and the first
+// convolution of the next).  Bound by memory: 16 -> 16 channels moves 64
+// bytes a pixel for 9 MFMAs per 16 pixels.  So every input element is loaded
+// once: a wave takes kConvGroups x 16 pixels of `rows` rows and walks down
+// them with the layer's weights and the operands of three rows in registers.
+// A row is loaded three rows ahead of its use, 8 bytes a lane, a whole
+// 512-byte line per 16 pixels and chunk.  511^2 x 8: 16 -> 16 channels 33 us
+// (134 MB, 4.1 TB/s), 48 -> 16 72 us, masked 16 -> 16 42 us, 16 -> 48 90 us;
+// a wave per 32 outputs of a row, which loaded three rows three times over
+// behind its loads of weights, took 86, 255, 109 and 194 us.
+template <int CK, int NT, bool MASK>
+__global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     constexpr int PG = kConvGroups;
     const int lane = threadIdx.x & 63;
-    const int wave = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
+    int wave = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
+    const int strips = (a.wd + 16 * PG - 1) / (16 * PG);
+    const int bands = (a.h + a.rows - 1) / a.rows;
+    if (wave >= a.batch * bands * strips) return;
+    wave = __builtin_amdgcn_readfirstlane(wave);
+    const int x0 = (wave % strips) * 16 * PG;
+    const int band = (wave / strips) % bands;
+    const int b = wave / (strips * bands);
+    const int y0 = band * a.rows, y1 = y0 + a.rows < a.h ? y0 + a.rows : a.h;
+    const int n = lane & 15, kq = (lane >> 4) * 4;
+
+    u32x2 w[CK][9][NT];
+#pragma unroll
+    for (int c = 0; c < CK; ++c)
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                w[c][k][t] = *reinterpret_cast<const u32x2*>(
+                    a.w + (((t * CK + c) * 9 + k) * 64 + lane) * 4);
+    f32x4 bias[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bias[t][i] = a.bias ? a.bias[t * 16 + kq + i] : 0.f;
+
+    const RowLanes<PG> lanes(x0, n, a.wd);
+    RowPixels<PG> raw[3][CK], msk[3][CK];
+    auto fetch = [&](int slot, int row) {
+        const int64_t pix = int64_t(b * a.h + (row < 0 ? 0 : row < a.h ? row : a.h - 1)) * a.wd;
+#pragma unroll
+        for (int c = 0; c < CK; ++c) {
+            if (c * 16 < a.xsplit)
+                lanes.load(raw[slot][c], a.x + pix * a.xs + c * 16, uint32_t(a.xs), uint32_t(kq));
+            else
+                lanes.load(raw[slot][c], a.x2 + pix * a.xs2 + (c * 16 - a.xsplit), uint32_t(a.xs2),
+                           uint32_t(kq));
+            if (MASK)
+                lanes.load(msk[slot][c], a.mask + pix * a.ms + c * 16, uint32_t(a.ms), uint32_t(kq));
+        }
+    };
+    u32x2 op[3][CK][3 * PG];  // three input rows' operands
+#pragma unroll
+    for (int k = 0; k < 3; ++k) fetch(k, y0 - 1 + k);
+    for (int base = y0 - 1; base <= y1; base += 3) {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int yi = base + u;  // input row, slot u; completes output row yi - 1
+            const uint32_t row_ok = yi >= 0 && yi < a.h ? ~0u : 0u;
+#pragma unroll
+            for (int c = 0; c < CK; ++c)
+                lanes.template taps<MASK>(raw[u][c], msk[u][c], row_ok, op[u][c], PG);
+            fetch(u, yi + 3);
+            if (yi - 1 < y0 || yi > y1) continue;
+            f32x4 acc[PG][NT];
+#pragma unroll
+            for (int g = 0; g < PG; ++g)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < CK; ++c)
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+#pragma unroll
+                    for (int g = 0; g < PG; ++g)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[g][t] = mfma16(w[c][k][t], op[(u + 1 + k / 3) % 3][c][(k % 3) * PG + g],
+                                               acc[g][t]);
+            const int64_t pix = int64_t(b * a.h + yi - 1) * a.wd;
+#pragma unroll
+            for (int g = 0; g < PG; ++g)
+                if (lanes.ok[g])
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        store_pixel(a, pix + lanes.px[g], t * 16 + kq, acc[g][t], bias[t]);
+        }
+    }
+}
+
+// Many channels, fewer pixels (cin a multiple of 32: the coarser levels).
+// D divides the number of chunks.  Bound by latency: an output's 9 cin / 16 MFMAs are a chain of at most 108,
+// under a microsecond, but each group of them waits for its loads.  So a
+// wave takes few outputs (PG x 16 pixels, NT x 16 channels) and keeps the
+// operands of D chunks in flight, which it reads in the order of the chain.
+// 8 samples: 128 -> 128 at 7^2 9 us, 64 -> 64 at 31^2 9 us, 192 -> 64 there
+// 21 us, 96 -> 32 at 127^2 37 us (one chunk and kernel row at a time: 82, 36,
+// 93 and 69 us).
+template <int PG, int NT, int D, bool MASK>
+__global__ __launch_bounds__(256) void k_conv_deep(ConvArgs a) {
+    const int lane = threadIdx.x & 63;
     const int segs = (a.wd + 16 * PG - 1) / (16 * PG);
-    if (wave >= a.batch * a.h * segs) return;
-    const int seg = wave % segs;
-    const int rowb = wave / segs;  // sample * h + row
-    const int row = rowb % a.h;
-    const int b = rowb / a.h;
-    const int x0 = seg * 16 * PG;
+    const int cts = a.cout / (16 * NT);
+    int r = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
+    if (r >= a.batch * a.h * segs * cts) return;
+    r = __builtin_amdgcn_readfirstlane(r);
+    const int ct = r % cts;
+    r /= cts;
+    const int x0 = (r % segs) * 16 * PG;
+    r /= segs;
+    const int row = r % a.h, b = r / a.h;
+    const int n = lane & 15, kq = (lane >> 4) * 4;
+    const int chunks = a.cin / 16;
+    const RowLanes<PG> lanes(x0, n, a.wd);
+    RowPixels<PG> raw[D][3], msk[D][3];
+    u32x2 w[D][9][NT];
+    int64_t pix[3];
+    uint32_t row_ok[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int yy = row + d - 1;
+        row_ok[d] = yy >= 0 && yy < a.h ? ~0u : 0u;
+        pix[d] = int64_t(b * a.h + (row_ok[d] ? yy : row)) * a.wd;
+    }
+    const bf16* wbase = a.w + int64_t(ct * NT) * chunks * 9 * 256;
+    auto fetch = [&](int slot, int c) {
+        const int c0 = c * 16;
+        const bool first = c0 < a.xsplit;
+        const bf16* xb = first ? a.x + c0 : a.x2 + (c0 - a.xsplit);
+        const int64_t st = first ? a.xs : a.xs2;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            lanes.load(raw[slot][d], xb + pix[d] * st, uint32_t(st), uint32_t(kq));
+            if (MASK) lanes.load(msk[slot][d], a.mask + pix[d] * a.ms + c0, uint32_t(a.ms), uint32_t(kq));
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                w[slot][k][t] = *reinterpret_cast<const u32x2*>(
+                    wbase + uint32_t((((t * chunks + c) * 9 + k) * 64 + lane) * 4));
+    };
     f32x4 acc[PG][NT];
 #pragma unroll
     for (int g = 0; g < PG; ++g)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int n = lane & 15, kq = (lane >> 4) * 4;
-    // Per 16-channel chunk and kernel row: the three taps' input operands
-    // are loaded first (pixels outside the grid read a pixel inside and are
-    // zeroed after the load, so no load sits behind a branch and they are in
-    // flight together), then each output tile's three weight operands and
-    // MFMAs.
-    for (int c0 = 0; c0 < a.cin; c0 += 16) {
-#pragma unroll 1
-        for (int d = 0; d < 3; ++d) {
-            const int yy = row + d - 1;
-            const bool rowok = yy >= 0 && yy < a.h;
-            const int64_t rbase = int64_t(b * a.h + (rowok ? yy : row)) * a.wd;
-            bf16x4 xv[3][PG];
 #pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
+    for (int k = 0; k < D; ++k) fetch(k, k);
+    for (int base = 0; base < chunks; base += D) {
 #pragma unroll
-                for (int g = 0; g < PG; ++g) {
-                    const int xx = x0 + g * 16 + n + dx - 1;
-                    const bool ok = rowok && xx >= 0 && xx < a.wd;
-                    const int64_t pix = rbase + (ok ? xx : 0);
-                    bf16x4 v = load4(a.x + pix * a.xs + c0 + kq);
-                    if (MASK) {
-                        const bf16x4 mv = load4(a.mask + pix * a.ms + c0 + kq);
+        for (int u = 0; u < D; ++u) {
+            const int c = base + u + D;  // the chunk loaded next
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (!(bf2f(bf16(mv[j])) > 0.f)) v[j] = 0;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) xv[dx][g][j] = ok ? v[j] : short(0);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const bf16* pw = a.w + (int64_t(t * 16 + n) * 9 + d * 3) * a.cin + c0 + kq;
-                bf16x4 wv[3];
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx) wv[dx] = load4(pw + dx * a.cin);
+            for (int d = 0; d < 3; ++d) {
+                u32x2 op[3 * PG];
+                lanes.template taps<MASK>(raw[u][d], msk[u][d], row_ok[d], op, PG);
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
                     for (int g = 0; g < PG; ++g)
-                        acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wv[dx], xv[dx][g], acc[g][t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[g][t] = mfma16(w[u][d * 3 + dx][t], op[dx * PG + g], acc[g][t]);
             }
+            fetch(u, c < chunks ? c : chunks - 1);
         }
     }
 #pragma unroll
-    for (int g = 0; g < PG; ++g) {
-        const int xx = x0 + g * 16 + n;
-        if (xx >= a.wd) continue;
-        bf16* py = a.y + (int64_t(b * a.h + row) * a.wd + xx) * a.ys + kq;
+    for (int t = 0; t < NT; ++t) {
+        const int co = (ct * NT + t) * 16 + kq;
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if (a.bias)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            bf16x4 out;
+            for (int i = 0; i < 4; ++i) bias[i] = a.bias[co + i];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float v = acc[g][t][i] + (a.bias ? a.bias[t * 16 + kq + i] : 0.f);
-                if (a.relu) v = v > 0.f ? v : 0.f;
-                out[i] = short(f2bf(v));
-            }
-            *reinterpret_cast<bf16x4*>(py + t * 16) = out;
-        }
+        for (int g = 0; g < PG; ++g)
+            if (lanes.ok[g])
+                store_pixel(a, int64_t(b * a.h + row) * a.wd + lanes.px[g], co, acc[g][t], bias);
     }
 }
 
@@ -174,8 +372,11 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
 // [tap]); k_reduce_parts adds the slots in a fixed order, so the gradient
 // has the same bits on every run.
 struct WGradArgs {
-    const bf16* x;
+    const bf16* x;     // input channels [0, xsplit), pixel stride xs
     int64_t xs;
+    const bf16* x2;    // input channels [xsplit, cin), pixel stride xs2
+    int64_t xs2;
+    int xsplit;
     const bf16* dy;
     int64_t dys;
     const bf16* y;  // layer output (mask), stride ys
@@ -207,13 +408,16 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WGradArgs a) {
         const int64_t prow = (int64_t(b) * a.h + row) * a.wd;  // first pixel of the row
         const bf16* ym = a.y + prow * a.ys + co_t * 16 + l16;
         const bf16* dym = a.dy + prow * a.dys + co_t * 16 + l16;
+        const bool first = ci_t * 16 < a.xsplit;
+        const bf16* xbase = first ? a.x + ci_t * 16 : a.x2 + (ci_t * 16 - a.xsplit);
+        const int64_t xs = first ? a.xs : a.xs2;
         const bf16* xr[3];
         bool rok[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const int yy = row + d - 1;
             rok[d] = yy >= 0 && yy < a.h;
-            xr[d] = a.x + ((int64_t(b) * a.h + (rok[d] ? yy : row)) * a.wd) * a.xs + ci_t * 16 + l16;
+            xr[d] = xbase + ((int64_t(b) * a.h + (rok[d] ? yy : row)) * a.wd) * xs + l16;
         }
         for (int x0 = 0; x0 < a.wd; x0 += 16) {
             const int xb = x0 + kq;  // this lane group's first pixel
@@ -232,7 +436,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WGradArgs a) {
 #pragma unroll
                 for (int m = 0; m < 6; ++m) {
                     const int xs2 = xb - 1 + m;
-                    xv[m] = (rok[d] && xs2 >= 0 && xs2 < a.wd) ? xr[d][int64_t(xs2) * a.xs] : bf16(0);
+                    xv[m] = (rok[d] && xs2 >= 0 && xs2 < a.wd) ? xr[d][int64_t(xs2) * xs] : bf16(0);
                 }
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) {
@@ -661,19 +865,42 @@ __global__ __launch_bounds__(256) void k_head_grad(const bf16* d, int64_t ds, co
             ((sw[0][threadIdx.x] + sw[1][threadIdx.x]) + sw[2][threadIdx.x]) + sw[3][threadIdx.x];
 }
 
-// Master FP32 weights [co][ci][9] -> forward BF16 [co][9][cin_p] (zero-padded
-// input channels) and backward-data BF16 [ci][9][co] with the taps flipped.
-__global__ __launch_bounds__(256) void k_prep_weights(const float* w, int cout, int cin, int cin_p,
-                                                      bf16* wf, bf16* wb) {
-    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t total = int64_t(cout) * cin_p * 9;
-    if (idx >= total) return;
-    const int ci = int(idx % cin_p);
-    const int tap = int((idx / cin_p) % 9);
-    const int co = int(idx / (int64_t(cin_p) * 9));
-    const float v = ci < cin ? w[(int64_t(co) * cin + ci) * 9 + tap] : 0.f;
-    wf[(int64_t(co) * 9 + tap) * cin_p + ci] = f2bf(v);
-    if (wb && ci < cin) wb[(int64_t(ci) * 9 + (8 - tap)) * cout + co] = f2bf(v);
+// Master FP32 weights [co][ci][9] -> BF16 operands of the convolutions:
+// forward (input channels zero-padded to cin_p), and backward-data (rows ci,
+// columns co, taps flipped; not for the first layer, whose input has no
+// gradient).  An operand is one 512-byte line, [tile of 16 rows][chunk of 16
+// columns][tap][lane][4]: a lane's four columns of one row (ConvArgs); as
+// [row][tap][column] each 8-byte load touched 16 lines.  One launch for all
+// layers: a layer's elements start at block `first`.
+constexpr int kMaxLayers = 16;
+
+struct PrepArgs {
+    const float* param;
+    int layers;
+    struct {
+        size_t w_off;
+        bf16 *wf, *wb;
+        int cout, cin, cin_p, first;
+    } l[kMaxLayers];
+};
+
+__device__ __forceinline__ int64_t operand_index(int row, int tap, int col, int cols) {
+    const int lane = ((col & 15) >> 2) * 16 + (row & 15);
+    return (((int64_t(row >> 4) * (cols >> 4) + (col >> 4)) * 9 + tap) * 64 + lane) * 4 + (col & 3);
+}
+
+__global__ __launch_bounds__(256) void k_prep_weights(PrepArgs a) {
+    int k = a.layers - 1;
+    while (k > 0 && int(blockIdx.x) < a.l[k].first) --k;
+    const auto& L = a.l[k];
+    const int idx = (int(blockIdx.x) - L.first) * 256 + int(threadIdx.x);
+    if (idx >= L.cout * L.cin_p * 9) return;
+    const int ci = idx % L.cin_p;
+    const int tap = (idx / L.cin_p) % 9;
+    const int co = idx / (L.cin_p * 9);
+    const bf16 v = ci < L.cin ? f2bf(a.param[L.w_off + (int64_t(co) * L.cin + ci) * 9 + tap]) : bf16(0);
+    L.wf[operand_index(co, tap, ci, L.cin_p)] = v;
+    if (L.wb && ci < L.cin) L.wb[operand_index(ci, 8 - tap, co, L.cout)] = v;
 }
 
 // Adam: b1, b2 and their complements 1 - b1, 1 - b2 and the bias corrections
@@ -714,8 +941,8 @@ struct Layer {
     const char* name;
     int cin, cin_p, cout, level;
     size_t w_off, b_off;  // float offsets in the master parameter vector
-    bf16* wf = nullptr;   // [cout][9][cin_p]
-    bf16* wb = nullptr;   // [cin][9][cout] (flipped taps) for the input gradient
+    bf16* wf = nullptr;   // forward operands
+    bf16* wb = nullptr;   // operands of the input gradient (flipped taps)
 };
 
 // Parameter order and shapes: each conv's weight (cout, cin, 3, 3) then its
@@ -772,15 +999,16 @@ struct Net {
     double* guess;  // natural-layout scratch grid for the learned solve
     int adam_t = 0;
     // activations (level-indexed) and their gradients
-    bf16 *in[kLevels], *aenc[kLevels], *cat[kLevels - 1], *e3, *adec[kLevels - 1], *d[kLevels - 1];
-    bf16 *gd[kLevels - 1], *ge3, *gadec[kLevels - 1], *gcat[kLevels - 1], *gaenc[kLevels],
+    // (enc: the encoder's outputs; up: the prolongations beside them)
+    bf16 *in[kLevels], *aenc[kLevels], *enc[kLevels], *up[kLevels - 1], *adec[kLevels - 1],
+        *d[kLevels - 1];
+    bf16 *gd[kLevels - 1], *genc[kLevels], *gup[kLevels - 1], *gadec[kLevels - 1], *gaenc[kLevels],
         *gin[kLevels];
     size_t total = 0;
 };
 
 namespace {
 
-int cat_channels(int l) { return kC[l + 1] + kC[l]; }
 int in_channels(int l) { return l == 0 ? 16 : kC[l - 1]; }
 
 int wgrad_quads(int h) { return (h + kWgradRows - 1) / kWgradRows; }
@@ -840,16 +1068,15 @@ size_t carve(Net& net, char* base) {
         net.aenc[l] = act(kC[l]);
         net.gaenc[l] = act(kC[l]);
         net.gin[l] = act(in_channels(l));
+        net.enc[l] = act(kC[l]);
+        net.genc[l] = act(kC[l]);
         if (l < kLevels - 1) {
-            net.cat[l] = act(cat_channels(l));
-            net.gcat[l] = act(cat_channels(l));
+            net.up[l] = act(kC[l + 1]);
+            net.gup[l] = act(kC[l + 1]);
             net.adec[l] = act(kC[l]);
             net.gadec[l] = act(kC[l]);
             net.d[l] = act(kC[l]);
             net.gd[l] = act(kC[l]);
-        } else {
-            net.e3 = act(kC[l]);
-            net.ge3 = act(kC[l]);
         }
     }
     return off;
@@ -859,28 +1086,68 @@ unsigned blocks_for(int64_t items, int per_block = 256) {
     return unsigned((items + per_block - 1) / per_block);
 }
 
+// A convolution's channels in memory: one tensor, or two side by side.
+template <typename P>
+struct Channels {
+    P a;
+    int ca;  // channels (and pixel stride) of a
+    P b = nullptr;
+    int cb = 0;
+    int count() const { return ca + cb; }
+};
+typedef Channels<const bf16*> In;
+typedef Channels<bf16*> Out;
+
 template <bool MASK>
-hipError_t launch_conv(const ConvArgs& a, dim3 grid, dim3 block, hipStream_t s) {
-    switch (a.cout / 16) {
-        case 1: hipLaunchKernelGGL((k_conv3x3<1, MASK>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_conv3x3<2, MASK>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_conv3x3<3, MASK>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_conv3x3<4, MASK>), grid, block, 0, s, a); break;
-        case 6: hipLaunchKernelGGL((k_conv3x3<6, MASK>), grid, block, 0, s, a); break;
-        case 8: hipLaunchKernelGGL((k_conv3x3<8, MASK>), grid, block, 0, s, a); break;
-        case 12: hipLaunchKernelGGL((k_conv3x3<12, MASK>), grid, block, 0, s, a); break;
-        default: return hipErrorInvalidValue;
+hipError_t launch_march(const ConvArgs& a, dim3 grid, hipStream_t s) {
+    const int ck = a.cin / 16, nt = a.cout / 16;
+    const dim3 block(256);
+    if (ck == 1 && nt == 1) {
+        hipLaunchKernelGGL((k_conv_march<1, 1, MASK>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
+    // the other shapes occur in one direction each
+    if constexpr (MASK) {
+        if (ck != 1 || nt != 3) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_conv_march<1, 3, true>), grid, block, 0, s, a);
+    } else if (ck == 1 && nt == 2) {
+        hipLaunchKernelGGL((k_conv_march<1, 2, false>), grid, block, 0, s, a);
+    } else if (ck == 3 && nt == 1) {
+        hipLaunchKernelGGL((k_conv_march<3, 1, false>), grid, block, 0, s, a);
+    } else {
+        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t conv(const Net& net, const Layer& L, const bf16* x, int64_t xs, const bf16* mask,
-                int64_t ms, bool forward, bf16* y, int64_t ys, int batch, hipStream_t s) {
+template <bool MASK>
+hipError_t launch_deep(const ConvArgs& a, int pg, int nt, dim3 grid, hipStream_t s) {
+    const dim3 block(256);
+    const int chunks = a.cin / 16;
+    if (pg == 1 && nt == 1 && chunks % 4 == 0)
+        hipLaunchKernelGGL((k_conv_deep<1, 1, 4, MASK>), grid, block, 0, s, a);
+    else if (pg == 1 && nt == 1 && chunks % 2 == 0)
+        hipLaunchKernelGGL((k_conv_deep<1, 1, 2, MASK>), grid, block, 0, s, a);
+    else if (pg == 2 && nt == 1 && chunks % 4 == 0)
+        hipLaunchKernelGGL((k_conv_deep<2, 1, 4, MASK>), grid, block, 0, s, a);
+    else if (pg == 2 && nt == 1 && chunks % 2 == 0)
+        hipLaunchKernelGGL((k_conv_deep<2, 1, 2, MASK>), grid, block, 0, s, a);
+    else if (pg == 2 && nt == 2 && chunks % 2 == 0)
+        hipLaunchKernelGGL((k_conv_deep<2, 2, 2, MASK>), grid, block, 0, s, a);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool forward, Out y,
+                int batch, hipStream_t s) {
     ConvArgs a;
-    a.x = x;
-    a.xs = xs;
+    a.x = x.a;
+    a.xs = a.xsplit = x.ca;
+    a.x2 = x.b;
+    a.xs2 = x.cb;
     a.mask = mask;
-    a.ms = ms;
+    a.ms = x.ca;
     a.batch = batch;
     a.h = a.wd = net.n[L.level];
     if (forward) {
@@ -896,19 +1163,44 @@ hipError_t conv(const Net& net, const Layer& L, const bf16* x, int64_t xs, const
         a.cout = L.cin;
         a.relu = 0;
     }
-    a.y = y;
-    a.ys = ys;
-    const int64_t waves = int64_t(batch) * a.h * ((a.wd + 16 * kConvGroups - 1) / (16 * kConvGroups));
-    if (waves > (int64_t(1) << 31) - 4 || int64_t(batch) * a.h * a.wd >= (int64_t(1) << 31))
+    a.y = y.a;
+    a.ys = a.ysplit = y.ca;
+    a.y2 = y.b;
+    a.ys2 = y.cb;
+    if (x.count() != a.cin || y.count() != a.cout || (mask && x.b) ||
+        int64_t(batch) * a.h * a.wd >= (int64_t(1) << 31))
         return hipErrorInvalidValue;
-    // 8-byte operand loads and stores: channel strides, counts and base
-    // addresses in whole groups of four channels
-    if ((a.xs | a.ys | a.cin | (a.mask ? a.ms : 0)) % 4 != 0 || a.cout % 16 != 0 ||
-        (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.y) |
+    // whole chunks of 16 channels, in 8-byte loads and stores
+    if ((x.ca | x.cb | y.ca | y.cb) % 16 != 0 ||
+        (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.x2) |
+         reinterpret_cast<uintptr_t>(a.y) | reinterpret_cast<uintptr_t>(a.y2) |
          reinterpret_cast<uintptr_t>(a.w) | reinterpret_cast<uintptr_t>(a.mask)) % 8 != 0)
         return hipErrorInvalidValue;
-    const dim3 grid(blocks_for(waves, 4)), block(256);
-    return a.mask ? launch_conv<true>(a, grid, block, s) : launch_conv<false>(a, grid, block, s);
+    if (a.cin % 32 != 0) {
+        // Rows of a wave: two rows more are read than written, so as many as
+        // still leave four waves a SIMD on 256 CUs.
+        const int64_t strips = int64_t(batch) * ((a.wd + 16 * kConvGroups - 1) / (16 * kConvGroups));
+        // (Three rows a step of the kernel: rows + 2 a multiple of 3.)
+        a.rows = int(std::max<int64_t>(strips * a.h / 4096, 4));
+        a.rows -= (a.rows + 2) % 3;
+        const int64_t waves = strips * ((a.h + a.rows - 1) / a.rows);
+        if (waves > (int64_t(1) << 31) - 4) return hipErrorInvalidValue;
+        const dim3 grid(blocks_for(waves, 4));
+        return mask ? launch_march<true>(a, grid, s) : launch_march<false>(a, grid, s);
+    }
+    a.rows = 0;
+    // As many outputs a wave (up to 2 x 2 tiles, whose operands are loaded
+    // half as often) as leave a wave for every SIMD.
+    const auto count = [&](int pg, int nt) {
+        return int64_t(batch) * a.h * ((a.wd + 16 * pg - 1) / (16 * pg)) * (a.cout / (16 * nt));
+    };
+    int pg = 2, nt = 2;
+    if (count(pg, nt) < 1024) nt = 1;
+    if (count(pg, nt) < 1024) pg = 1;
+    const int64_t waves = count(pg, nt);
+    if (waves > (int64_t(1) << 31) - 4) return hipErrorInvalidValue;
+    const dim3 grid(blocks_for(waves, 4));
+    return mask ? launch_deep<true>(a, pg, nt, grid, s) : launch_deep<false>(a, pg, nt, grid, s);
 }
 
 // out[e] = sum over the nparts slots of net.parts[k * count + e] (two passes).
@@ -922,11 +1214,14 @@ hipError_t reduce_slots(const Net& net, int64_t nparts, int64_t count, float* ou
     return hipGetLastError();
 }
 
-hipError_t wgrad(const Net& net, const Layer& L, const bf16* x, int64_t xs, const bf16* dy,
-                 int64_t dys, const bf16* y, int64_t ys, int batch, hipStream_t s) {
+hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf16* y, int batch,
+                 hipStream_t s) {
+    const int64_t dys = L.cout, ys = L.cout;
     WGradArgs a;
-    a.x = x;
-    a.xs = xs;
+    a.x = x.a;
+    a.xs = a.xsplit = x.ca;
+    a.x2 = x.b;
+    a.xs2 = x.cb;
     a.dy = dy;
     a.dys = dys;
     a.y = y;
@@ -1012,12 +1307,18 @@ hipError_t prolong_op(const Net& net, const bf16* in, int64_t is, bf16* out, int
 }
 
 hipError_t prep_weights(Net& net, hipStream_t s) {
-    for (auto& l : net.layers) {
-        hipLaunchKernelGGL(k_prep_weights, dim3(blocks_for(int64_t(l.cout) * l.cin_p * 9)), dim3(256),
-                           0, s, net.param + l.w_off, l.cout, l.cin, l.cin_p, l.wf, l.wb);
-        NN_TRY(hipGetLastError());
+    PrepArgs a;
+    if (net.layers.size() > kMaxLayers) return hipErrorInvalidValue;
+    a.param = net.param;
+    a.layers = int(net.layers.size());
+    unsigned blocks = 0;
+    for (int k = 0; k < a.layers; ++k) {
+        const Layer& l = net.layers[size_t(k)];
+        a.l[k] = {l.w_off, l.wf, l.cin % 16 ? nullptr : l.wb, l.cout, l.cin, l.cin_p, int(blocks)};
+        blocks += blocks_for(int64_t(l.cout) * l.cin_p * 9);
     }
-    return hipSuccess;
+    hipLaunchKernelGGL(k_prep_weights, dim3(blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 const Layer& layer(const Net& net, const char* name) {
@@ -1047,25 +1348,24 @@ hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gst
         n0name[3] = n1name[3] = char('0' + l);
         const Layer& c0 = layer(net, n0name);
         const Layer& c1 = layer(net, n1name);
-        NN_TRY(conv(net, c0, net.in[l], in_channels(l), nullptr, 0, true, net.aenc[l], kC[l], batch, s));
-        bf16* e = l < kLevels - 1 ? net.cat[l] + kC[l + 1] : net.e3;
-        const int64_t es = l < kLevels - 1 ? cat_channels(l) : kC[l];
-        NN_TRY(conv(net, c1, net.aenc[l], kC[l], nullptr, 0, true, e, es, batch, s));
+        NN_TRY(conv(net, c0, In{net.in[l], in_channels(l)}, nullptr, true, Out{net.aenc[l], kC[l]},
+                    batch, s));
+        NN_TRY(conv(net, c1, In{net.aenc[l], kC[l]}, nullptr, true, Out{net.enc[l], kC[l]}, batch, s));
         if (l + 1 < kLevels)
-            NN_TRY(restrict_op(net, e, es, net.in[l + 1], in_channels(l + 1), batch, net.n[l + 1],
-                               kC[l], 1.f, 0, s));
+            NN_TRY(restrict_op(net, net.enc[l], kC[l], net.in[l + 1], in_channels(l + 1), batch,
+                               net.n[l + 1], kC[l], 1.f, 0, s));
     }
     // decoder
     for (int l = kLevels - 2; l >= 0; --l) {
-        const bf16* below = l == kLevels - 2 ? net.e3 : net.d[l + 1];
-        NN_TRY(prolong_op(net, below, kC[l + 1], net.cat[l], cat_channels(l), batch, net.n[l + 1],
+        const bf16* below = l == kLevels - 2 ? net.enc[l + 1] : net.d[l + 1];
+        NN_TRY(prolong_op(net, below, kC[l + 1], net.up[l], kC[l + 1], batch, net.n[l + 1],
                           kC[l + 1], 1.f, 0, s));
         char n0name[8] = "dec0.0", n1name[8] = "dec0.1";
         n0name[3] = n1name[3] = char('0' + l);
-        NN_TRY(conv(net, layer(net, n0name), net.cat[l], cat_channels(l), nullptr, 0, true,
-                    net.adec[l], kC[l], batch, s));
-        NN_TRY(conv(net, layer(net, n1name), net.adec[l], kC[l], nullptr, 0, true, net.d[l], kC[l],
-                    batch, s));
+        NN_TRY(conv(net, layer(net, n0name), In{net.up[l], kC[l + 1], net.enc[l], kC[l]}, nullptr,
+                    true, Out{net.adec[l], kC[l]}, batch, s));
+        NN_TRY(conv(net, layer(net, n1name), In{net.adec[l], kC[l]}, nullptr, true,
+                    Out{net.d[l], kC[l]}, batch, s));
     }
     const size_t hw = net.nparam - 17;
     hipLaunchKernelGGL(k_head, dim3(blocks_for(int64_t(batch) * n0 * n0)), dim3(256), 0, s, net.d[0],
@@ -1095,14 +1395,15 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
         n0name[3] = n1name[3] = char('0' + l);
         const Layer& c0 = layer(net, n0name);
         const Layer& c1 = layer(net, n1name);
-        const int C = kC[l], CC = cat_channels(l);
-        NN_TRY(wgrad(net, c1, net.adec[l], C, net.gd[l], C, net.d[l], C, batch, s));
-        NN_TRY(conv(net, c1, net.gd[l], C, net.d[l], C, false, net.gadec[l], C, batch, s));
-        NN_TRY(wgrad(net, c0, net.cat[l], CC, net.gadec[l], C, net.adec[l], C, batch, s));
-        NN_TRY(conv(net, c0, net.gadec[l], C, net.adec[l], C, false, net.gcat[l], CC, batch, s));
+        const int C = kC[l], U = kC[l + 1];
+        NN_TRY(wgrad(net, c1, In{net.adec[l], C}, net.gd[l], net.d[l], batch, s));
+        NN_TRY(conv(net, c1, In{net.gd[l], C}, net.d[l], false, Out{net.gadec[l], C}, batch, s));
+        NN_TRY(wgrad(net, c0, In{net.up[l], U, net.enc[l], C}, net.gadec[l], net.adec[l], batch, s));
+        NN_TRY(conv(net, c0, In{net.gadec[l], C}, net.adec[l], false,
+                    Out{net.gup[l], U, net.genc[l], C}, batch, s));
         // up = P(d_{l+1}) with P = F^2 R^T: the gradient reaching d_{l+1} is F^2 R(dup)
-        bf16* gbelow = l == kLevels - 2 ? net.ge3 : net.gd[l + 1];
-        NN_TRY(restrict_op(net, net.gcat[l], CC, gbelow, kC[l + 1], batch, net.n[l + 1], kC[l + 1],
+        bf16* gbelow = l == kLevels - 2 ? net.genc[l + 1] : net.gd[l + 1];
+        NN_TRY(restrict_op(net, net.gup[l], U, gbelow, U, batch, net.n[l + 1], U,
                            float(net.factor * net.factor), 0, s));
     }
     // encoder, from the bottom level up
@@ -1112,19 +1413,15 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
         const Layer& c0 = layer(net, n0name);
         const Layer& c1 = layer(net, n1name);
         const int C = kC[l];
-        const bf16* e = l < kLevels - 1 ? net.cat[l] + kC[l + 1] : net.e3;
-        bf16* ge = l < kLevels - 1 ? net.gcat[l] + kC[l + 1] : net.ge3;
-        const int64_t es = l < kLevels - 1 ? cat_channels(l) : C;
-        NN_TRY(wgrad(net, c1, net.aenc[l], C, ge, es, e, es, batch, s));
-        NN_TRY(conv(net, c1, ge, es, e, es, false, net.gaenc[l], C, batch, s));
-        NN_TRY(wgrad(net, c0, net.in[l], in_channels(l), net.gaenc[l], C, net.aenc[l], C, batch, s));
+        NN_TRY(wgrad(net, c1, In{net.aenc[l], C}, net.genc[l], net.enc[l], batch, s));
+        NN_TRY(conv(net, c1, In{net.genc[l], C}, net.enc[l], false, Out{net.gaenc[l], C}, batch, s));
+        NN_TRY(wgrad(net, c0, In{net.in[l], in_channels(l)}, net.gaenc[l], net.aenc[l], batch, s));
         if (l > 0) {
-            NN_TRY(conv(net, c0, net.gaenc[l], C, net.aenc[l], C, false, net.gin[l], in_channels(l),
-                        batch, s));
+            NN_TRY(conv(net, c0, In{net.gaenc[l], C}, net.aenc[l], false,
+                        Out{net.gin[l], in_channels(l)}, batch, s));
             // in_l = R(e_{l-1}): add R^T(g_in) = P(g_in)/F^2 to e_{l-1}'s gradient
             // (which already holds its skip-connection part)
-            bf16* gprev = net.gcat[l - 1] + kC[l];
-            NN_TRY(prolong_op(net, net.gin[l], in_channels(l), gprev, cat_channels(l - 1), batch,
+            NN_TRY(prolong_op(net, net.gin[l], in_channels(l), net.genc[l - 1], kC[l - 1], batch,
                               net.n[l], in_channels(l), 1.f / float(net.factor * net.factor), 1, s));
         }
     }
