@@ -360,17 +360,26 @@ __global__ __launch_bounds__(256) void k_conv_deep(ConvArgs a) {
     }
 }
 
-// Weight gradient dW[co][ci][tap] = sum_p dZ[p][co] * X[p + off(tap)][ci],
-// dZ = dY masked by (Y > 0).  MFMA with M = 16 output channels, N = 16
-// input channels, K = 16 pixels of a row.  A workgroup of four waves takes
-// four consecutive rows of one sample (one row per wave) for one (ci tile,
-// co tile) pair and all nine taps: per 16-pixel chunk a wave loads its dZ
-// operand once and, for each of the three X rows, the six pixels its lane
-// group spans once, and issues the nine taps' MFMAs from them.  The four
-// waves' sums meet in LDS and are added in a fixed order ((w0 + w1) + (w2 +
-// w3)) into the workgroup's slot (part[sample * row quads + quad][co][ci]
-// [tap]); k_reduce_parts adds the slots in a fixed order, so the gradient
-// has the same bits on every run.
+// Weight gradient dW[co][ci][tap] = sum_p dZ[p][co] * X[p + off(tap)][ci] and
+// bias gradient db[co] = sum_p dZ[p][co], dZ = dY masked by (Y > 0): a
+// contraction over pixels, on the 16x16x32 MFMA with M = 16 output channels,
+// N = 16 input channels, K = 32 pixels of a row (the bias against ones).
+// The operands need four pixels of one channel a lane, where memory has the
+// channels of a pixel together: rows are loaded as they lie, 8 bytes a lane,
+// put into the wave's LDS, and read back through the transposing LDS load
+// (ds_read_b64_tr_b16: lane l of the 64 gets channel l%16 of pixels
+// 4(l/16)+j; the three columns of taps are three addresses of one row).
+// Bound by memory on the finest level (200 MB for 16 -> 16 channels at
+// 511^2 x 8), so a wave takes TI x TO tiles of channels and walks down
+// `rows` rows of a 32-pixel strip, loading three rows ahead: X once, dY and
+// Y once.  Three rows of dZ operands stay in registers: row y of X meets
+// rows y + 1, y and y - 1 of dZ.  511^2 x 8: 16 -> 16 channels 44 us, 48 ->
+// 16 81 us (one wave a row with 26 two-byte loads for 16 pixels: 112-162 and
+// 361 us, and 24-63 us more for the bias); 96 -> 32 at 127^2 32 us (93).
+// The workgroup's four waves (consecutive bands of rows) meet in LDS and are
+// added as (w0 + w1) + (w2 + w3) into the workgroup's slot
+// (part[slot][cout x cin x 9, then cout]); k_reduce_slots adds the slots in a
+// fixed order, so the gradient has the same bits on every run.
 struct WGradArgs {
     const bf16* x;     // input channels [0, xsplit), pixel stride xs
     int64_t xs;
@@ -381,114 +390,206 @@ struct WGradArgs {
     int64_t dys;
     const bf16* y;  // layer output (mask), stride ys
     int64_t ys;
-    float* part;    // [batch * row quads][cout][cin_w][9] partial sums
-    int batch, h, wd, cin, cout;
+    float* part;
+    int batch, h, wd, cin, cout, rows;
     int cin_w;      // input channels of the weight tensor (cin is padded to 16)
 };
 
-constexpr int kWgradRows = 4;  // rows per workgroup (one per wave)
+constexpr int kWgradWaves = 4;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bfx8 __attribute__((ext_vector_type(8)));
 
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(WGradArgs a) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int cit = a.cin / 16, cot = a.cout / 16;
-    const int quads = (a.h + kWgradRows - 1) / kWgradRows;
-    int64_t r = blockIdx.x;  // the grid is exactly batch x quads x cit x cot
-    const int co_t = int(r % cot);
-    r /= cot;
-    const int ci_t = int(r % cit);
-    r /= cit;
-    const int qd = int(r % quads);
-    const int b = int(r / quads);
-    const int row = qd * kWgradRows + wv;
-    const int l16 = lane & 15, kq = (lane >> 4) * 4;
-    f32x4 acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (row < a.h) {
-        const int64_t prow = (int64_t(b) * a.h + row) * a.wd;  // first pixel of the row
-        const bf16* ym = a.y + prow * a.ys + co_t * 16 + l16;
-        const bf16* dym = a.dy + prow * a.dys + co_t * 16 + l16;
-        const bool first = ci_t * 16 < a.xsplit;
-        const bf16* xbase = first ? a.x + ci_t * 16 : a.x2 + (ci_t * 16 - a.xsplit);
-        const int64_t xs = first ? a.xs : a.xs2;
-        const bf16* xr[3];
-        bool rok[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const int yy = row + d - 1;
-            rok[d] = yy >= 0 && yy < a.h;
-            xr[d] = xbase + ((int64_t(b) * a.h + (rok[d] ? yy : row)) * a.wd) * xs + l16;
-        }
-        for (int x0 = 0; x0 < a.wd; x0 += 16) {
-            const int xb = x0 + kq;  // this lane group's first pixel
-            bf16x4 av;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int xx = xb + j;
-                bf16 g = 0;
-                if (xx < a.wd && bf2f(ym[int64_t(xx) * a.ys]) > 0.f) g = dym[int64_t(xx) * a.dys];
-                av[j] = short(g);
-            }
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                // X at pixels xb - 1 .. xb + 4 of row `row + d - 1` (0 outside)
-                bf16 xv[6];
-#pragma unroll
-                for (int m = 0; m < 6; ++m) {
-                    const int xs2 = xb - 1 + m;
-                    xv[m] = (rok[d] && xs2 >= 0 && xs2 < a.wd) ? xr[d][int64_t(xs2) * xs] : bf16(0);
-                }
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    bf16x4 bv;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) bv[j] = xb + j < a.wd ? short(xv[j + dx]) : short(0);
-                    acc[d * 3 + dx] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[d * 3 + dx], 0, 0, 0);
-                }
-            }
-        }
-    }
-    // [wave][tap][co][ci] in LDS, then the fixed-order sum over the waves
-    __shared__ float sh[kWgradRows][9][16][16];
-    const int n = lane & 15, mq = (lane >> 4) * 4;
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sh[wv][t][mq + i][n] = acc[t][i];
-    __syncthreads();
-    const int64_t slot = int64_t(b) * quads + qd;
-    for (int e = threadIdx.x; e < 16 * 16 * 9; e += 256) {
-        const int tap = e % 9, ci = (e / 9) % 16, co = e / 144;
-        const float v = (sh[0][tap][co][ci] + sh[1][tap][co][ci]) + (sh[2][tap][co][ci] + sh[3][tap][co][ci]);
-        const int ci_g = ci_t * 16 + ci, co_g = co_t * 16 + co;
-        if (ci_g < a.cin_w) a.part[((slot * a.cout + co_g) * a.cin_w + ci_g) * 9 + tap] = v;
-    }
+__device__ __forceinline__ f32x4 mfma32(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfx8, a),
+                                                   __builtin_bit_cast(bfx8, b), c, 0, 0, 0);
 }
 
-// Bias gradient: per row (one block each) part[row][ch] = sum over the row
-// of dY[p][ch] where Y[p][ch] > 0, in a fixed order: thread t takes channel
-// t % c of the pixels x = t / c, t / c + g, ... (g = 256 / c pixel groups;
-// c is a power of two up to 256), then a fixed tree over the groups;
-// k_reduce_parts adds the rows in order.
-__global__ __launch_bounds__(256) void k_bias_grad(const bf16* dy, int64_t dys, const bf16* y,
-                                                   int64_t ys, float* part, int wd, int c) {
-    const int64_t row = blockIdx.x;
-    const int t = threadIdx.x;
-    const int g = 256 / c;
-    const int ch = t % c, x0 = t / c;
-    float s = 0.f;
-    for (int x = x0; x < wd; x += g) {
-        const int64_t p = row * wd + x;
-        if (bf2f(y[p * ys + ch]) > 0.f) s += bf2f(dy[p * dys + ch]);
+typedef __attribute__((address_space(3))) bf16x4* lds4;
+
+// Two transposed groups of 16 pixels (16 channels, 32 bytes a pixel in LDS).
+__device__ __forceinline__ u32x4 read_pixels(bf16* lane_base, int pixel) {
+    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(lane_base + pixel * 16));
+    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(lane_base + (pixel + 16) * 16));
+    const u32x2 lo = __builtin_bit_cast(u32x2, a), hi = __builtin_bit_cast(u32x2, b);
+    return u32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+
+template <int TI, int TO>
+__global__ __launch_bounds__(64 * kWgradWaves) void k_conv3x3_wgrad(WGradArgs a) {
+    constexpr int kXElems = 34 * 16, kZElems = 32 * 16;      // one tile's row in LDS
+    constexpr int kStage = TI * kXElems + TO * kZElems;      // a wave's
+    constexpr int kStageBytes = kWgradWaves * kStage * 2;
+    constexpr int kSumBytes = kWgradWaves * 9 * 256 * 4;
+    __shared__ __attribute__((aligned(16))) char smem[kStageBytes > kSumBytes ? kStageBytes : kSumBytes];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cig = a.cin / (16 * TI), cog = a.cout / (16 * TO);
+    const int strips = (a.wd + 31) / 32;
+    const int groups = (a.h + a.rows * kWgradWaves - 1) / (a.rows * kWgradWaves);
+    int r = blockIdx.x;  // the grid is exactly batch x groups x strips x cig x cog
+    const int co_t = (r % cog) * TO;
+    r /= cog;
+    const int ci_t = (r % cig) * TI;
+    r /= cig;
+    const int strip = r % strips;
+    r /= strips;
+    const int group = r % groups, b = r / groups;
+    const int x0 = strip * 32;
+    const int y0 = (group * kWgradWaves + wv) * a.rows;
+    const int y1 = y0 + a.rows < a.h ? y0 + a.rows : a.h;
+    const int n = lane & 15, kq = (lane >> 4) * 4;
+
+    f32x4 acc[TI][TO][9], accb[TO];
+#pragma unroll
+    for (int to = 0; to < TO; ++to) {
+        accb[to] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) acc[ti][to][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    __shared__ float sh[256];
-    sh[t] = s;
+    if (y0 < a.h) {
+        bf16* stage = reinterpret_cast<bf16*>(smem) + wv * kStage;
+        bf16* zstage = stage + TI * kXElems;
+        const RowLanes<2> lanes(x0, n, a.wd);
+        // pixel x = wd of the strip is no pixel: X one column left of it is kept out
+        u32x4 inside;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int x = x0 + (k >> 1) * 16 + kq + (k & 1) * 2;
+            inside[k] = (x < a.wd ? 0xffffu : 0u) | (x + 1 < a.wd ? 0xffff0000u : 0u);
+        }
+        RowPixels<2> rx[3][TI];
+        u32x2 rdy[3][TO][2], ry[3][TO][2];
+        // row `row` of X and the row below it of dY and Y
+        auto fetch = [&](int slot, int row) {
+            const int64_t px = int64_t(b * a.h + (row < 0 ? 0 : row < a.h ? row : a.h - 1)) * a.wd;
+            const int64_t pz = int64_t(b * a.h + (row + 1 < a.h ? row + 1 : a.h - 1)) * a.wd;
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) {
+                const int c0 = (ci_t + ti) * 16;
+                if (c0 < a.xsplit)
+                    lanes.load(rx[slot][ti], a.x + px * a.xs + c0, uint32_t(a.xs), uint32_t(kq));
+                else
+                    lanes.load(rx[slot][ti], a.x2 + px * a.xs2 + (c0 - a.xsplit), uint32_t(a.xs2),
+                               uint32_t(kq));
+            }
+#pragma unroll
+            for (int to = 0; to < TO; ++to)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const uint32_t c0 = uint32_t((co_t + to) * 16 + kq), p = uint32_t(lanes.px[g]);
+                    rdy[slot][to][g] = *reinterpret_cast<const u32x2*>(
+                        a.dy + pz * a.dys + (p * uint32_t(a.dys) + c0));
+                    ry[slot][to][g] = *reinterpret_cast<const u32x2*>(
+                        a.y + pz * a.ys + (p * uint32_t(a.ys) + c0));
+                }
+        };
+        u32x4 dz[3][TO];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int to = 0; to < TO; ++to) dz[k][to] = u32x4{0u, 0u, 0u, 0u};
+        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fetch(k, y0 - 1 + k);
+        for (int base = y0 - 1; base <= y1; base += 3) {
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int yi = base + u;
+                const uint32_t row_ok = yi >= 0 && yi < a.h ? ~0u : 0u;
+#pragma unroll
+                for (int ti = 0; ti < TI; ++ti) {
+                    bf16* p = stage + ti * kXElems + kq;
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+                        *reinterpret_cast<u32x2*>(p + (g * 16 + n + 1) * 16) =
+                            rx[u][ti].v[g] & (lanes.ok[g] & row_ok);
+                    if (n == 0 || n == 15)
+                        *reinterpret_cast<u32x2*>(p + (n == 0 ? 0 : 33) * 16) =
+                            rx[u][ti].v[2] & (lanes.ok[2] & row_ok);
+                }
+#pragma unroll
+                for (int to = 0; to < TO; ++to)
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        u32x2 v = rdy[u][to][g] & lanes.ok[g];
+                        v[0] &= positive(ry[u][to][g][0]);
+                        v[1] &= positive(ry[u][to][g][1]);
+                        *reinterpret_cast<u32x2*>(zstage + to * kZElems + (g * 16 + n) * 16 + kq) = v;
+                    }
+                fetch(u, yi + 3);
+                // the wave's own LDS, in order: no barrier, but no reordering either
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                u32x4 xo[TI][3];
+#pragma unroll
+                for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+                        xo[ti][dx] = read_pixels(stage + ti * kXElems + lane * 4, dx);
+                    xo[ti][0] &= inside;
+                }
+#pragma unroll
+                for (int to = 0; to < TO; ++to)
+                    dz[u][to] = read_pixels(zstage + to * kZElems + lane * 4, 0);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (row_ok)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const int row = yi + 1 - d;  // of dZ
+                        if (row < y0 || row >= y1) continue;
+#pragma unroll
+                        for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+                            for (int to = 0; to < TO; ++to)
+#pragma unroll
+                                for (int dx = 0; dx < 3; ++dx)
+                                    acc[ti][to][d * 3 + dx] = mfma32(dz[(u + 3 - d) % 3][to], xo[ti][dx],
+                                                                     acc[ti][to][d * 3 + dx]);
+                    }
+                if (ci_t == 0 && yi >= y0 && yi < y1)
+#pragma unroll
+                    for (int to = 0; to < TO; ++to) accb[to] = mfma32(dz[(u + 2) % 3][to], ones, accb[to]);
+            }
+        }
+    }
+    // per pair of tiles: [wave][tap][co][ci] in LDS, then the sum over the waves
+    float* sh = reinterpret_cast<float*>(smem);
+    const int64_t wcount = int64_t(a.cout) * a.cin_w * 9;
+    float* slot = a.part + ((int64_t(b) * groups + group) * strips + strip) * (wcount + a.cout);
+#pragma unroll
+    for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+        for (int to = 0; to < TO; ++to) {
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sh[((wv * 9 + t) * 16 + kq + i) * 16 + n] = acc[ti][to][t][i];
+            __syncthreads();
+            for (int e = threadIdx.x; e < 16 * 16 * 9; e += 64 * kWgradWaves) {
+                const int tap = e % 9, ci = (e / 9) % 16, co = e / 144;
+                const float* p = sh + (tap * 16 + co) * 16 + ci;
+                const float v = (p[0] + p[9 * 256]) + (p[2 * 9 * 256] + p[3 * 9 * 256]);
+                const int ci_g = (ci_t + ti) * 16 + ci, co_g = (co_t + to) * 16 + co;
+                if (ci_g < a.cin_w) slot[(int64_t(co_g) * a.cin_w + ci_g) * 9 + tap] = v;
+            }
+        }
+    if (ci_t != 0) return;
     __syncthreads();
-    for (int st = g / 2; st > 0; st >>= 1) {
-        if (x0 < st) sh[t] += sh[t + st * c];
-        __syncthreads();
+    if (n == 0)
+#pragma unroll
+        for (int to = 0; to < TO; ++to)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sh[(wv * TO + to) * 16 + kq + i] = accb[to][i];
+    __syncthreads();
+    if (threadIdx.x < TO * 16) {
+        const float* p = sh + threadIdx.x;
+        slot[wcount + co_t * 16 + threadIdx.x] =
+            (p[0] + p[TO * 16]) + (p[2 * TO * 16] + p[3 * TO * 16]);
     }
-    if (x0 == 0) part[row * c + ch] = sh[t];
 }
 
 // out[e] = sum over slots k = 0 .. nparts-1 of part[k * count + e], in a
@@ -511,39 +612,37 @@ __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ 
     if (threadIdx.x == 0) out[e] = sh[0];
 }
 
-// The same sums for many slots, in two coalesced passes: pass 1 splits the
-// slots into kReduceChunks contiguous chunks; a block takes 64 consecutive
-// elements and one chunk, its four waves add slots g, g + 4, ... of the
-// chunk (each wave reading 64 consecutive floats of a slot), and the four
-// wave sums are added as (w0 + w1) + (w2 + w3) into stage[chunk][e];
-// pass 2 adds the chunks in order.  A fixed order again.
-constexpr int kReduceChunks = 16;
+// The same sums for many elements, coalesced: a block takes 64 consecutive
+// elements, its 16 waves the slots w, w + 16, ... (64 consecutive floats of
+// a slot at a time, four partial sums), whose sums are added in the waves'
+// order.  A fixed order again.  (512 slots of 2320: 6.5 us.)
+constexpr int kReduceWaves = 16;
 
-__global__ __launch_bounds__(256) void k_reduce_chunks(const float* __restrict__ part,
-                                                       int64_t nparts, int64_t count,
-                                                       float* __restrict__ stage) {
+__global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_slots(const float* __restrict__ part,
+                                                                    int64_t nparts, int64_t count,
+                                                                    float* __restrict__ out) {
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int64_t e = int64_t(blockIdx.x) * 64 + l;
-    const int64_t per = (nparts + kReduceChunks - 1) / kReduceChunks;
-    const int64_t k0 = int64_t(blockIdx.y) * per;
-    const int64_t k1 = k0 + per < nparts ? k0 + per : nparts;
-    float acc = 0.f;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     if (e < count)
-        for (int64_t k = k0 + g; k < k1; k += 4) acc += part[k * count + e];
-    __shared__ float sh[4][64];
-    sh[g][l] = acc;
+        for (int64_t k = g; k < nparts; k += 4 * kReduceWaves) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t ki = k + int64_t(i) * kReduceWaves;
+                v[i] = ki < nparts ? part[ki * count + e] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += v[i];
+        }
+    __shared__ float sh[kReduceWaves][64];
+    sh[g][l] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     __syncthreads();
-    if (g == 0 && e < count)
-        stage[int64_t(blockIdx.y) * count + e] = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
-}
-
-__global__ __launch_bounds__(256) void k_reduce_stage(const float* __restrict__ stage,
-                                                      int64_t count, float* __restrict__ out) {
-    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (e >= count) return;
-    float s = 0.f;
-    for (int c = 0; c < kReduceChunks; ++c) s += stage[int64_t(c) * count + e];
-    out[e] = s;
+    if (g == 0 && e < count) {
+        float s = sh[0][l];
+        for (int w = 1; w < kReduceWaves; ++w) s += sh[w][l];
+        out[e] = s;
+    }
 }
 
 // Grid transfers between levels coarsened by a factor F (2 or 4): fine
@@ -994,8 +1093,6 @@ struct Net {
     float *param, *grad, *m, *v, *rms, *loss, *y, *dy;
     float* parts = nullptr;  // partial sums of the fixed-order gradient reductions
     size_t parts_floats = 0;
-    float* stage = nullptr;  // per-chunk sums of the two-pass reduction
-    size_t stage_floats = 0;
     double* guess;  // natural-layout scratch grid for the learned solve
     int adam_t = 0;
     // activations (level-indexed) and their gradients
@@ -1011,20 +1108,52 @@ namespace {
 
 int in_channels(int l) { return l == 0 ? 16 : kC[l - 1]; }
 
-int wgrad_quads(int h) { return (h + kWgradRows - 1) / kWgradRows; }
+// How the weight gradient of a layer is split: TI x TO channel tiles and
+// `rows` rows of a 32-pixel strip a wave.  Few rows read the two beside them
+// too often and leave many slots to add, so as many as fill 256 CUs once
+// with the workgroups that fit (three of one tile, one of three or four, by
+// their registers), and at least four.
+struct WgradSplit {
+    int ti, to, rows;
+    int64_t strips, groups;  // per sample; a slot each
+};
 
-// Floats of partial sums the largest fixed-order reduction needs: weight
-// gradients (batch x row blocks slots of cout x cin x 9), bias gradients
-// (batch x rows slots of cout), the head (blocks of 17), the loss and the
-// rms row sums.
+WgradSplit wgrad_split(int batch, int n, int cin_p, int cout) {
+    WgradSplit p;
+    const int cit = cin_p / 16, cot = cout / 16;
+    p.strips = (n + 31) / 32;
+    const int64_t strip_rows = int64_t(batch) * p.strips * n;
+    p.ti = cit == 3 ? 3 : 1;
+    p.to = 1;
+    // operands loaded half as often, where that leaves enough waves (8 samples
+    // of 127^2, 32 -> 32: 20 us against 38; of 31^2 there are too few)
+    if (cit % 2 == 0 && cot % 2 == 0 && strip_rows * (cit / 2) * (cot / 2) >= 2048) p.ti = p.to = 2;
+    const int64_t column = batch * p.strips * (cit / p.ti) * (cot / p.to);  // workgroups
+    const int64_t fit = p.ti * p.to == 1 ? 768 : 256;
+    const int64_t bands = std::max<int64_t>(fit / column, 1) * kWgradWaves;
+    p.rows = int(std::max<int64_t>((n + bands - 1) / bands, 4));
+    p.groups = (n + int64_t(p.rows) * kWgradWaves - 1) / (int64_t(p.rows) * kWgradWaves);
+    return p;
+}
+
+// Floats of partial sums the largest fixed-order reduction needs: a layer's
+// gradients (a slot of cout x cin x 9 and cout per workgroup; no batch has
+// more slots than the largest), the head (blocks of 17), the loss and the rms
+// row sums.
+size_t wgrad_floats(const Net& net, const Layer& l) {
+    size_t most = 0;
+    for (int b = 1; b <= net.batch; ++b) {
+        const WgradSplit p = wgrad_split(b, net.n[l.level], l.cin_p, l.cout);
+        most = std::max(most, size_t(b) * size_t(p.strips * p.groups));
+    }
+    return most * (size_t(l.cout) * size_t(l.cin) * 9 + size_t(l.cout));
+}
+
 size_t parts_floats(const Net& net) {
     size_t most = 0;
     const size_t B = size_t(net.batch);
     for (const auto& l : net.layers) {
-        const int h = net.n[l.level];
-        const size_t rb = size_t(wgrad_quads(h));
-        most = std::max(most, B * rb * size_t(l.cout) * size_t(l.cin) * 9);
-        most = std::max(most, B * size_t(h) * size_t(l.cout));
+        most = std::max(most, wgrad_floats(net, l));
     }
     const size_t px0 = B * size_t(net.n[0]) * size_t(net.n[0]);
     most = std::max(most, (px0 + 255) / 256 * 17);
@@ -1056,10 +1185,6 @@ size_t carve(Net& net, char* base) {
     net.dy = reinterpret_cast<float*>(take(B * px0 * 4));
     net.parts_floats = parts_floats(net);
     net.parts = reinterpret_cast<float*>(take(net.parts_floats * 4));
-    size_t most = 0;
-    for (const auto& l : net.layers) most = std::max(most, size_t(l.cout) * size_t(l.cin) * 9);
-    net.stage_floats = size_t(kReduceChunks) * most;
-    net.stage = reinterpret_cast<float*>(take(net.stage_floats * 4));
     net.guess = reinterpret_cast<double*>(take(size_t(net.n[0] + 2) * (net.n[0] + 2) * 8));
     for (int l = 0; l < kLevels; ++l) {
         const int64_t px = B * net.n[l] * net.n[l];
@@ -1203,17 +1328,6 @@ hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool for
     return mask ? launch_deep<true>(a, pg, nt, grid, s) : launch_deep<false>(a, pg, nt, grid, s);
 }
 
-// out[e] = sum over the nparts slots of net.parts[k * count + e] (two passes).
-hipError_t reduce_slots(const Net& net, int64_t nparts, int64_t count, float* out, hipStream_t s) {
-    if (size_t(count) * kReduceChunks > net.stage_floats) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_reduce_chunks, dim3(unsigned((count + 63) / 64), kReduceChunks), dim3(256), 0,
-                       s, net.parts, nparts, count, net.stage);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_stage, dim3(blocks_for(count)), dim3(256), 0, s, net.stage, count, out);
-    return hipGetLastError();
-}
-
 hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf16* y, int batch,
                  hipStream_t s) {
     const int64_t dys = L.cout, ys = L.cout;
@@ -1232,25 +1346,27 @@ hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf1
     a.cout = L.cout;
     a.cin_w = L.cin;  // the first layer's padded input channels feed no weight
     a.part = net.parts;
-    const int rb = wgrad_quads(a.h);
-    const int64_t blocks = int64_t(batch) * rb * (a.cin / 16) * (a.cout / 16);
-    hipLaunchKernelGGL(k_conv3x3_wgrad, dim3(unsigned(blocks)), dim3(256), 0, s, a);
+    const WgradSplit p = wgrad_split(batch, a.h, a.cin, a.cout);
+    a.rows = p.rows;
+    const int64_t slots = int64_t(batch) * p.strips * p.groups;
+    const int64_t blocks = slots * (a.cin / (16 * p.ti)) * (a.cout / (16 * p.to));
+    const int64_t count = int64_t(L.cout) * L.cin * 9 + L.cout;  // the bias follows the weights
+    if (size_t(slots * count) > net.parts_floats || blocks > (int64_t(1) << 31) - 1 ||
+        L.b_off != L.w_off + size_t(count - L.cout) || (x.ca | x.cb | a.cout) % 16 != 0 ||
+        x.count() != a.cin ||
+        (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.x2) |
+         reinterpret_cast<uintptr_t>(a.dy) | reinterpret_cast<uintptr_t>(a.y)) % 8 != 0)
+        return hipErrorInvalidValue;
+    const dim3 grid{unsigned(blocks)}, block{64 * kWgradWaves};
+    if (p.ti == 1 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<1, 1>), grid, block, 0, s, a);
+    else if (p.ti == 3 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<3, 1>), grid, block, 0, s, a);
+    else if (p.ti == 2 && p.to == 2) hipLaunchKernelGGL((k_conv3x3_wgrad<2, 2>), grid, block, 0, s, a);
+    else return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t wcount = int64_t(L.cout) * L.cin * 9;
-    if ((e = reduce_slots(net, int64_t(batch) * rb, wcount, net.grad + L.w_off, s)) != hipSuccess)
-        return e;
-    if (L.cout > 256 || (256 % L.cout) != 0) return hipErrorInvalidValue;
-    const bool wide = L.cout % 8 == 0 && dys % 8 == 0 && ys % 8 == 0 &&
-                      (reinterpret_cast<uintptr_t>(dy) | reinterpret_cast<uintptr_t>(y)) % 16 == 0;
-    if (wide)
-        hipLaunchKernelGGL(k_bias_grad8, dim3(unsigned(int64_t(batch) * a.h)), dim3(256), 0, s, dy,
-                           dys, y, ys, net.parts, a.wd, L.cout);
-    else
-        hipLaunchKernelGGL(k_bias_grad, dim3(unsigned(int64_t(batch) * a.h)), dim3(256), 0, s, dy,
-                           dys, y, ys, net.parts, a.wd, L.cout);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return reduce_slots(net, int64_t(batch) * a.h, int64_t(L.cout), net.grad + L.b_off, s);
+    hipLaunchKernelGGL(k_reduce_slots, dim3(unsigned((count + 63) / 64)), dim3(64 * kReduceWaves), 0, s,
+                       net.parts, slots, count, net.grad + L.w_off);
+    return hipGetLastError();
 }
 
 }  // namespace

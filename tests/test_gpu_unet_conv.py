@@ -64,3 +64,30 @@ def test_gradients_at_tile_edges(factor, n):
     for k in want:
         rel = np.linalg.norm(got[k].ravel() - want[k].ravel()) / np.linalg.norm(want[k].ravel())
         assert rel < TOL, f"{k}: relative L2 error {rel:.3e}"
+
+
+def test_gradient_of_a_batch_is_the_mean_of_its_samples():
+    """Eight samples of 255^2 walk down bands of 16 rows, one alone bands of
+    four.  The loss is a mean over 8 = 2^3 samples, so the stored gradients of
+    a sample are the same numbers times 1/8; the weight gradients differ by
+    FP32 sums of about 100 roundings, 6e-6 of their terms' magnitudes, which
+    are taken to be at most 16 times the result's."""
+    say("unet batch gradient")
+    n, batch = 255, 8
+    p = make_params(seed=5)
+    net = rb.UNet(n, batch, factor=4)
+    net.set_params(flatten(p).astype(np.float32))
+    f = torch.from_numpy(batch_fields(range(batch), n)).to(DEV)
+    g = torch.Generator().manual_seed(1)
+    target = torch.zeros_like(f)
+    target[:, 1:-1, 1:-1] = (torch.randn(batch, n, n, generator=g, dtype=torch.float64) * 0.01).to(DEV)
+    net.train_step(f, target, 0.0, update=False)
+    got = unflatten(net.get_grads().astype(np.float64), p)
+    total = 0.0
+    for b in range(batch):
+        net.train_step(f[b:b + 1].contiguous(), target[b:b + 1].contiguous(), 0.0, update=False)
+        total = total + net.get_grads().astype(np.float64) / batch
+    want = unflatten(total, p)
+    for k in want:
+        rel = np.linalg.norm(got[k].ravel() - want[k].ravel()) / np.linalg.norm(want[k].ravel())
+        assert rel < 1e-4, f"{k}: relative L2 error {rel:.3e}"
