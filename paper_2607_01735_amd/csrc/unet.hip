@@ -38,13 +38,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(bf16 v) { return __uint_as_float(uint32_t(v) << 16); }
 
-__device__ __forceinline__ bf16 f2bf(float x) {
-    // round to nearest, ties to even (NaN kept quiet)
-    uint32_t b = __float_as_uint(x);
-    if ((b & 0x7f800000u) == 0x7f800000u && (b & 0x007fffffu) != 0u) return bf16((b | 0x00400000u) >> 16);
-    b += 0x7fffu + ((b >> 16) & 1u);
-    return bf16(b >> 16);
-}
+// round to nearest, ties to even (NaN kept quiet), two to a v_cvt_pk_bf16_f32
+__device__ __forceinline__ bf16 f2bf(float x) { return __builtin_bit_cast(bf16, static_cast<__bf16>(x)); }
 
 // ---------------------------------------------------------------------------
 // 3x3 convolution, stride 1, zero padding 1, as an implicit GEMM:
@@ -93,6 +88,10 @@ __device__ __forceinline__ f32x4 mfma16(u32x2 a, u32x2 b, f32x4 c) {
                                                      __builtin_bit_cast(bf16x4, b), c, 0, 0, 0);
 }
 
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+    return uint32_t(f2bf(lo)) | (uint32_t(f2bf(hi)) << 16);
+}
+
 // all ones in the halves of m that are > 0 (as a BF16 that is no NaN)
 __device__ __forceinline__ uint32_t positive(uint32_t m) {
     const s16x2 v = __builtin_bit_cast(s16x2, m);
@@ -109,15 +108,15 @@ __device__ __forceinline__ u32x2 dpp(u32x2 old, u32x2 v) {
 
 __device__ __forceinline__ void store_pixel(const ConvArgs& a, int64_t pix, int co, f32x4 v,
                                             f32x4 bias) {
-    bf16x4 out;
+    float r[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float r = v[i] + bias[i];
-        if (a.relu) r = r > 0.f ? r : 0.f;
-        out[i] = short(f2bf(r));
+        r[i] = v[i] + bias[i];
+        if (a.relu) r[i] = r[i] > 0.f ? r[i] : 0.f;
     }
+    const u32x2 out = {pack2(r[0], r[1]), pack2(r[2], r[3])};
     bf16* p = co < a.ysplit ? a.y + pix * a.ys + co : a.y2 + pix * a.ys2 + (co - a.ysplit);
-    *reinterpret_cast<bf16x4*>(p) = out;
+    *reinterpret_cast<u32x2*>(p) = out;
 }
 
 // Four channels of PG x 16 pixels of a row and of the two pixels beside
@@ -146,6 +145,11 @@ struct RowLanes {
 #pragma unroll
         for (int g = 0; g <= PG; ++g)
             r.v[g] = *reinterpret_cast<const u32x2*>(p + (uint32_t(px[g]) * stride + ch));
+    }
+    // one channel of 16 (the network's input), the others 0
+    __device__ void load_one(RowPixels<PG>& r, const bf16* p, int kq) const {
+#pragma unroll
+        for (int g = 0; g <= PG; ++g) r.v[g] = u32x2{kq == 0 ? uint32_t(p[uint32_t(px[g])]) : 0u, 0u};
     }
     // The B operands of the three taps of a kernel row: the pixels shifted
     // by a lane either way (DPP), op[column * step + group].
@@ -184,7 +188,7 @@ struct RowLanes {
 // (134 MB, 4.1 TB/s), 48 -> 16 72 us, masked 16 -> 16 42 us, 16 -> 48 90 us;
 // a wave per 32 outputs of a row, which loaded three rows three times over
 // behind its loads of weights, took 86, 255, 109 and 194 us.
-template <int CK, int NT, bool MASK>
+template <int CK, int NT, bool MASK, bool ONE = false>
 __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     constexpr int PG = kConvGroups;
     const int lane = threadIdx.x & 63;
@@ -220,7 +224,9 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
         const int64_t pix = int64_t(b * a.h + (row < 0 ? 0 : row < a.h ? row : a.h - 1)) * a.wd;
 #pragma unroll
         for (int c = 0; c < CK; ++c) {
-            if (c * 16 < a.xsplit)
+            if (ONE)
+                lanes.load_one(raw[slot][c], a.x + pix, kq);
+            else if (c * 16 < a.xsplit)
                 lanes.load(raw[slot][c], a.x + pix * a.xs + c * 16, uint32_t(a.xs), uint32_t(kq));
             else
                 lanes.load(raw[slot][c], a.x2 + pix * a.xs2 + (c * 16 - a.xsplit), uint32_t(a.xs2),
@@ -414,7 +420,7 @@ __device__ __forceinline__ u32x4 read_pixels(bf16* lane_base, int pixel) {
     return u32x4{lo[0], lo[1], hi[0], hi[1]};
 }
 
-template <int TI, int TO>
+template <int TI, int TO, bool ONE = false>
 __global__ __launch_bounds__(64 * kWgradWaves) void k_conv3x3_wgrad(WGradArgs a) {
     constexpr int kXElems = 34 * 16, kZElems = 32 * 16;      // one tile's row in LDS
     constexpr int kStage = TI * kXElems + TO * kZElems;      // a wave's
@@ -468,7 +474,9 @@ __global__ __launch_bounds__(64 * kWgradWaves) void k_conv3x3_wgrad(WGradArgs a)
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti) {
                 const int c0 = (ci_t + ti) * 16;
-                if (c0 < a.xsplit)
+                if (ONE)
+                    lanes.load_one(rx[slot][ti], a.x + px, kq);
+                else if (c0 < a.xsplit)
                     lanes.load(rx[slot][ti], a.x + px * a.xs + c0, uint32_t(a.xs), uint32_t(kq));
                 else
                     lanes.load(rx[slot][ti], a.x2 + px * a.xs2 + (c0 - a.xsplit), uint32_t(a.xs2),
@@ -752,62 +760,71 @@ __global__ __launch_bounds__(256) void k_restrict(const bf16* in, int64_t is, bf
     }
     bf16* o = out + ((int64_t(b) * nc + I) * nc + J) * os + ch;
     bf16x8 prev = accumulate ? load8(o) : bf16x8{make_uint4(0, 0, 0, 0)};
-    bf16x8 res;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        float v = s[k] * (scale / float(F * F * F * F));
-        if (accumulate) v += prev.get(k);
-        res.set(k, f2bf(v));
+        s[k] *= scale / float(F * F * F * F);
+        if (accumulate) s[k] += prev.get(k);
     }
-    *reinterpret_cast<uint4*>(o) = res.v;
+    *reinterpret_cast<uint4*>(o) = make_uint4(pack2(s[0], s[1]), pack2(s[2], s[3]), pack2(s[4], s[5]),
+                                              pack2(s[6], s[7]));
 }
 
+// One thread per coarse interval of a fine row: the F fine points from the
+// coarse point J on (J = -1: the F - 1 points before the first) and 8
+// channels, from the same two coarse columns; the row's coarse rows and
+// weights are the block's.  The weights are multiples of 1 / F^2, so a
+// product is exact and the FMA rounds as the sum does; a neighbour outside
+// the grid counts as 0, which changes no sum.  One fine point a thread took
+// its index apart by three divisions and was bound by the vector unit: 65 us
+// for 32 channels to 511^2 x 8 (134 MB), now 33 us.
 template <int F>
 __global__ __launch_bounds__(256) void k_prolong(const bf16* in, int64_t is, bf16* out, int64_t os,
-                                                 int batch, int nc, int c, float scale,
-                                                 int accumulate) {
+                                                 int nc, int c8_shift, float scale, int accumulate) {
     const int nf = F * nc + F - 1;
-    const int c8 = c / 8;
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t total = uint32_t(batch) * uint32_t(nf) * uint32_t(nf) * uint32_t(c8);
-    if (idx >= total) return;
-    const int ch = int(idx % uint32_t(c8)) * 8;
-    uint32_t r = idx / uint32_t(c8);
-    const int j = int(r % uint32_t(nf));
-    r /= uint32_t(nf);
-    const int i = int(r % uint32_t(nf));
-    const int b = int(r / uint32_t(nf));
-    // the coarse points within F - 1 of fine i are I = (i + 1) / F - 1 and
-    // the next one; weight (F - |d|) / F with d = i - (F I + F - 1)
+    const int idx = int(blockIdx.x) * 256 + int(threadIdx.x);
+    const int ch = (idx & ((1 << c8_shift) - 1)) * 8;
+    const int J = (idx >> c8_shift) - 1;
+    if (J >= nc) return;
+    const int i = blockIdx.y, b = blockIdx.z;
+    const int I = (i + 1) / F - 1, ki = (i + 1) % F;
     const float invF = 1.f / float(F);
-    float s[8];
+    float x[2][2][8];  // coarse rows I and I + 1, columns J and J + 1
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] = 0.f;
+    for (int r = 0; r < 2; ++r) {
+        const bool row_ok = I + r >= 0 && I + r < nc && (r == 0 || ki != 0);
 #pragma unroll
-    for (int I = (i + 1) / F - 1; I <= (i + 1) / F; ++I) {
-        const int di = i - (F * I + F - 1);
-        if (I < 0 || I >= nc || di <= -F || di >= F) continue;
-        const float wi = float(F - (di < 0 ? -di : di)) * invF;
+        for (int q = 0; q < 2; ++q) {
+            bf16x8 v{make_uint4(0, 0, 0, 0)};
+            if (row_ok && J + q >= 0 && J + q < nc)
+                v = load8(in + ((int64_t(b) * nc + I + r) * nc + J + q) * is + ch);
 #pragma unroll
-        for (int J = (j + 1) / F - 1; J <= (j + 1) / F; ++J) {
-            const int dj = j - (F * J + F - 1);
-            if (J < 0 || J >= nc || dj <= -F || dj >= F) continue;
-            const float wj = float(F - (dj < 0 ? -dj : dj)) * invF;
-            const bf16x8 x = load8(in + ((int64_t(b) * nc + I) * nc + J) * is + ch);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) s[k] += wi * wj * x.get(k);
+            for (int k = 0; k < 8; ++k) x[r][q][k] = v.get(k);
         }
     }
-    bf16* o = out + ((int64_t(b) * nf + i) * nf + j) * os + ch;
-    bf16x8 prev = accumulate ? load8(o) : bf16x8{make_uint4(0, 0, 0, 0)};
-    bf16x8 res;
+    const float wi[2] = {float(F - ki) * invF, float(ki) * invF};
+    bf16* o = out + ((int64_t(b) * nf + i) * nf + F * (J + 1) - 1) * os + ch;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        float v = s[k] * scale;
-        if (accumulate) v += prev.get(k);
-        res.set(k, f2bf(v));
+    for (int kj = 0; kj < F; ++kj) {
+        if (kj == 0 && J < 0) continue;
+        const float wj[2] = {float(F - kj) * invF, float(kj) * invF};
+        float s[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s[k] = 0.f;
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int q = 0; q < (kj == 0 ? 1 : 2); ++q)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) s[k] = fmaf(wi[r] * wj[q], x[r][q][k], s[k]);
+        const bf16x8 prev = accumulate ? load8(o + kj * os) : bf16x8{make_uint4(0, 0, 0, 0)};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s[k] *= scale;
+            if (accumulate) s[k] += prev.get(k);
+        }
+        *reinterpret_cast<uint4*>(o + kj * os) = make_uint4(
+            pack2(s[0], s[1]), pack2(s[2], s[3]), pack2(s[4], s[5]), pack2(s[6], s[7]));
     }
-    *reinterpret_cast<uint4*>(o) = res.v;
 }
 
 // Sum of one double per thread over a block of 256, by a fixed tree; every
@@ -853,45 +870,37 @@ __global__ __launch_bounds__(256) void k_rms_final(const double* part, int n, fl
     }
 }
 
-// Network input: channel 0 = f / rms, channels 1..15 = 0 (the first conv's
-// K is padded to one 16-wide MFMA chunk per tap).
+// Network input f / rms, one channel (the first convolution's 15 others are
+// zeros that it does not load).
 __global__ __launch_bounds__(256) void k_input(const double* f, int n, int64_t ld, int64_t gstride,
-                                               const float* rms, bf16* x, int batch) {
-    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t total = int64_t(batch) * n * n;
-    if (idx >= total) return;
-    const int b = int(idx / (int64_t(n) * n));
-    const int64_t k = idx % (int64_t(n) * n);
-    const int64_t i = k / n + 1, j = k % n + 1;
-    const float v = float(f[int64_t(b) * gstride + i * ld + j] / double(rms[b]));
-    bf16* px = x + idx * 16;
-    px[0] = f2bf(v);
-#pragma unroll
-    for (int c = 1; c < 16; ++c) px[c] = 0;
+                                               const float* rms, bf16* x) {
+    const int j = int(blockIdx.x) * 256 + int(threadIdx.x), i = blockIdx.y, b = blockIdx.z;
+    if (j >= n) return;
+    const float v = float(f[int64_t(b) * gstride + int64_t(i + 1) * ld + j + 1] / double(rms[b]));
+    x[(int64_t(b) * n + i) * n + j] = f2bf(v);
 }
 
 // Head: y[p] = sum_c w[c] d[p][c] + b (FP32 out).  c = 16 channels at
 // pixel stride ds (a multiple of 8, 16-byte aligned rows): two 16-byte
 // loads per pixel.
 __global__ __launch_bounds__(256) void k_head(const bf16* d, int64_t ds, const float* w,
-                                              const float* bias, float* y, int64_t npix, int c) {
+                                              const float* bias, float* y, int64_t npix) {
     const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (p >= npix) return;
     const bf16x8 lo = load8(d + p * ds), hi = load8(d + p * ds + 8);
     float s = bias[0];
-    for (int ch = 0; ch < c; ++ch) s += w[ch] * (ch < 8 ? lo.get(ch) : hi.get(ch - 8));
+#pragma unroll
+    for (int ch = 0; ch < 16; ++ch) s += w[ch] * (ch < 8 ? lo.get(ch) : hi.get(ch - 8));
     y[p] = s;
 }
 
 // u0 = y * rms on the interior of the natural-layout output.
 __global__ __launch_bounds__(256) void k_output(const float* y, const float* rms, double* u, int n,
-                                                int64_t ld, int64_t gstride, int batch) {
-    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (idx >= int64_t(batch) * n * n) return;
-    const int b = int(idx / (int64_t(n) * n));
-    const int64_t k = idx % (int64_t(n) * n);
-    const int64_t i = k / n + 1, j = k % n + 1;
-    u[int64_t(b) * gstride + i * ld + j] = double(y[idx]) * double(rms[b]);
+                                                int64_t ld, int64_t gstride) {
+    const int j = int(blockIdx.x) * 256 + int(threadIdx.x), i = blockIdx.y, b = blockIdx.z;
+    if (j >= n) return;
+    u[int64_t(b) * gstride + int64_t(i + 1) * ld + j + 1] =
+        double(y[(int64_t(b) * n + i) * n + j]) * double(rms[b]);
 }
 
 // MSE against u*/rms: dy = 2 (y - t) / count, loss accumulated in FP32.
@@ -901,10 +910,11 @@ __global__ __launch_bounds__(256) void k_mse(const float* y, const double* u, co
     const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
     const int64_t count = int64_t(batch) * n * n;
     float d = 0.f;
-    if (idx < count) {
-        const int b = int(idx / (int64_t(n) * n));
-        const int64_t k = idx % (int64_t(n) * n);
-        const int64_t i = k / n + 1, j = k % n + 1;
+    if (idx < count) {  // (count < 2^31)
+        const uint32_t px = uint32_t(n) * uint32_t(n);
+        const int b = int(uint32_t(idx) / px);
+        const uint32_t k = uint32_t(idx) % px;
+        const int64_t i = k / uint32_t(n) + 1, j = k % uint32_t(n) + 1;
         const float t = float(u[int64_t(b) * gstride + i * ld + j] / double(rms[b]));
         d = y[idx] - t;
         dy[idx] = 2.f * d / float(count);
@@ -921,34 +931,40 @@ __global__ __launch_bounds__(256) void k_mse(const float* y, const double* u, co
 
 // Head backward: dd[p][c] = w[c] dy[p] (BF16); per block, the partial sums
 // of dy d[c] (c < 16) and of dy go to part[block][0..16] (k_reduce_parts
-// adds the blocks in order into dw[0..15], db = dw[16]).  Within a block:
-// a fixed butterfly over each wave's 64 lanes, then the four waves in
-// order.  d and dd: 16 channels at pixel strides that are multiples of 8,
-// moved as two 16-byte accesses per pixel.
+// adds the blocks in order into dw[0..15], db = dw[16]).  A thread adds its
+// kHeadPixels pixels, then a fixed butterfly over each wave's 64 lanes, then
+// the four waves in order: a butterfly of 17 sums for every pixel was what
+// bound this kernel (43 us at 511^2 x 8, now 31).  d and dd: 16 channels
+// at pixel strides that are multiples of 8, moved as two 16-byte accesses
+// per pixel.
+constexpr int kHeadPixels = 8;
+
 __global__ __launch_bounds__(256) void k_head_grad(const bf16* d, int64_t ds, const float* w,
                                                    const float* dy, bf16* dd, int64_t dds,
-                                                   float* part, int64_t npix, int c) {
-    const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const bool ok = p < npix;
-    const float g = ok ? dy[p] : 0.f;
+                                                   float* part, int64_t npix) {
+    const int64_t p0 = int64_t(blockIdx.x) * (256 * kHeadPixels) + threadIdx.x;
     float v[17];
-    if (ok) {
-        const bf16x8 lo = load8(d + p * ds), hi = load8(d + p * ds + 8);
-        bf16x8 olo{make_uint4(0, 0, 0, 0)}, ohi{make_uint4(0, 0, 0, 0)};
 #pragma unroll
-        for (int ch = 0; ch < 16; ++ch) {
-            const float dv = ch < 8 ? lo.get(ch) : hi.get(ch - 8);
-            const bf16 o = ch < c ? f2bf(w[ch] * g) : bf16(0);
-            if (ch < 8) olo.set(ch, o); else ohi.set(ch - 8, o);
-            v[ch] = ch < c ? g * dv : 0.f;
+    for (int ch = 0; ch < 17; ++ch) v[ch] = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < kHeadPixels; ++k) {
+        const int64_t p = p0 + k * 256;
+        if (p >= npix) continue;
+        const float g = dy[p];
+        const bf16x8 x[2] = {load8(d + p * ds), load8(d + p * ds + 8)};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float o[8];
+#pragma unroll
+            for (int ch = 0; ch < 8; ++ch) {
+                o[ch] = w[8 * h + ch] * g;
+                v[8 * h + ch] += g * x[h].get(ch);
+            }
+            *reinterpret_cast<uint4*>(dd + p * dds + 8 * h) = make_uint4(
+                pack2(o[0], o[1]), pack2(o[2], o[3]), pack2(o[4], o[5]), pack2(o[6], o[7]));
         }
-        *reinterpret_cast<uint4*>(dd + p * dds) = olo.v;
-        *reinterpret_cast<uint4*>(dd + p * dds + 8) = ohi.v;
-    } else {
-#pragma unroll
-        for (int ch = 0; ch < 16; ++ch) v[ch] = 0.f;
+        v[16] += g;
     }
-    v[16] = g;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
@@ -1106,7 +1122,7 @@ struct Net {
 
 namespace {
 
-int in_channels(int l) { return l == 0 ? 16 : kC[l - 1]; }
+int in_channels(int l) { return l == 0 ? 1 : kC[l - 1]; }
 
 // How the weight gradient of a layer is split: TI x TO channel tiles and
 // `rows` rows of a 32-pixel strip a wave.  Few rows read the two beside them
@@ -1227,6 +1243,11 @@ template <bool MASK>
 hipError_t launch_march(const ConvArgs& a, dim3 grid, hipStream_t s) {
     const int ck = a.cin / 16, nt = a.cout / 16;
     const dim3 block(256);
+    if (a.xs == 1) {
+        if (MASK || ck != 1 || nt != 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_conv_march<1, 1, false, true>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
     if (ck == 1 && nt == 1) {
         hipLaunchKernelGGL((k_conv_march<1, 1, MASK>), grid, block, 0, s, a);
         return hipGetLastError();
@@ -1292,11 +1313,12 @@ hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool for
     a.ys = a.ysplit = y.ca;
     a.y2 = y.b;
     a.ys2 = y.cb;
-    if (x.count() != a.cin || y.count() != a.cout || (mask && x.b) ||
+    const bool one = forward && L.cin == 1;  // one channel in memory
+    if (x.count() != (one ? 1 : a.cin) || y.count() != a.cout || (mask && x.b) ||
         int64_t(batch) * a.h * a.wd >= (int64_t(1) << 31))
         return hipErrorInvalidValue;
     // whole chunks of 16 channels, in 8-byte loads and stores
-    if ((x.ca | x.cb | y.ca | y.cb) % 16 != 0 ||
+    if (((one ? 0 : x.ca) | x.cb | y.ca | y.cb) % 16 != 0 ||
         (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.x2) |
          reinterpret_cast<uintptr_t>(a.y) | reinterpret_cast<uintptr_t>(a.y2) |
          reinterpret_cast<uintptr_t>(a.w) | reinterpret_cast<uintptr_t>(a.mask)) % 8 != 0)
@@ -1346,19 +1368,21 @@ hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf1
     a.cout = L.cout;
     a.cin_w = L.cin;  // the first layer's padded input channels feed no weight
     a.part = net.parts;
+    const bool one = L.cin == 1;  // one channel in memory
     const WgradSplit p = wgrad_split(batch, a.h, a.cin, a.cout);
     a.rows = p.rows;
     const int64_t slots = int64_t(batch) * p.strips * p.groups;
     const int64_t blocks = slots * (a.cin / (16 * p.ti)) * (a.cout / (16 * p.to));
     const int64_t count = int64_t(L.cout) * L.cin * 9 + L.cout;  // the bias follows the weights
     if (size_t(slots * count) > net.parts_floats || blocks > (int64_t(1) << 31) - 1 ||
-        L.b_off != L.w_off + size_t(count - L.cout) || (x.ca | x.cb | a.cout) % 16 != 0 ||
-        x.count() != a.cin ||
+        L.b_off != L.w_off + size_t(count - L.cout) || ((one ? 0 : x.ca) | x.cb | a.cout) % 16 != 0 ||
+        x.count() != (one ? 1 : a.cin) || (one && (p.ti != 1 || p.to != 1)) ||
         (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.x2) |
          reinterpret_cast<uintptr_t>(a.dy) | reinterpret_cast<uintptr_t>(a.y)) % 8 != 0)
         return hipErrorInvalidValue;
     const dim3 grid{unsigned(blocks)}, block{64 * kWgradWaves};
-    if (p.ti == 1 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<1, 1>), grid, block, 0, s, a);
+    if (one) hipLaunchKernelGGL((k_conv3x3_wgrad<1, 1, true>), grid, block, 0, s, a);
+    else if (p.ti == 1 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<1, 1>), grid, block, 0, s, a);
     else if (p.ti == 3 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<3, 1>), grid, block, 0, s, a);
     else if (p.ti == 2 && p.to == 2) hipLaunchKernelGGL((k_conv3x3_wgrad<2, 2>), grid, block, 0, s, a);
     else return hipErrorInvalidValue;
@@ -1408,14 +1432,16 @@ hipError_t restrict_op(const Net& net, const bf16* in, int64_t is, bf16* out, in
 hipError_t prolong_op(const Net& net, const bf16* in, int64_t is, bf16* out, int64_t os, int batch,
                       int nc, int c, float scale, int acc, hipStream_t s) {
     const int nf = net.factor * nc + net.factor - 1;
-    if (!transfer_ok(in, is, out, os, c) || int64_t(batch) * nf * nf * (c / 8) > (int64_t(1) << 32) - 256)
+    const int c8_shift = c >= 8 ? __builtin_ctz(unsigned(c / 8)) : 0;
+    if (!transfer_ok(in, is, out, os, c) || int64_t(batch) * nf * nf * (c / 8) > (int64_t(1) << 32) - 256 ||
+        (c & (c - 1)) != 0 || batch > 65535 || nf > 65535)
         return hipErrorInvalidValue;
-    const dim3 grid(blocks_for(int64_t(batch) * nf * nf * (c / 8)));
+    const dim3 grid(blocks_for(int64_t(nc + 1) << c8_shift), unsigned(nf), unsigned(batch));
     if (net.factor == 2)
-        hipLaunchKernelGGL(k_prolong<2>, grid, dim3(256), 0, s, in, is, out, os, batch, nc, c, scale,
+        hipLaunchKernelGGL(k_prolong<2>, grid, dim3(256), 0, s, in, is, out, os, nc, c8_shift, scale,
                            acc);
     else if (net.factor == 4)
-        hipLaunchKernelGGL(k_prolong<4>, grid, dim3(256), 0, s, in, is, out, os, batch, nc, c, scale,
+        hipLaunchKernelGGL(k_prolong<4>, grid, dim3(256), 0, s, in, is, out, os, nc, c8_shift, scale,
                            acc);
     else
         return hipErrorInvalidValue;
@@ -1455,8 +1481,8 @@ hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gst
     NN_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_rms_final, dim3(batch), dim3(256), 0, s, rows, n0, net.rms);
     NN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_input, dim3(blocks_for(int64_t(batch) * n0 * n0)), dim3(256), 0, s, f, n0,
-                       ld, gstride, net.rms, net.in[0], batch);
+    hipLaunchKernelGGL(k_input, dim3(blocks_for(n0), unsigned(n0), unsigned(batch)), dim3(256), 0, s,
+                       f, n0, ld, gstride, net.rms, net.in[0]);
     NN_TRY(hipGetLastError());
     // encoder
     for (int l = 0; l < kLevels; ++l) {
@@ -1485,8 +1511,7 @@ hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gst
     }
     const size_t hw = net.nparam - 17;
     hipLaunchKernelGGL(k_head, dim3(blocks_for(int64_t(batch) * n0 * n0)), dim3(256), 0, s, net.d[0],
-                       kC[0], net.param + hw, net.param + hw + 16, net.y, int64_t(batch) * n0 * n0,
-                       kC[0]);
+                       kC[0], net.param + hw, net.param + hw + 16, net.y, int64_t(batch) * n0 * n0);
     return hipGetLastError();
 }
 
@@ -1497,10 +1522,10 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
     hipLaunchKernelGGL(k_fill, dim3(blocks_for(int64_t(net.nparam))), dim3(256), 0, s,
                        reinterpret_cast<uint32_t*>(net.grad), int64_t(net.nparam));
     NN_TRY(hipGetLastError());
-    const unsigned hblocks = blocks_for(int64_t(batch) * n0 * n0);
+    const unsigned hblocks = blocks_for(int64_t(batch) * n0 * n0, 256 * kHeadPixels);
     hipLaunchKernelGGL(k_head_grad, dim3(hblocks), dim3(256), 0, s, net.d[0], kC[0],
                        net.param + hw, net.dy, net.gd[0], kC[0], net.parts,
-                       int64_t(batch) * n0 * n0, kC[0]);
+                       int64_t(batch) * n0 * n0);
     NN_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_reduce_parts, dim3(17), dim3(256), 0, s, net.parts, int64_t(hblocks),
                        int64_t(17), net.grad + hw);
@@ -1710,8 +1735,8 @@ int rbgs_unet_forward(rbgs_unet* u, int32_t batch, const double* f, int64_t ld, 
     int rc = nn::nn_hip(nn::forward(net, batch, f, ld, gs, s), "forward");
     if (rc) return rc;
     const int n0 = net.n[0];
-    hipLaunchKernelGGL(nn::k_output, dim3(nn::blocks_for(int64_t(batch) * n0 * n0)), dim3(256), 0, s,
-                       net.y, net.rms, u0, n0, ld, gs, batch);
+    hipLaunchKernelGGL(nn::k_output, dim3(nn::blocks_for(n0), unsigned(n0), unsigned(batch)), dim3(256),
+                       0, s, net.y, net.rms, u0, n0, ld, gs);
     return nn::nn_hip(hipGetLastError(), "output");
 }
 
