@@ -322,17 +322,20 @@ int rbgs_solve(const rbgs_grid *g, rbgs_dtype dt, void *u, const void *f,
                void *workspace, size_t workspace_bytes, void *stream);
 
 /* ---------------------------------------------------------------------
- * Batches of independent grids (one persistent launch for all of them).
+ * Batches of independent grids (each launch for all of them).
  * Grid g has its own size grids[g], device arrays u[g] and f[g] (natural
- * layout, type dt; the HOST arrays u and f hold the device pointers).  Work
- * items are (pass, grid, tile) of the persistent blocked kernel, handed out
- * pass by pass with the largest grids first; each grid's tiles follow the
- * same dependency rule as a single grid, so every grid's result is bitwise
- * what rbgs_sweep gives it alone.  Small grids (opts->lds_max_n) are instead
- * swept entirely in one workgroup's LDS, with the same operations in the
- * same order, hence the same bits.  count in [1, 65535].
- * opts: kernel must be AUTO or BLOCKED; fuse/tile_rows 0 take the values
- * rbgs_autotune_batched stored for this batch shape (else the defaults).
+ * layout, type dt; the HOST arrays u and f hold the device pointers).
+ * count in [1, 65535].  opts: kernel must be AUTO or BLOCKED.
+ * AUTO with every tuning and debug option 0, and no grid above 4095 (FP64) /
+ * 10000 (FP32): launches of up to 4 - 6 sweeps over the register windows of
+ * all grids.  Otherwise the persistent blocked kernel: work items (pass,
+ * grid, tile), handed out pass by pass with the largest grids first; each
+ * grid's tiles follow the same dependency rule as a single grid; small grids
+ * (opts->lds_max_n) are instead swept entirely in one workgroup's LDS;
+ * fuse/tile_rows/lds_max_n 0 take the values rbgs_autotune_batched stored
+ * for this batch shape (else the defaults).  Either way every operation and
+ * its order is rbgs_sweep's, so each grid's result is bitwise what that
+ * gives it alone.
  * --------------------------------------------------------------------- */
 
 /* Workspace bytes for a batch (0 for invalid arguments). */
@@ -347,7 +350,7 @@ int rbgs_sweep_batched(int32_t count, const rbgs_grid *grids, rbgs_dtype dt,
                        const rbgs_sweep_opts *opts, void *workspace,
                        size_t workspace_bytes, void *stream);
 
-/* A batched sweep captured once into a HIP graph (pack, persistent
+/* A batched sweep captured once into a HIP graph (pack, sweep
  * kernel(s), unpack; flags and tickets are cleared by kernels inside the
  * graph, so every replay starts clean).  The plan keeps the pointers given
  * here: u, f and the workspace must stay allocated while it is used.  Each

@@ -1,6 +1,8 @@
-// Batched persistent sweep: many independent grids of uneven sizes in one
-// launch of the tile pipeline (blocked_pipeline.h), plus the batched
-// pack/unpack kernels, the graph-captured plan and the autotuner.
+// Batched sweeps: many independent grids of uneven sizes, by register windows
+// (batched_window.hip) where the caller leaves the way open, else in one
+// launch of the tile pipeline (blocked_pipeline.h); plus the batched
+// pack/unpack kernels, the graph-captured plan and the autotuner (of the
+// pipeline).  Of the pipeline:
 //
 // Work items are (pass, grid, tile).  Tickets run pass-major, and inside a
 // pass the grids are ordered largest first (longest-processing-time first),
@@ -289,7 +291,34 @@ struct BatchSetup {
     std::vector<int> tile_map;
     std::vector<int> small_ids;  // grids swept LDS-resident by k_batch_lds
     size_t small_lds_bytes = 0;  // dynamic LDS for the largest of them
+    // Swept by windows (win.passes > 0): tile_map holds the grids' order and
+    // small_ids their first windows instead.
+    BatchWindows win;
 };
+
+// Whether the caller leaves the way of sweeping a batch open.
+bool batch_open(const rbgs_sweep_opts* o) {
+    return !o || (o->kernel == RBGS_KERNEL_AUTO && o->fuse == 0 && o->tile_rows == 0 &&
+                  o->lds_max_n == 0 && o->debug_delay == 0 && o->debug_spin_limit == 0 &&
+                  o->debug_stall_tile == 0);
+}
+
+// Makes a batch's sweeps run by windows, where they are the choice.
+void choose_windows(BatchSetup& s, int count, const rbgs_grid* grids, size_t es, int nsweeps,
+                    const rbgs_sweep_opts* o) {
+    if (!batch_open(o) || nsweeps < 1) return;
+    std::vector<int> n(static_cast<size_t>(count)), first, order;
+    for (int g = 0; g < count; ++g) n[size_t(g)] = grids[g].n;
+    BatchWindows b;
+    b.nsweeps = nsweeps;
+    if (!batch_windows(count, n.data(), es, nsweeps, &b, &first, &order)) return;
+    s.win = b;
+    s.small_ids = std::move(first);
+    s.tile_map = std::move(order);
+    s.total_tiles = 0;
+    s.small_lds_bytes = 0;
+}
+
 
 // LDS-resident threshold the autotuner tries: the largest grid of the
 // benchmark's size mix that fits (127 in FP32: 133 KB; 63 in FP64: 68 KB).
@@ -450,6 +479,18 @@ hipError_t enqueue_batch(const BatchSetup& su, const BatchLayout& lay, char* ws,
     qu.stop = nullptr;
     // the error word is cleared once; tickets and flags before every launch
     if ((e = launch_zero(ws + lay.header, 256, s)) != hipSuccess) return e;
+    if (su.win.passes > 0) {
+        const int* first = reinterpret_cast<const int*>(ws + lay.small);
+        for (int p = 0; p < su.win.passes; ++p)
+            if ((e = launch_batch_pass<T>(su.win, gd, first, map, p, s)) != hipSuccess) return e;
+        if (do_unpack) {
+            hipLaunchKernelGGL((k_batch_unpack<typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type>),
+                               dim3(unsigned(su.total_rows)), dim3(256), 0, s, pd, count,
+                               su.win.passes & 1);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     int parity = 0;
     // full passes of `fuse` sweeps, then (if nsweeps is not a multiple) one
     // pass of the remaining sweeps; its smaller depth fits the same tiles,
@@ -648,7 +689,8 @@ int sweep_batched_t(int32_t count, const rbgs_grid* grids, void* const* u, const
     const BatchLayout lay = batch_layout(count, grids, dt);
     int fuse = 0, rows = 0, lds = 0;
     choose_params(count, grids, dt, o, &fuse, &rows, &lds);
-    const BatchSetup su = build_setup<T>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
+    BatchSetup su = build_setup<T>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
+    choose_windows(su, count, grids, sizeof(T), nsweeps, o);
     int rc = upload_setup<T>(su, lay, ws, count, s);
     if (rc) return rc;
     EventPair ev;
@@ -665,7 +707,8 @@ int sweep_batched_t(int32_t count, const rbgs_grid* grids, void* const* u, const
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, ev.a, ev.b);
         const int tiled = su.total_tiles > 0 ? (su.passes > 0) + (su.rem > 0) : 0;
-        *o->timing = rbgs_timing{0.f, ms, 0.f, tiled + (su.small_ids.empty() ? 0 : 1)};
+        const int launches = tiled + (su.small_ids.empty() ? 0 : 1);
+        *o->timing = rbgs_timing{0.f, ms, 0.f, su.win.passes > 0 ? su.win.passes : launches};
     }
     return read_error_word(lay, ws, s);
 }
@@ -1080,9 +1123,11 @@ int rbgs_batch_plan_create(rbgs_batch_plan** plan, int32_t count, const rbgs_gri
     BatchSetup su;
     if (dt == RBGS_F64) {
         su = build_setup<double>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
+        choose_windows(su, count, grids, 8, nsweeps, opts);
         rc = upload_setup<double>(su, lay, ws, count, cs);
     } else {
         su = build_setup<float>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
+        choose_windows(su, count, grids, 4, nsweeps, opts);
         rc = upload_setup<float>(su, lay, ws, count, cs);
     }
     if (rc) {

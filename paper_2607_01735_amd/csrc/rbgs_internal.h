@@ -15,6 +15,7 @@
 // once: 3 words per point update instead of the 6 of the natural layout.
 #pragma once
 
+#include <vector>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -92,6 +93,23 @@ bool window_takes(int n, size_t elem_bytes, int nsweeps);  // whether it is the 
 int window_fuse(int n, size_t elem_bytes);  // most sweeps a launch
 template <typename T>
 hipError_t launch_window(const WindowArgs<T>& a, int sweeps, hipStream_t s);
+
+// The same over a batch of grids (batched_window.hip).
+struct BatchWindows {
+    int count = 0, nsweeps = 0;
+    int passes = 0;   // 0: not by windows
+    int top = 0;      // sweeps of the deepest pass (the others run top - 1)
+    int rows = 0;     // rows a window writes
+    int windows = 0;  // of all grids
+};
+// The split of a batch (grid sizes n) and its tables; false: not the choice.
+bool batch_windows(int count, const int* n, size_t elem_bytes, int nsweeps, BatchWindows* b,
+                   std::vector<int>* first, std::vector<int>* order);
+// Pass 0 .. passes - 1; pass p reads buffer p & 1 and writes the other (red
+// only in the last).  grids: GridDesc<T>[count] in device memory.
+template <typename T>
+hipError_t launch_batch_pass(const BatchWindows& b, const void* grids, const int* first,
+                             const int* order, int pass, hipStream_t s);
 
 // Number of partial-sum slots the residual kernels need for grid size n.
 int residual_partial_slots(int n, int64_t pitch, size_t elem_bytes);

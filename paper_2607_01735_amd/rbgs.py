@@ -686,7 +686,7 @@ def rbgs_batch_workspace_size(us, fs, hs=None):
 
 def rbgs_sweep_batched(us, fs, nsweeps, hs=None, workspace=None, stream=None, timing=False,
                        **tuning):
-    """nsweeps sweeps of every grid in one persistent launch (synchronises)."""
+    """nsweeps sweeps of every grid, each launch for all of them (synchronises)."""
     b = _Batch(us, fs, hs)
     ws = b.workspace(workspace)
     t = rbgs_timing() if timing else None
