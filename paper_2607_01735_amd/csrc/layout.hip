@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void k_pack_grid(const W* __restrict__ u,
 // those q comes along, harmlessly).  The first 2 x parts workgroups take 64
 // columns of the two whole rows each, the others two points of 32 rows (one
 // workgroup per row, whose wave went through a whole row 64 columns at a time:
-// 34 us at 8191^2, now 5).
+// 34 us at 8191^2, now 8).
 template <typename W>
 __global__ __launch_bounds__(64) void k_copy_ring(W* __restrict__ dst_red, W* __restrict__ dst_black,
                                                   const W* __restrict__ src_red,

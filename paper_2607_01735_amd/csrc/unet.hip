@@ -178,8 +178,8 @@ struct RowLanes {
     }
 };
 
-// Few channels, many pixels (cin = 16 or 48: the finest level, and the first
-// convolution of the next).  Bound by memory: 16 -> 16 channels moves 64
+// Few channels, many pixels (cin = 16, 32 or 48: the finest level, and the next
+// but for its 96).  Bound by memory: 16 -> 16 channels moves 64
 // bytes a pixel for 9 MFMAs per 16 pixels.  So every input element is loaded
 // once: a wave takes kConvGroups x 16 pixels of `rows` rows and walks down
 // them with the layer's weights and the operands of three rows in registers.
@@ -187,7 +187,8 @@ struct RowLanes {
 // 512-byte line per 16 pixels and chunk.  511^2 x 8: 16 -> 16 channels 33 us
 // (134 MB, 4.1 TB/s), 48 -> 16 72 us, masked 16 -> 16 42 us, 16 -> 48 90 us;
 // a wave per 32 outputs of a row, which loaded three rows three times over
-// behind its loads of weights, took 86, 255, 109 and 194 us.
+// behind its loads of weights, took 86, 255, 109 and 194 us.  32 -> 32 at
+// 127^2 x 8 10 us, masked 12 (k_conv_deep 15 and 24).
 template <int CK, int NT, bool MASK, bool ONE = false>
 __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     constexpr int PG = kConvGroups;
@@ -195,8 +196,11 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     int wave = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
     const int strips = (a.wd + 16 * PG - 1) / (16 * PG);
     const int bands = (a.h + a.rows - 1) / a.rows;
-    if (wave >= a.batch * bands * strips) return;
+    const int cts = a.cout / (16 * NT);
+    if (wave >= a.batch * bands * strips * cts) return;
     wave = __builtin_amdgcn_readfirstlane(wave);
+    const int t0 = (wave % cts) * NT;  // first output tile
+    wave /= cts;
     const int x0 = (wave % strips) * 16 * PG;
     const int band = (wave / strips) % bands;
     const int b = wave / (strips * bands);
@@ -211,12 +215,12 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 w[c][k][t] = *reinterpret_cast<const u32x2*>(
-                    a.w + (((t * CK + c) * 9 + k) * 64 + lane) * 4);
+                    a.w + ((((t0 + t) * CK + c) * 9 + k) * 64 + lane) * 4);
     f32x4 bias[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bias[t][i] = a.bias ? a.bias[t * 16 + kq + i] : 0.f;
+        for (int i = 0; i < 4; ++i) bias[t][i] = a.bias ? a.bias[(t0 + t) * 16 + kq + i] : 0.f;
 
     const RowLanes<PG> lanes(x0, n, a.wd);
     RowPixels<PG> raw[3][CK], msk[3][CK];
@@ -269,12 +273,13 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
                 if (lanes.ok[g])
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        store_pixel(a, pix + lanes.px[g], t * 16 + kq, acc[g][t], bias[t]);
+                        store_pixel(a, pix + lanes.px[g], (t0 + t) * 16 + kq, acc[g][t],
+                                    bias[t]);
         }
     }
 }
 
-// Many channels, fewer pixels (cin a multiple of 32: the coarser levels).
+// Many channels, fewer pixels (cin a multiple of 32, from 64: the coarser levels).
 // D divides the number of chunks.  Bound by latency: an output's 9 cin / 16 MFMAs are a chain of at most 108,
 // under a microsecond, but each group of them waits for its loads.  So a
 // wave takes few outputs (PG x 16 pixels, NT x 16 channels) and keeps the
@@ -620,17 +625,32 @@ __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ 
     if (threadIdx.x == 0) out[e] = sh[0];
 }
 
-// The same sums for many elements, coalesced: a block takes 64 consecutive
-// elements, its 16 waves the slots w, w + 16, ... (64 consecutive floats of
-// a slot at a time, four partial sums), whose sums are added in the waves'
-// order.  A fixed order again.  (512 slots of 2320: 6.5 us.)
+// The same sums for many elements and all layers at once, coalesced: a block
+// takes 64 consecutive elements of a layer, its 16 waves the slots w, w + 16,
+// ... (64 consecutive floats of a slot at a time, four partial sums), whose
+// sums are added in the waves' order.  A fixed order again.  (A launch a layer
+// took 4.5 to 7 us, 14 times, 76 in all at 511^2 x 8; now 49.)
 constexpr int kReduceWaves = 16;
+constexpr int kMaxLayers = 16;
 
-__global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_slots(const float* __restrict__ part,
-                                                                    int64_t nparts, int64_t count,
-                                                                    float* __restrict__ out) {
+struct ReduceArgs {
+    int layers = 0;
+    struct {
+        const float* part;
+        float* out;
+        int64_t slots, count;
+        int first;  // block
+    } l[kMaxLayers];
+};
+
+__global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_slots(ReduceArgs a) {
+    int layer = a.layers - 1;
+    while (layer > 0 && int(blockIdx.x) < a.l[layer].first) --layer;
+    const auto& L = a.l[layer];
+    const float* __restrict__ part = L.part;
+    const int64_t nparts = L.slots, count = L.count;
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int64_t e = int64_t(blockIdx.x) * 64 + l;
+    const int64_t e = int64_t(int(blockIdx.x) - L.first) * 64 + l;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     if (e < count)
         for (int64_t k = g; k < nparts; k += 4 * kReduceWaves) {
@@ -649,7 +669,7 @@ __global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_slots(const float*
     if (g == 0 && e < count) {
         float s = sh[0][l];
         for (int w = 1; w < kReduceWaves; ++w) s += sh[w][l];
-        out[e] = s;
+        L.out[e] = s;
     }
 }
 
@@ -987,8 +1007,6 @@ __global__ __launch_bounds__(256) void k_head_grad(const bf16* d, int64_t ds, co
 // columns][tap][lane][4]: a lane's four columns of one row (ConvArgs); as
 // [row][tap][column] each 8-byte load touched 16 lines.  One launch for all
 // layers: a layer's elements start at block `first`.
-constexpr int kMaxLayers = 16;
-
 struct PrepArgs {
     const float* param;
     int layers;
@@ -1152,10 +1170,9 @@ WgradSplit wgrad_split(int batch, int n, int cin_p, int cout) {
     return p;
 }
 
-// Floats of partial sums the largest fixed-order reduction needs: a layer's
-// gradients (a slot of cout x cin x 9 and cout per workgroup; no batch has
-// more slots than the largest), the head (blocks of 17), the loss and the rms
-// row sums.
+// Floats of partial sums the largest fixed-order reduction needs: all layers'
+// gradients (a slot of cout x cin x 9 and cout per workgroup, for the batch
+// that has most), the head (blocks of 17), the loss and the rms row sums.
 size_t wgrad_floats(const Net& net, const Layer& l) {
     size_t most = 0;
     for (int b = 1; b <= net.batch; ++b) {
@@ -1166,11 +1183,12 @@ size_t wgrad_floats(const Net& net, const Layer& l) {
 }
 
 size_t parts_floats(const Net& net) {
-    size_t most = 0;
+    size_t most = 0, sum = 0;
     const size_t B = size_t(net.batch);
     for (const auto& l : net.layers) {
-        most = std::max(most, wgrad_floats(net, l));
+        sum += wgrad_floats(net, l);
     }
+    most = sum;
     const size_t px0 = B * size_t(net.n[0]) * size_t(net.n[0]);
     most = std::max(most, (px0 + 255) / 256 * 17);
     most = std::max(most, 2 * B * size_t(net.n[0]));  // the rms row sums (doubles)
@@ -1252,10 +1270,18 @@ hipError_t launch_march(const ConvArgs& a, dim3 grid, hipStream_t s) {
         hipLaunchKernelGGL((k_conv_march<1, 1, MASK>), grid, block, 0, s, a);
         return hipGetLastError();
     }
+    if (ck == 2 && nt % 2 == 0) {
+        hipLaunchKernelGGL((k_conv_march<2, 2, MASK>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
     // the other shapes occur in one direction each
     if constexpr (MASK) {
-        if (ck != 1 || nt != 3) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_conv_march<1, 3, true>), grid, block, 0, s, a);
+        if (ck == 1 && nt == 3)
+            hipLaunchKernelGGL((k_conv_march<1, 3, true>), grid, block, 0, s, a);
+        else if (ck == 2 && nt == 1)
+            hipLaunchKernelGGL((k_conv_march<2, 1, true>), grid, block, 0, s, a);
+        else
+            return hipErrorInvalidValue;
     } else if (ck == 1 && nt == 2) {
         hipLaunchKernelGGL((k_conv_march<1, 2, false>), grid, block, 0, s, a);
     } else if (ck == 3 && nt == 1) {
@@ -1323,10 +1349,14 @@ hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool for
          reinterpret_cast<uintptr_t>(a.y) | reinterpret_cast<uintptr_t>(a.y2) |
          reinterpret_cast<uintptr_t>(a.w) | reinterpret_cast<uintptr_t>(a.mask)) % 8 != 0)
         return hipErrorInvalidValue;
-    if (a.cin % 32 != 0) {
+    // 32 channels: down the rows where there are waves enough for that (32 -> 64
+    // at 31^2 x 8: 8.5 us against 5.6)
+    const int64_t strip_rows = int64_t(batch) * a.h * ((a.wd + 31) / 32) * (a.cout / 16);
+    if (a.cin % 32 != 0 || (a.cin == 32 && strip_rows >= 4096)) {
         // Rows of a wave: two rows more are read than written, so as many as
         // still leave four waves a SIMD on 256 CUs.
-        const int64_t strips = int64_t(batch) * ((a.wd + 16 * kConvGroups - 1) / (16 * kConvGroups));
+        const int64_t strips = int64_t(batch) * ((a.wd + 16 * kConvGroups - 1) / (16 * kConvGroups)) *
+                               (a.cin == 32 && a.cout % 32 == 0 ? a.cout / 32 : 1);
         // (Three rows a step of the kernel: rows + 2 a multiple of 3.)
         a.rows = int(std::max<int64_t>(strips * a.h / 4096, 4));
         a.rows -= (a.rows + 2) % 3;
@@ -1350,8 +1380,16 @@ hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool for
     return mask ? launch_deep<true>(a, pg, nt, grid, s) : launch_deep<false>(a, pg, nt, grid, s);
 }
 
-hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf16* y, int batch,
-                 hipStream_t s) {
+// The backward pass's partial sums: where the next layer's go, and what
+// k_reduce_slots then adds.
+struct Partials {
+    ReduceArgs args;
+    size_t used = 0;  // floats
+    int blocks = 0;
+};
+
+hipError_t wgrad(const Net& net, Partials& parts, const Layer& L, In x, const bf16* dy, const bf16* y,
+                 int batch, hipStream_t s) {
     const int64_t dys = L.cout, ys = L.cout;
     WGradArgs a;
     a.x = x.a;
@@ -1367,14 +1405,15 @@ hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf1
     a.cin = L.cin_p;
     a.cout = L.cout;
     a.cin_w = L.cin;  // the first layer's padded input channels feed no weight
-    a.part = net.parts;
+    a.part = net.parts + parts.used;
     const bool one = L.cin == 1;  // one channel in memory
     const WgradSplit p = wgrad_split(batch, a.h, a.cin, a.cout);
     a.rows = p.rows;
     const int64_t slots = int64_t(batch) * p.strips * p.groups;
     const int64_t blocks = slots * (a.cin / (16 * p.ti)) * (a.cout / (16 * p.to));
     const int64_t count = int64_t(L.cout) * L.cin * 9 + L.cout;  // the bias follows the weights
-    if (size_t(slots * count) > net.parts_floats || blocks > (int64_t(1) << 31) - 1 ||
+    if (parts.used + size_t(slots * count) > net.parts_floats || parts.args.layers == kMaxLayers ||
+        blocks > (int64_t(1) << 31) - 1 ||
         L.b_off != L.w_off + size_t(count - L.cout) || ((one ? 0 : x.ca) | x.cb | a.cout) % 16 != 0 ||
         x.count() != (one ? 1 : a.cin) || (one && (p.ti != 1 || p.to != 1)) ||
         (reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.x2) |
@@ -1386,10 +1425,9 @@ hipError_t wgrad(const Net& net, const Layer& L, In x, const bf16* dy, const bf1
     else if (p.ti == 3 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<3, 1>), grid, block, 0, s, a);
     else if (p.ti == 2 && p.to == 2) hipLaunchKernelGGL((k_conv3x3_wgrad<2, 2>), grid, block, 0, s, a);
     else return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_slots, dim3(unsigned((count + 63) / 64)), dim3(64 * kReduceWaves), 0, s,
-                       net.parts, slots, count, net.grad + L.w_off);
+    parts.args.l[parts.args.layers++] = {a.part, net.grad + L.w_off, slots, count, parts.blocks};
+    parts.used += size_t(slots * count);
+    parts.blocks += int((count + 63) / 64);
     return hipGetLastError();
 }
 
@@ -1530,6 +1568,7 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce_parts, dim3(17), dim3(256), 0, s, net.parts, int64_t(hblocks),
                        int64_t(17), net.grad + hw);
     NN_TRY(hipGetLastError());
+    Partials parts;
     // decoder, from level 0 (computed last) up
     for (int l = 0; l < kLevels - 1; ++l) {
         char n0name[8] = "dec0.0", n1name[8] = "dec0.1";
@@ -1537,9 +1576,9 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
         const Layer& c0 = layer(net, n0name);
         const Layer& c1 = layer(net, n1name);
         const int C = kC[l], U = kC[l + 1];
-        NN_TRY(wgrad(net, c1, In{net.adec[l], C}, net.gd[l], net.d[l], batch, s));
+        NN_TRY(wgrad(net, parts, c1, In{net.adec[l], C}, net.gd[l], net.d[l], batch, s));
         NN_TRY(conv(net, c1, In{net.gd[l], C}, net.d[l], false, Out{net.gadec[l], C}, batch, s));
-        NN_TRY(wgrad(net, c0, In{net.up[l], U, net.enc[l], C}, net.gadec[l], net.adec[l], batch, s));
+        NN_TRY(wgrad(net, parts, c0, In{net.up[l], U, net.enc[l], C}, net.gadec[l], net.adec[l], batch, s));
         NN_TRY(conv(net, c0, In{net.gadec[l], C}, net.adec[l], false,
                     Out{net.gup[l], U, net.genc[l], C}, batch, s));
         // up = P(d_{l+1}) with P = F^2 R^T: the gradient reaching d_{l+1} is F^2 R(dup)
@@ -1554,9 +1593,9 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
         const Layer& c0 = layer(net, n0name);
         const Layer& c1 = layer(net, n1name);
         const int C = kC[l];
-        NN_TRY(wgrad(net, c1, In{net.aenc[l], C}, net.genc[l], net.enc[l], batch, s));
+        NN_TRY(wgrad(net, parts, c1, In{net.aenc[l], C}, net.genc[l], net.enc[l], batch, s));
         NN_TRY(conv(net, c1, In{net.genc[l], C}, net.enc[l], false, Out{net.gaenc[l], C}, batch, s));
-        NN_TRY(wgrad(net, c0, In{net.in[l], in_channels(l)}, net.gaenc[l], net.aenc[l], batch, s));
+        NN_TRY(wgrad(net, parts, c0, In{net.in[l], in_channels(l)}, net.gaenc[l], net.aenc[l], batch, s));
         if (l > 0) {
             NN_TRY(conv(net, c0, In{net.gaenc[l], C}, net.aenc[l], false,
                         Out{net.gin[l], in_channels(l)}, batch, s));
@@ -1566,7 +1605,9 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
                               net.n[l], in_channels(l), 1.f / float(net.factor * net.factor), 1, s));
         }
     }
-    return hipSuccess;
+    hipLaunchKernelGGL(k_reduce_slots, dim3(unsigned(parts.blocks)), dim3(64 * kReduceWaves), 0, s,
+                       parts.args);
+    return hipGetLastError();
 }
 
 hipError_t adam(Net& net, float lr, hipStream_t s) {
