@@ -78,6 +78,11 @@ struct ConvArgs {
     int64_t ys2;
     int batch, h, wd, cin, cout, relu, xsplit, ysplit;
     int rows;          // k_conv_march: rows of a wave
+    // k_conv_march<1, 1, false, false, true>: instead of y, the head's output
+    // times rms goes to u (natural layout)
+    const float *head, *rms;  // head: 16 weights, bias
+    double* u;
+    int64_t ld, gstride;
 };
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -104,6 +109,29 @@ template <int CTRL>
 __device__ __forceinline__ u32x2 dpp(u32x2 old, u32x2 v) {
     return u32x2{uint32_t(__builtin_amdgcn_update_dpp(int(old[0]), int(v[0]), CTRL, 0xf, 0xf, false)),
                  uint32_t(__builtin_amdgcn_update_dpp(int(old[1]), int(v[1]), CTRL, 0xf, 0xf, false))};
+}
+
+// The head of one pixel, its 16 channels in the four lane groups (v, four a
+// lane): bias + w[0] d[0] + w[1] d[1] ..., in that order, each lane group
+// handing its sum to the next.  (Inference: the last activations are neither
+// written nor read again, 30 us of 401 at 511^2 x 8.)
+__device__ __forceinline__ float head_pixel(f32x4 v, f32x4 bias, const float (&w)[4], float head_bias,
+                                            int lane) {
+    float d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float r = v[i] + bias[i];
+        d[i] = bf2f(f2bf(r > 0.f ? r : 0.f));
+    }
+    float s = head_bias;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float t = s;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t += w[i] * d[i];
+        s = __shfl(t, k * 16 + (lane & 15), 64);
+    }
+    return s;
 }
 
 __device__ __forceinline__ void store_pixel(const ConvArgs& a, int64_t pix, int co, f32x4 v,
@@ -184,12 +212,12 @@ struct RowLanes {
 // once: a wave takes kConvGroups x 16 pixels of `rows` rows and walks down
 // them with the layer's weights and the operands of three rows in registers.
 // A row is loaded three rows ahead of its use, 8 bytes a lane, a whole
-// 512-byte line per 16 pixels and chunk.  511^2 x 8: 16 -> 16 channels 33 us
-// (134 MB, 4.1 TB/s), 48 -> 16 72 us, masked 16 -> 16 42 us, 16 -> 48 90 us;
+// 512-byte line per 16 pixels and chunk.  511^2 x 8: 16 -> 16 channels 30 us
+// (134 MB, 4.5 TB/s), 48 -> 16 67 us, masked 16 -> 16 39 us, 16 -> 48 85 us;
 // a wave per 32 outputs of a row, which loaded three rows three times over
 // behind its loads of weights, took 86, 255, 109 and 194 us.  32 -> 32 at
 // 127^2 x 8 10 us, masked 12 (k_conv_deep 15 and 24).
-template <int CK, int NT, bool MASK, bool ONE = false>
+template <int CK, int NT, bool MASK, bool ONE = false, bool HEAD = false>
 __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     constexpr int PG = kConvGroups;
     const int lane = threadIdx.x & 63;
@@ -239,6 +267,13 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
                 lanes.load(msk[slot][c], a.mask + pix * a.ms + c * 16, uint32_t(a.ms), uint32_t(kq));
         }
     };
+    float hw[4], hb = 0.f, rms = 0.f;
+    if (HEAD) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hw[i] = a.head[kq + i];
+        hb = a.head[16];
+        rms = a.rms[b];
+    }
     u32x2 op[3][CK][3 * PG];  // three input rows' operands
 #pragma unroll
     for (int k = 0; k < 3; ++k) fetch(k, y0 - 1 + k);
@@ -268,6 +303,15 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
                             acc[g][t] = mfma16(w[c][k][t], op[(u + 1 + k / 3) % 3][c][(k % 3) * PG + g],
                                                acc[g][t]);
             const int64_t pix = int64_t(b * a.h + yi - 1) * a.wd;
+            if constexpr (HEAD) {
+                double* u = a.u + int64_t(b) * a.gstride + int64_t(yi) * a.ld + 1;  // row yi - 1
+#pragma unroll
+                for (int g = 0; g < PG; ++g) {
+                    const float y = head_pixel(acc[g][0], bias[0], hw, hb, lane);
+                    if (lanes.ok[g] && kq == 0) u[lanes.px[g]] = double(y) * double(rms);
+                }
+                continue;
+            }
 #pragma unroll
             for (int g = 0; g < PG; ++g)
                 if (lanes.ok[g])
@@ -614,7 +658,15 @@ __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ 
                                                       float* __restrict__ out) {
     const int64_t e = blockIdx.x;
     float s = 0.f;
-    for (int64_t k = threadIdx.x; k < nparts; k += 256) s += part[k * count + e];
+    // eight loads at a time, added in slot order
+    for (int64_t k0 = threadIdx.x; k0 < nparts; k0 += 8 * 256) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = k0 + i * 256 < nparts ? part[(k0 + i * 256) * count + e] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (k0 + i * 256 < nparts) s += v[i];
+    }
     __shared__ float sh[256];
     sh[threadIdx.x] = s;
     __syncthreads();
@@ -912,15 +964,6 @@ __global__ __launch_bounds__(256) void k_head(const bf16* d, int64_t ds, const f
 #pragma unroll
     for (int ch = 0; ch < 16; ++ch) s += w[ch] * (ch < 8 ? lo.get(ch) : hi.get(ch - 8));
     y[p] = s;
-}
-
-// u0 = y * rms on the interior of the natural-layout output.
-__global__ __launch_bounds__(256) void k_output(const float* y, const float* rms, double* u, int n,
-                                                int64_t ld, int64_t gstride) {
-    const int j = int(blockIdx.x) * 256 + int(threadIdx.x), i = blockIdx.y, b = blockIdx.z;
-    if (j >= n) return;
-    u[int64_t(b) * gstride + int64_t(i + 1) * ld + j + 1] =
-        double(y[(int64_t(b) * n + i) * n + j]) * double(rms[b]);
 }
 
 // MSE against u*/rms: dy = 2 (y - t) / count, loss accumulated in FP32.
@@ -1262,12 +1305,16 @@ hipError_t launch_march(const ConvArgs& a, dim3 grid, hipStream_t s) {
     const int ck = a.cin / 16, nt = a.cout / 16;
     const dim3 block(256);
     if (a.xs == 1) {
-        if (MASK || ck != 1 || nt != 1) return hipErrorInvalidValue;
+        if (MASK || ck != 1 || nt != 1 || a.u) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_conv_march<1, 1, false, true>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     if (ck == 1 && nt == 1) {
-        hipLaunchKernelGGL((k_conv_march<1, 1, MASK>), grid, block, 0, s, a);
+        if (a.u && MASK) return hipErrorInvalidValue;
+        if (a.u)
+            hipLaunchKernelGGL((k_conv_march<1, 1, false, false, true>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_conv_march<1, 1, MASK>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     if (ck == 2 && nt % 2 == 0) {
@@ -1311,9 +1358,24 @@ hipError_t launch_deep(const ConvArgs& a, int pg, int nt, dim3 grid, hipStream_t
     return hipGetLastError();
 }
 
+// The last convolution of a forward pass alone ends in the output.
+struct HeadOut {
+    double* u;
+    int64_t ld, gstride;
+};
+
 hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool forward, Out y,
-                int batch, hipStream_t s) {
+                int batch, hipStream_t s, const HeadOut* head = nullptr) {
     ConvArgs a;
+    a.u = nullptr;
+    if (head) {
+        if (!forward || L.cout != 16 || L.cin != 16) return hipErrorInvalidValue;
+        a.head = net.param + (net.nparam - 17);
+        a.rms = net.rms;
+        a.u = head->u;
+        a.ld = head->ld;
+        a.gstride = head->gstride;
+    }
     a.x = x.a;
     a.xs = a.xsplit = x.ca;
     a.x2 = x.b;
@@ -1354,12 +1416,15 @@ hipError_t conv(const Net& net, const Layer& L, In x, const bf16* mask, bool for
     const int64_t strip_rows = int64_t(batch) * a.h * ((a.wd + 31) / 32) * (a.cout / 16);
     if (a.cin % 32 != 0 || (a.cin == 32 && strip_rows >= 4096)) {
         // Rows of a wave: two rows more are read than written, so as many as
-        // still leave four waves a SIMD on 256 CUs.
+        // still fill 256 CUs once, four waves a SIMD of the 16 -> 16 form and two
+        // of the others (their registers); three rows a step of the kernel, so
+        // rows + 2 a multiple of 3.
         const int64_t strips = int64_t(batch) * ((a.wd + 16 * kConvGroups - 1) / (16 * kConvGroups)) *
                                (a.cin == 32 && a.cout % 32 == 0 ? a.cout / 32 : 1);
-        // (Three rows a step of the kernel: rows + 2 a multiple of 3.)
-        a.rows = int(std::max<int64_t>(strips * a.h / 4096, 4));
-        a.rows -= (a.rows + 2) % 3;
+        const int64_t fit = a.cin == 16 && a.cout == 16 ? 4096 : 2048;
+        const int64_t bands = std::max<int64_t>(fit / strips, 1);
+        a.rows = int(std::max<int64_t>((a.h + bands - 1) / bands, 4));
+        a.rows += (4 - a.rows % 3) % 3;
         const int64_t waves = strips * ((a.h + a.rows - 1) / a.rows);
         if (waves > (int64_t(1) << 31) - 4) return hipErrorInvalidValue;
         const dim3 grid(blocks_for(waves, 4));
@@ -1508,9 +1573,11 @@ const Layer& layer(const Net& net, const char* name) {
 }
 
 // Forward pass of `batch` samples; f: batch grids back to back (natural
-// layout, gstride elements apart).  Leaves y (FP32, normalised) and rms.
-hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gstride,
+// layout, gstride elements apart).  Leaves rms and, where the result is not
+// wanted in u (as f lies), y (FP32, normalised) and the last activations.
+hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gstride, double* u,
                    hipStream_t s) {
+    const HeadOut out = {u, ld, gstride};
     const int n0 = net.n[0];
     // the row sums sit in the gradient partials, which are free during a forward pass
     double* rows = reinterpret_cast<double*>(net.parts);
@@ -1545,8 +1612,9 @@ hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gst
         NN_TRY(conv(net, layer(net, n0name), In{net.up[l], kC[l + 1], net.enc[l], kC[l]}, nullptr,
                     true, Out{net.adec[l], kC[l]}, batch, s));
         NN_TRY(conv(net, layer(net, n1name), In{net.adec[l], kC[l]}, nullptr, true,
-                    Out{net.d[l], kC[l]}, batch, s));
+                    Out{net.d[l], kC[l]}, batch, s, l == 0 && u ? &out : nullptr));
     }
+    if (u) return hipSuccess;
     const size_t hw = net.nparam - 17;
     hipLaunchKernelGGL(k_head, dim3(blocks_for(int64_t(batch) * n0 * n0)), dim3(256), 0, s, net.d[0],
                        kC[0], net.param + hw, net.param + hw + 16, net.y, int64_t(batch) * n0 * n0);
@@ -1773,12 +1841,7 @@ int rbgs_unet_forward(rbgs_unet* u, int32_t batch, const double* f, int64_t ld, 
     if (ld < int64_t(net.n[0]) + 2) return nn::nnfail(RBGS_EINVAL, "ld must be >= n + 2");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t gs = int64_t(net.n[0] + 2) * ld;
-    int rc = nn::nn_hip(nn::forward(net, batch, f, ld, gs, s), "forward");
-    if (rc) return rc;
-    const int n0 = net.n[0];
-    hipLaunchKernelGGL(nn::k_output, dim3(nn::blocks_for(n0), unsigned(n0), unsigned(batch)), dim3(256),
-                       0, s, net.y, net.rms, u0, n0, ld, gs);
-    return nn::nn_hip(hipGetLastError(), "output");
+    return nn::nn_hip(nn::forward(net, batch, f, ld, gs, u0, s), "forward");
 }
 
 int rbgs_unet_train_step(rbgs_unet* u, int32_t batch, const double* f, const double* target,
@@ -1791,7 +1854,7 @@ int rbgs_unet_train_step(rbgs_unet* u, int32_t batch, const double* f, const dou
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t gs = int64_t(net.n[0] + 2) * ld;
     const int n0 = net.n[0];
-    int rc = nn::nn_hip(nn::forward(net, batch, f, ld, gs, s), "forward");
+    int rc = nn::nn_hip(nn::forward(net, batch, f, ld, gs, nullptr, s), "forward");
     if (rc) return rc;
     const unsigned mblocks = nn::blocks_for(int64_t(batch) * n0 * n0);
     hipLaunchKernelGGL(nn::k_mse, dim3(mblocks), dim3(256), 0, s, net.y, target, net.rms, n0, ld,
