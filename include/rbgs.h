@@ -70,10 +70,11 @@ typedef enum {
 
 typedef enum {
     RBGS_KERNEL_AUTO = 0,    /* library choice, from measured time per sweep:
-                                launches of up to 4 - 6 sweeps over independent
-                                overlapping windows held in registers, up to
-                                n = 2300 (FP64) / 10000 (FP32) and for calls of
-                                few sweeps beyond; else BLOCKED.  With tuning or
+                                launches of up to 4 - 7 sweeps over independent
+                                overlapping windows or row-walking tiles held
+                                in registers, up to n = 8000 (FP64) / 10000
+                                (FP32) and for calls of few sweeps beyond;
+                                else BLOCKED.  With tuning or
                                 debug options set: PLAIN below 8 sweeps,
                                 RESIDENT up to n = 384 (FP64) / 768 (FP32),
                                 PLAIN for FP32 n < 1536, BLOCKED otherwise     */

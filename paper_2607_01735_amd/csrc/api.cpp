@@ -271,7 +271,7 @@ int choose_kernel(int n, size_t elem_bytes, int nsweeps, const rbgs_sweep_opts* 
 
 // Launches of nsweeps sweeps by the windows.
 int window_passes(int n, size_t elem_bytes, int nsweeps) {
-    const int k = window_fuse(n, elem_bytes);
+    const int k = window_fuse(n, elem_bytes, nsweeps);
     return nsweeps / k + (nsweeps % k ? 1 : 0);
 }
 
@@ -312,6 +312,7 @@ int run_sweeps(const rbgs_grid* g, const Workspace& w, int32_t nsweeps, const rb
             a.h2 = h2;
             a.omega = T(omega);
             a.n = n;
+            a.deep = pipeline_takes(n, sizeof(T), nsweeps);
             for (int p = 0; p < passes; ++p) {
                 const int k = nsweeps / passes + (p < nsweeps % passes ? 1 : 0);
                 const bool second = ((p + start) & 1) != 0;

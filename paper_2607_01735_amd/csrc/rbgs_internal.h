@@ -88,9 +88,15 @@ struct WindowArgs {
     T omega;  // != 1: red-black SOR (FP64), red read and written by every pass
     int n, last;
     int bands;  // filled by launch_window
+    bool deep;  // by the row pipeline (pipeline_takes)
 };
 bool window_takes(int n, size_t elem_bytes, int nsweeps);  // whether it is the choice
-int window_fuse(int n, size_t elem_bytes);  // most sweeps a launch
+int window_fuse(int n, size_t elem_bytes, int nsweeps);  // most sweeps a launch
+// Whether the call's passes run down the rows of tall tiles (sweep_pipeline.hip)
+// and not in windows.
+bool pipeline_takes(int n, size_t elem_bytes, int nsweeps);
+int pipeline_fuse(int n);  // most sweeps a launch
+hipError_t launch_pipeline(const WindowArgs<double>& a, int sweeps, hipStream_t s);
 template <typename T>
 hipError_t launch_window(const WindowArgs<T>& a, int sweeps, hipStream_t s);
 

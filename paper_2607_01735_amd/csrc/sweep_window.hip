@@ -77,26 +77,30 @@ Shape shape(int n, size_t elem_bytes) {
 }  // namespace
 
 // Where the windows are the choice (against the plain, resident and blocked
-// kernels, MI355X): always up to 2300 (FP64) / 10000 (FP32), the figures above;
-// beyond, calls of few sweeps, where the persistent kernel's ramp or two
-// launches a sweep cost more (FP64 4095^2: 7 sweeps 341 us against 683, 24
-// sweeps 704 against 757; 8191^2: 8 sweeps 1341 against 1436, 10 sweeps 1549
-// against 1475; FP32 12287^2: 24 sweeps 2463 against 2788); not for one sweep
-// of a large grid, which the half-sweeps do in fewer bytes (FP64 4095^2 243
-// against 223; FP32 12287^2 1248 against 1127).
+// kernels, MI355X): always up to 2300 (FP64; from 1600 and nine sweeps the row
+// pipeline is the faster one) / 10000 (FP32), the figures above; beyond, calls of
+// few sweeps, where the persistent kernel's ramp or two launches a sweep cost
+// more (FP64 4095^2: 7 sweeps 341 us against 683; 8191^2: 8 sweeps 1341 against
+// 1436; FP32 12287^2: 24 sweeps 2463 against 2788); not for one sweep of a
+// large grid, which the half-sweeps do in fewer bytes (FP64 4095^2 243 against
+// 223; FP32 12287^2 1248 against 1127).
 bool window_takes(int n, size_t elem_bytes, int nsweeps) {
+    if (pipeline_takes(n, elem_bytes, nsweeps)) return true;
     const bool f64 = elem_bytes == 8;
     if (nsweeps == 1) return n <= (f64 ? 3000 : 4500);
     if (n <= (f64 ? 2300 : 10000)) return true;
-    return nsweeps <= (f64 && n > 4500 ? 8 : 24);
+    return nsweeps <= (f64 ? 8 : 24);
 }
 
-int window_fuse(int n, size_t elem_bytes) { return shape(n, elem_bytes).k; }
+int window_fuse(int n, size_t elem_bytes, int nsweeps) {
+    return pipeline_takes(n, elem_bytes, nsweeps) ? pipeline_fuse(n) : shape(n, elem_bytes).k;
+}
 
 // A call's passes run at depth k or k - 1 where it has enough sweeps; depths
 // below that (calls of a few sweeps) all take eight rows.
 template <>
 hipError_t launch_window<double>(const WindowArgs<double>& a, int sweeps, hipStream_t s) {
+    if (a.deep) return launch_pipeline(a, sweeps, s);
     const int r = shape(a.n, 8).r;
     switch (sweeps) {
         case 1: return launch<double, 1, 8>(a, s);
