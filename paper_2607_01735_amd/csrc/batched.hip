@@ -408,6 +408,12 @@ BatchSetup build_setup(int count, const rbgs_grid* grids, void* const* u, const 
     return s;
 }
 
+// The buffer a batch's sweeps leave their result in, from buffer 0.
+int result_buffer(const BatchSetup& s) {
+    if (s.win.passes > 0) return s.win.passes & 1;
+    return (s.passes + (s.rem > 0 ? 1 : 0)) & 1;
+}
+
 template <typename T, int V, int L, bool SOR>
 hipError_t launch_batched_k(const GridDesc<T>* d, const int* map, int total_tiles, const Queue& qu,
                             hipStream_t s) {
@@ -716,7 +722,7 @@ int sweep_batched_t(int32_t count, const rbgs_grid* grids, void* const* u, const
 // ---------------------------------------------------------------------------
 // Batched solve: FP64 iterative refinement (the single-grid rbgs_solve's
 // steps, grid by grid) whose FP32 inner sweeps run as one batched
-// persistent launch over every grid that has not yet converged.
+// sweep over every grid that has not yet converged.
 // ---------------------------------------------------------------------------
 
 // Workspace of a batched solve: the FP32 batch (per grid: the correction e
@@ -864,14 +870,15 @@ int solve_batched_ir(int32_t count, const rbgs_grid* grids, double* const* u,
             }
             int fuse = 0, rows = 0, lds = 0;
             choose_params(na, sg.data(), RBGS_F32, &o->sweep, &fuse, &rows, &lds);
-            const BatchSetup su =
+            BatchSetup su =
                 build_setup<float>(na, sg.data(), nu.data(), nf.data(), sub, ws, fuse, rows, k, lds);
+            choose_windows(su, na, sg.data(), 4, k, &o->sweep);
             if ((rc = upload_setup<float>(su, sub, ws, na, s))) return rc;
             e = enqueue_batch<float>(su, sub, ws, na, &o->sweep, false, false, s);
             if (e != hipSuccess)
                 return bfail(RBGS_EHIP, std::string("inner sweeps: ") + hipGetErrorString(e));
             if ((rc = read_error_word(sub, ws, s))) return rc;
-            const int out = (su.passes + (su.rem > 0 ? 1 : 0)) & 1;
+            const int out = result_buffer(su);
             for (int g : act) {
                 e = launch_add_correction(ga[g].u_red, ga[g].u_black, ga[g].p64, ga[g].e[out][0],
                                           ga[g].e[out][1], ga[g].p32, grids[g].n, s);
@@ -906,7 +913,7 @@ int solve_batched_ir(int32_t count, const rbgs_grid* grids, double* const* u,
 // ---------------------------------------------------------------------------
 // Batched FP64 solve: the single-grid FP64 solve loop (residual, then
 // check_every sweeps, until rel <= rel_tol or max_sweeps), with the sweeps
-// of every grid still iterating in one batched persistent launch; with
+// of every grid still iterating in one batched sweep; with
 // omega != 1 the sweeps are red-black SOR, each grid with its own omega.
 // ---------------------------------------------------------------------------
 
@@ -1024,6 +1031,7 @@ int solve_batched_f64(int32_t count, const rbgs_grid* grids, double* const* u,
             if (sor) lds = -1;  // the LDS-resident sweep is Gauss-Seidel only
             BatchSetup su =
                 build_setup<double>(na, sg.data(), nu.data(), nf.data(), sub, ws, fuse, rows, k, lds);
+            if (!sor) choose_windows(su, na, sg.data(), 8, k, &o->sweep);
             // a grid whose iterate sits in buffer 1 runs with its buffers
             // swapped, so that every launch starts from "buffer 0"
             GridDesc<double>* gd = reinterpret_cast<GridDesc<double>*>(su.gdesc.data());
@@ -1038,7 +1046,7 @@ int solve_batched_f64(int32_t count, const rbgs_grid* grids, double* const* u,
             e = enqueue_batch<double>(su, sub, ws, na, &o->sweep, false, false, s, sor);
             if (e != hipSuccess) return bfail(RBGS_EHIP, std::string("sweeps: ") + hipGetErrorString(e));
             if ((rc = read_error_word(sub, ws, s))) return rc;
-            const int out = (su.passes + (su.rem > 0 ? 1 : 0)) & 1;
+            const int out = result_buffer(su);
             for (int g : act) {
                 cur[g] ^= out;
                 done[g] += k;

@@ -55,3 +55,20 @@ def test_plan_replays(nsweeps):
         for g, n in enumerate(SMALL):
             assert torch.equal(a[g], b[g]), f"replay {r}, grid {g} (n={n})"
     plan.close()
+
+
+@pytest.mark.parametrize("precision,omega", [("f64", 1.0), ("f32_ir", 1.0), ("f64", 1.5)])
+def test_batched_solves_equal_the_persistent_kernel(precision, omega):
+    """Rounds of 25 sweeps (an odd number of passes), grids that leave early,
+    and a last round cut short by the sweep budget."""
+    print(f"batched solve {precision} omega={omega}", flush=True)
+    sizes = [3, 15, 63, 64, 31, 7]
+    us, fs = batch(sizes, np.float64)
+    a, b = [u.clone() for u in us], [u.clone() for u in us]
+    kw = dict(precision=precision, omega=omega)
+    ia = rb.rbgs_solve_batched(a, fs, 310, 1e-6, 25, **kw)
+    ib = rb.rbgs_solve_batched(b, fs, 310, 1e-6, 25, kernel="blocked", **kw)
+    for g, n in enumerate(sizes):
+        assert torch.equal(a[g], b[g]), f"grid {g} (n={n})"
+        assert ia[g]["sweeps"] == ib[g]["sweeps"]
+        assert ia[g]["rel_residual"] == ib[g]["rel_residual"]
