@@ -677,11 +677,14 @@ __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ 
     if (threadIdx.x == 0) out[e] = sh[0];
 }
 
-// The same sums for many elements and all layers at once, coalesced: a block
-// takes 64 consecutive elements of a layer, its 16 waves the slots w, w + 16,
-// ... (64 consecutive floats of a slot at a time, four partial sums), whose
-// sums are added in the waves' order.  A fixed order again.  (A launch a layer
-// took 4.5 to 7 us, 14 times, 76 in all at 511^2 x 8; now 49.)
+// The same sums for many elements and all layers at once, coalesced: `ways`
+// waves share 64 consecutive elements of a layer, taking the slots w, w +
+// ways, ... (64 consecutive floats of a slot at a time, four partial sums),
+// whose sums are added in the waves' order.  A block of 16 waves takes 64
+// elements of a layer with many slots (16 ways), 256 of one with up to 64,
+// which would leave most waves a single load.  A fixed order again.  (A launch a layer
+// took 4.5 to 7 us, 14 times, 76 in all at 511^2 x 8; 16 ways throughout 46; now
+// 29.)
 constexpr int kReduceWaves = 16;
 constexpr int kMaxLayers = 16;
 
@@ -692,6 +695,7 @@ struct ReduceArgs {
         float* out;
         int64_t slots, count;
         int first;  // block
+        int ways;   // 16 or 4
     } l[kMaxLayers];
 };
 
@@ -701,26 +705,28 @@ __global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_slots(ReduceArgs a
     const auto& L = a.l[layer];
     const float* __restrict__ part = L.part;
     const int64_t nparts = L.slots, count = L.count;
-    const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int64_t e = int64_t(int(blockIdx.x) - L.first) * 64 + l;
+    const int ways = L.ways;
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, g = w & (ways - 1);
+    const int64_t e = int64_t(int(blockIdx.x) - L.first) * (64 * (kReduceWaves / ways)) +
+                      (w / ways) * 64 + l;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     if (e < count)
-        for (int64_t k = g; k < nparts; k += 4 * kReduceWaves) {
+        for (int64_t k = g; k < nparts; k += 4 * ways) {
             float v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int64_t ki = k + int64_t(i) * kReduceWaves;
+                const int64_t ki = k + int64_t(i) * ways;
                 v[i] = ki < nparts ? part[ki * count + e] : 0.f;
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[i] += v[i];
         }
     __shared__ float sh[kReduceWaves][64];
-    sh[g][l] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    sh[w][l] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     __syncthreads();
     if (g == 0 && e < count) {
-        float s = sh[0][l];
-        for (int w = 1; w < kReduceWaves; ++w) s += sh[w][l];
+        float s = sh[w][l];
+        for (int k = 1; k < ways; ++k) s += sh[w + k][l];
         L.out[e] = s;
     }
 }
@@ -743,53 +749,10 @@ struct bf16x8 {
         const uint32_t w = (&v.x)[k >> 1];
         return __uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
     }
-    __device__ void set(int k, bf16 h) {
-        uint32_t& w = (&v.x)[k >> 1];
-        w = (k & 1) ? ((w & 0x0000ffffu) | (uint32_t(h) << 16)) : ((w & 0xffff0000u) | h);
-    }
 };
 
 __device__ __forceinline__ bf16x8 load8(const bf16* p) {
     return bf16x8{*reinterpret_cast<const uint4*>(p)};
-}
-
-// k_bias_grad with 16-byte loads (c a multiple of 8, 16-byte aligned rows):
-// thread t takes channels 8 (t % c8) .. 8 (t % c8) + 7 of pixels t / c8,
-// t / c8 + g, ... (c8 = c / 8, g = 256 / c8), then a fixed tree over the g
-// pixel groups; one partial per (row, channel) as there.
-__global__ __launch_bounds__(256) void k_bias_grad8(const bf16* dy, int64_t dys, const bf16* y,
-                                                    int64_t ys, float* part, int wd, int c) {
-    const int64_t row = blockIdx.x;
-    const int t = threadIdx.x;
-    const int c8 = c / 8;
-    const int g = 256 / c8;
-    const int grp = t / c8, ch = (t % c8) * 8;
-    float s[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] = 0.f;
-    for (int x = grp; x < wd; x += g) {
-        const int64_t p = row * wd + x;
-        const bf16x8 yv = load8(y + p * ys + ch);
-        const bf16x8 dv = load8(dy + p * dys + ch);
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (yv.get(k) > 0.f) s[k] += dv.get(k);
-    }
-    __shared__ float sh[8][256];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sh[k][t] = s[k];
-    __syncthreads();
-    for (int st = g / 2; st > 0; st >>= 1) {
-        if (grp < st) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sh[k][t] += sh[k][t + st * c8];
-        }
-        __syncthreads();
-    }
-    if (grp == 0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) part[row * c + ch + k] = sh[k][t];
-    }
 }
 
 // F (the coarsening factor, 2 or 4) is a template parameter so that the
@@ -1490,9 +1453,11 @@ hipError_t wgrad(const Net& net, Partials& parts, const Layer& L, In x, const bf
     else if (p.ti == 3 && p.to == 1) hipLaunchKernelGGL((k_conv3x3_wgrad<3, 1>), grid, block, 0, s, a);
     else if (p.ti == 2 && p.to == 2) hipLaunchKernelGGL((k_conv3x3_wgrad<2, 2>), grid, block, 0, s, a);
     else return hipErrorInvalidValue;
-    parts.args.l[parts.args.layers++] = {a.part, net.grad + L.w_off, slots, count, parts.blocks};
+    const int ways = slots > 64 ? kReduceWaves : 4;
+    parts.args.l[parts.args.layers++] = {a.part, net.grad + L.w_off, slots, count, parts.blocks, ways};
     parts.used += size_t(slots * count);
-    parts.blocks += int((count + 63) / 64);
+    const int64_t per_block = 64 * (kReduceWaves / ways);
+    parts.blocks += int((count + per_block - 1) / per_block);
     return hipGetLastError();
 }
 
@@ -1625,9 +1590,6 @@ hipError_t forward(Net& net, int batch, const double* f, int64_t ld, int64_t gst
 hipError_t backward(Net& net, int batch, hipStream_t s) {
     const int n0 = net.n[0];
     const size_t hw = net.nparam - 17;
-    hipLaunchKernelGGL(k_fill, dim3(blocks_for(int64_t(net.nparam))), dim3(256), 0, s,
-                       reinterpret_cast<uint32_t*>(net.grad), int64_t(net.nparam));
-    NN_TRY(hipGetLastError());
     const unsigned hblocks = blocks_for(int64_t(batch) * n0 * n0, 256 * kHeadPixels);
     hipLaunchKernelGGL(k_head_grad, dim3(hblocks), dim3(256), 0, s, net.d[0], kC[0],
                        net.param + hw, net.dy, net.gd[0], kC[0], net.parts,
