@@ -378,7 +378,9 @@ int rbgs_batch_plan_destroy(rbgs_batch_plan *plan);
  * multiset of grid sizes) in a process-wide table, appends it to the file
  * named by the environment variable RBGS_TUNE_CACHE if set (and reads that
  * file on first use), and returns it in *best (HOST, may be NULL) with its
- * time per sweep in *best_ms_per_sweep (HOST, may be NULL).  Synchronises. */
+ * time per sweep in *best_ms_per_sweep (HOST, may be NULL).  The stored
+ * choice serves calls that run the persistent kernel (kernel BLOCKED, or a
+ * grid too large for the windows).  Synchronises. */
 int rbgs_autotune_batched(int32_t count, const rbgs_grid *grids,
                           rbgs_dtype dt, void *const *u, const void *const *f,
                           void *workspace, size_t workspace_bytes,
