@@ -508,9 +508,9 @@ hipError_t enqueue_batch(const BatchSetup& su, const BatchLayout& lay, char* ws,
         // the LDS-resident grids: all their sweeps in one launch, written to
         // the buffer the unpack reads
         const int nsweeps = su.passes * su.fuse + su.rem;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_lds<T>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  int(su.small_lds_bytes));
+        static std::atomic<uint64_t> allowed{0};  // of this T's kernel
+        (void)allow_dynamic_lds(reinterpret_cast<const void*>(&k_batch_lds<T>), lds_limit_bytes(),
+                                allowed);
         hipLaunchKernelGGL((k_batch_lds<T>), dim3(unsigned(su.small_ids.size())), dim3(kLdsThreads),
                            su.small_lds_bytes, s, gd, reinterpret_cast<const int*>(ws + lay.small),
                            nsweeps, final_parity);

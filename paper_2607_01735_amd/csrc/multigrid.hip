@@ -29,6 +29,15 @@ constexpr int kMgThreads = 256;
 // One colour of a level with its ring in LDS, (n + 2) rows of (n + 3) / 2.
 __host__ __device__ constexpr int mg_coarse_cells(int n) { return (n + 2) * ((n + 3) / 2); }
 
+// LDS of the largest coarse end: four colour arrays of every level from
+// kMgCoarseN down to a single point and the top level's residual.
+constexpr size_t mg_coarse_lds() {
+    size_t cells = size_t(kMgCoarseN + 2) * size_t(kMgCoarseN + 2);
+    for (int n = kMgCoarseN; n >= 1; n = (n - 1) / 2) cells += 4 * size_t(mg_coarse_cells(n));
+    return cells * sizeof(double);
+}
+constexpr size_t kMgCoarseLds = mg_coarse_lds();
+
 constexpr int kRestrictRows = 4;  // coarse rows one thread marches down
 
 // Element k of a split row, 0 outside [0, pitch): only ever used for points
@@ -451,12 +460,13 @@ hipError_t launch_mg_coarse_vcycle(const MgCoarseLevels& levels, int nu1, int nu
                                    int coarse_sweeps, const int* stop, hipStream_t s) {
     if (levels.count < 1 || levels.count > kMgMaxCoarseLevels || levels.level[0].n > kMgCoarseN)
         return hipErrorInvalidValue;
+    static std::atomic<uint64_t> allowed{0};
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&k_mg_coarse_vcycle),
+                                     kMgCoarseLds, allowed);
+    if (e != hipSuccess) return e;
     size_t cells = size_t(levels.level[0].n + 2) * size_t(levels.level[0].n + 2);  // the residual
     for (int l = 0; l < levels.count; ++l) cells += 4 * size_t(mg_coarse_cells(levels.level[l].n));
     const size_t lds = cells * sizeof(double);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mg_coarse_vcycle),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mg_coarse_vcycle, dim3(1), dim3(kCoarseThreads), lds, s, levels, nu1, nu2,
                        coarse_sweeps, stop);
     return hipGetLastError();
