@@ -228,23 +228,39 @@ hipError_t launch_copy_ring(void* dst_red, void* dst_black, const void* src_red,
 }
 
 namespace {
-__global__ __launch_bounds__(256) void k_copy_unless(uint4* __restrict__ dst,
-                                                     const uint4* __restrict__ src, size_t n,
+// 16 bytes a thread; the last of a row may hold fewer words of the grid.
+template <typename W>
+__global__ __launch_bounds__(256) void k_copy_unless(W* __restrict__ dst, const W* __restrict__ src,
+                                                     int64_t rows, int64_t pitch, int width,
                                                      const int* __restrict__ stop) {
     if (stop != nullptr && *stop != 0) return;
-    for (size_t k = size_t(blockIdx.x) * 256 + threadIdx.x; k < n; k += size_t(gridDim.x) * 256)
-        dst[k] = src[k];
+    constexpr int kWords = 16 / int(sizeof(W));
+    const int q = (int(blockIdx.x) * 256 + int(threadIdx.x)) * kWords;
+    if (q >= width) return;
+    for (int64_t i = blockIdx.y; i < rows; i += gridDim.y) {
+        const int64_t at = i * pitch + q;
+        if (q + kWords <= width) {
+            *reinterpret_cast<uint4*>(dst + at) = *reinterpret_cast<const uint4*>(src + at);
+        } else {
+            for (int k = 0; q + k < width; ++k) dst[at + k] = src[at + k];
+        }
+    }
 }
 }  // namespace
 
-hipError_t launch_copy_unless(void* dst, const void* src, size_t bytes, const int* stop,
-                              hipStream_t s) {
-    const size_t n = bytes / 16;
-    if (n == 0) return hipSuccess;
-    size_t blocks = (n + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_copy_unless, dim3(unsigned(blocks)), dim3(256), 0, s,
-                       static_cast<uint4*>(dst), static_cast<const uint4*>(src), n, stop);
+hipError_t launch_copy_unless(void* dst, const void* src, int n, int64_t pitch, int elem_bytes,
+                              const int* stop, hipStream_t s) {
+    const int width = (n + 3) / 2;  // of the split rows, the points of the grid
+    const int rows = n + 2, words = 16 / elem_bytes;
+    const dim3 grid(unsigned((width + 256 * words - 1) / (256 * words)), unsigned(rows));
+    if (elem_bytes == 8)
+        hipLaunchKernelGGL(k_copy_unless<uint64_t>, grid, dim3(256), 0, s,
+                           static_cast<uint64_t*>(dst), static_cast<const uint64_t*>(src),
+                           int64_t(rows), pitch, width, stop);
+    else
+        hipLaunchKernelGGL(k_copy_unless<uint32_t>, grid, dim3(256), 0, s,
+                           static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src),
+                           int64_t(rows), pitch, width, stop);
     return hipGetLastError();
 }
 

@@ -390,9 +390,9 @@ hipError_t launch_copy_ring(void* dst_red, void* dst_black, const void* src_red,
 // Zero a device range with a kernel (usable inside graph capture).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 
-// dst <- src for `bytes` (a multiple of 16, 16-byte aligned buffers) unless
-// stop != nullptr and *stop != 0.
-hipError_t launch_copy_unless(void* dst, const void* src, size_t bytes, const int* stop,
-                              hipStream_t s);
+// One colour array's points, ring included, dst <- src unless stop != nullptr and
+// *stop != 0; entries past column n + 1 are left alone (dst may be the caller's).
+hipError_t launch_copy_unless(void* dst, const void* src, int n, int64_t pitch, int elem_bytes,
+                              const int* stop, hipStream_t s);
 
 }  // namespace rbgs

@@ -327,7 +327,6 @@ hipError_t run_blocked(T* const buf_red[2], T* const buf_black[2], const T* f_re
     *timed_fuse = 0;
     *launches = 0;
     const int k = bp.fuse;
-    const size_t colour_bytes = size_t(n + 2) * size_t(pitch) * sizeof(T);
     char* base = static_cast<char*>(state);
     // the error word starts at zero once per call (once per solve for the
     // rounds of a captured graph); tickets and flags before every launch (an
@@ -469,15 +468,15 @@ hipError_t run_blocked(T* const buf_red[2], T* const buf_black[2], const T* f_re
         if (n_lo > 0 && (e = run_passes(d_hi - 1, n_lo, false)) != hipSuccess) return e;
     }
     if (result_in_last && cur == 0) {  // an even count after all: move it to where the caller wants it
-        e = launch_copy_unless(buf_red[1], buf_red[0], colour_bytes, bp.stop, s);
+        e = launch_copy_unless(buf_red[1], buf_red[0], n, pitch, int(sizeof(T)), bp.stop, s);
         if (e != hipSuccess) return e;
-        e = launch_copy_unless(buf_black[1], buf_black[0], colour_bytes, bp.stop, s);
+        e = launch_copy_unless(buf_black[1], buf_black[0], n, pitch, int(sizeof(T)), bp.stop, s);
         if (e != hipSuccess) return e;
     }
     if (cur != 0 && !result_in_last) {  // a kernel, so that a converged graph-captured solve skips it too
-        e = launch_copy_unless(buf_red[0], buf_red[1], colour_bytes, bp.stop, s);
+        e = launch_copy_unless(buf_red[0], buf_red[1], n, pitch, int(sizeof(T)), bp.stop, s);
         if (e != hipSuccess) return e;
-        e = launch_copy_unless(buf_black[0], buf_black[1], colour_bytes, bp.stop, s);
+        e = launch_copy_unless(buf_black[0], buf_black[1], n, pitch, int(sizeof(T)), bp.stop, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
