@@ -72,12 +72,16 @@ typedef enum {
     RBGS_KERNEL_AUTO = 0,    /* library choice, from measured time per sweep:
                                 launches of up to 4 - 7 sweeps over independent
                                 overlapping windows or row-walking tiles held
-                                in registers, up to n = 8000 (FP64) / 10000
-                                (FP32) and for calls of few sweeps beyond;
-                                else BLOCKED.  With tuning or
-                                debug options set: PLAIN below 8 sweeps,
-                                RESIDENT up to n = 384 (FP64) / 768 (FP32),
-                                PLAIN for FP32 n < 1536, BLOCKED otherwise     */
+                                in registers, for n up to 8000 (FP64) / 9200
+                                (FP32), for 2 - 7 sweeps of any grid and for up
+                                to about 30 of n up to 15500 / 12500 (somewhat
+                                lower where the sweeps have to end in the buffer
+                                they start from: solve rounds, split sweeps);
+                                not for one sweep of n above 3000 / 4500.  Else,
+                                and with tuning or debug options set: PLAIN
+                                below 8 sweeps, RESIDENT up to n = 384 (FP64) /
+                                768 (FP32), PLAIN for FP32 n < 1536, BLOCKED
+                                otherwise                                      */
     RBGS_KERNEL_PLAIN = 1,   /* one kernel launch per half-sweep (Algorithm 1's
                                 barrier after every colour)                     */
     RBGS_KERNEL_BLOCKED = 2, /* persistent, temporally blocked kernel: several

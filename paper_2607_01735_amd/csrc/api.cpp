@@ -255,24 +255,20 @@ struct GroupTimer {
 
 // The library's own choice of kernel: beside the public ones the register
 // windows (sweep_window.hip), for small and middle-sized grids and calls of few
-// sweeps.  Tuning and debug options address the other kernels.
+// sweeps.  Tuning and debug options address the other kernels.  in_place, sor: as
+// for window_takes.
 constexpr int kKernelWindow = 100;
 
-int choose_kernel(int n, size_t elem_bytes, int nsweeps, const rbgs_sweep_opts* o) {
+int choose_kernel(int n, size_t elem_bytes, int nsweeps, const rbgs_sweep_opts* o, bool in_place,
+                  bool sor) {
     if (o && o->kernel != RBGS_KERNEL_AUTO) return o->kernel;
     const bool plainly = !o || (o->fuse == 0 && o->tile_rows == 0 && o->tile_cols == 0 &&
                                 o->rows_per_block == 0 && o->debug_delay == 0 &&
                                 o->debug_spin_limit == 0 && o->debug_stall_tile == 0 &&
                                 o->debug_tile_order == 0 && o->debug_stamp_check == 0 &&
                                 o->debug_trace == nullptr);
-    if (plainly && window_takes(n, elem_bytes, nsweeps)) return kKernelWindow;
+    if (plainly && window_takes(n, elem_bytes, nsweeps, in_place, sor)) return kKernelWindow;
     return auto_kernel(n, elem_bytes, nsweeps);
-}
-
-// Launches of nsweeps sweeps by the windows.
-int window_passes(int n, size_t elem_bytes, int nsweeps) {
-    const int k = window_fuse(n, elem_bytes, nsweeps);
-    return nsweeps / k + (nsweeps % k ? 1 : 0);
 }
 
 constexpr int kStartRing = 2;  // see run_sweeps
@@ -290,47 +286,44 @@ int run_sweeps(const rbgs_grid* g, const Workspace& w, int32_t nsweeps, const rb
     T* ub = static_cast<T*>(w.u_black);
     const T* fr = static_cast<const T*>(w.f_red);
     const T* fb = static_cast<const T*>(w.f_black);
-    const int kernel = choose_kernel(n, sizeof(T), nsweeps, o);
     *launches = 0;
-    // start: bit 0, u is in the second buffer; bit 1, both buffers hold the ring
+    // start: bit 0, u is in the second buffer, packed there for the windows or the
+    // blocked kernel; bit 1, both buffers hold the ring, packed for the windows
     const bool ring_ready = (start & kStartRing) != 0;
     start &= 1;
+    const int kernel = ring_ready ? kKernelWindow
+                       : start    ? RBGS_KERNEL_BLOCKED
+                                  : choose_kernel(n, sizeof(T), nsweeps, o, true, omega != 1.0);
     if (kernel == kKernelWindow) {
-        int passes = window_passes(n, sizeof(T), nsweeps);
-        if (start == 0 && (passes & 1) && nsweeps > passes) ++passes;
-        if ((passes & 1) == start) {
-            if (!ring_ready)
-                HIP_TRY(launch_copy_ring(start ? w.u_red : w.u2_red, start ? w.u_black : w.u2_black,
-                                         start ? w.u2_red : w.u_red, start ? w.u2_black : w.u_black,
-                                         n, w.pitch, int(sizeof(T)), s),
-                        "ring copy");
-            WindowArgs<T> a{};
-            a.f[0] = fr;
-            a.f[1] = fb;
-            a.stop = stop;
-            a.pitch = w.pitch;
-            a.h2 = h2;
-            a.omega = T(omega);
-            a.n = n;
-            a.deep = pipeline_takes(n, sizeof(T), nsweeps);
-            for (int p = 0; p < passes; ++p) {
-                const int k = nsweeps / passes + (p < nsweeps % passes ? 1 : 0);
-                const bool second = ((p + start) & 1) != 0;
-                T* const b[2][2] = {{ur, ub}, {static_cast<T*>(w.u2_red), static_cast<T*>(w.u2_black)}};
-                for (int c = 0; c < 2; ++c) {
-                    a.in[c] = b[second ? 1 : 0][c];
-                    a.out[c] = b[second ? 0 : 1][c];
-                }
-                a.last = p == passes - 1;
-                HIP_TRY(launch_window<T>(a, k, s), "window sweep");
-                ++*launches;
+        const int passes = window_passes(n, sizeof(T), nsweeps, !ring_ready);
+        if ((passes & 1) != start) return fail(RBGS_EINVAL, "internal: window passes end elsewhere");
+        if (!ring_ready)
+            HIP_TRY(launch_copy_ring(w.u2_red, w.u2_black, w.u_red, w.u_black, n, w.pitch,
+                                     int(sizeof(T)), s),
+                    "ring copy");
+        WindowArgs<T> a{};
+        a.f[0] = fr;
+        a.f[1] = fb;
+        a.stop = stop;
+        a.pitch = w.pitch;
+        a.h2 = h2;
+        a.omega = T(omega);
+        a.n = n;
+        a.deep = pipeline_takes(n, sizeof(T), nsweeps);
+        for (int p = 0; p < passes; ++p) {
+            const int k = nsweeps / passes + (p < nsweeps % passes ? 1 : 0);
+            const bool second = ((p + start) & 1) != 0;
+            T* const b[2][2] = {{ur, ub}, {static_cast<T*>(w.u2_red), static_cast<T*>(w.u2_black)}};
+            for (int c = 0; c < 2; ++c) {
+                a.in[c] = b[second ? 1 : 0][c];
+                a.out[c] = b[second ? 0 : 1][c];
             }
-            return RBGS_OK;
+            a.last = p == passes - 1;
+            HIP_TRY(launch_window<T>(a, k, s), "window sweep");
+            ++*launches;
         }
-        // a single sweep that has to end where it started: half-sweeps
+        return RBGS_OK;
     }
-    if (start != 0 && kernel != RBGS_KERNEL_BLOCKED)
-        return fail(RBGS_EINVAL, "internal: this kernel does not start in the second buffer");
     if (kernel == RBGS_KERNEL_BLOCKED) {
         BlockedParams bp = blocked_params(n, sizeof(T), o);
         bp.stop = stop;
@@ -404,9 +397,10 @@ int run_sweeps_dt(rbgs_dtype dt, const rbgs_grid* g, const Workspace& w, int32_t
 // u: the second buffer (1) when the persistent kernel will run an odd number
 // of passes, whose result then lands in the first buffer with no copy back;
 // else the first (0).
-int pack_buffer(const rbgs_grid* g, rbgs_dtype dt, int32_t nsweeps, const rbgs_sweep_opts* o) {
-    const int kernel = choose_kernel(g->n, elem_size(dt), nsweeps, o);
-    if (kernel == kKernelWindow) return window_passes(g->n, elem_size(dt), nsweeps) & 1;
+int pack_buffer(const rbgs_grid* g, rbgs_dtype dt, int32_t nsweeps, const rbgs_sweep_opts* o,
+                bool sor) {
+    const int kernel = choose_kernel(g->n, elem_size(dt), nsweeps, o, false, sor);
+    if (kernel == kKernelWindow) return window_passes(g->n, elem_size(dt), nsweeps, false) & 1;
     if (kernel != RBGS_KERNEL_BLOCKED) return 0;
     return blocked_pass_parity(g->n, elem_size(dt), nsweeps, o);
 }
@@ -1235,8 +1229,9 @@ int rbgs_sweep(const rbgs_grid* g, rbgs_dtype dt, void* u, const void* f, int32_
     HIP_TRY(tm.init(opts && opts->timing), "event create");
     PersistentTimer pt;
     HIP_TRY(pt.init(opts && opts->timing), "event create");
-    int start = pack_buffer(g, dt, nsweeps, opts);
-    const bool windows = choose_kernel(g->n, size_t(es), nsweeps, opts) == kKernelWindow;
+    int start = pack_buffer(g, dt, nsweeps, opts, false);
+    const bool windows =
+        choose_kernel(g->n, size_t(es), nsweeps, opts, false, false) == kKernelWindow;
     HIP_TRY(tm.mark(0, s), "event record");
     HIP_TRY(pack_grid(g, w, u, f, windows, &start, es, s), "pack");
     HIP_TRY(tm.mark(1, s), "event record");
@@ -1371,9 +1366,10 @@ int rbgs_solve(const rbgs_grid* g, rbgs_dtype dt, void* u, const void* f,
     // the final one), so a timed solve keeps the GPU as busy as an untimed one.
     // a fixed sweep count (no refinement) packs u where its sweeps end
     const bool fixed = !ir && o->rel_tol <= 0.0;
-    int start = fixed ? pack_buffer(g, dt, o->max_sweeps, &o->sweep) : 0;
-    const bool windows =
-        fixed && choose_kernel(g->n, size_t(es), o->max_sweeps, &o->sweep) == kKernelWindow;
+    const bool sor = omega != 1.0;
+    int start = fixed ? pack_buffer(g, dt, o->max_sweeps, &o->sweep, sor) : 0;
+    const bool windows = fixed && choose_kernel(g->n, size_t(es), o->max_sweeps, &o->sweep, false,
+                                                sor) == kKernelWindow;
     HIP_TRY(gt.t.mark(0, s), "event record");
     HIP_TRY(pack_grid(g, w, u, f, windows, &start, es, s), "pack");
     HIP_TRY(gt.t.mark(3, s), "event record");

@@ -106,7 +106,10 @@ struct WindowArgs {
     int bands;  // filled by launch_window
     bool deep;  // by the row pipeline (pipeline_takes)
 };
-bool window_takes(int n, size_t elem_bytes, int nsweeps);  // whether it is the choice
+// Whether they are the choice; in_place: the result has to end in the buffer the
+// iterate starts in, sor: omega != 1.  What is taken in place is taken otherwise.
+bool window_takes(int n, size_t elem_bytes, int nsweeps, bool in_place, bool sor);
+int window_passes(int n, size_t elem_bytes, int nsweeps, bool in_place);  // launches
 int window_fuse(int n, size_t elem_bytes, int nsweeps);  // most sweeps a launch
 // Whether the call's passes run down the rows of tall tiles (sweep_pipeline.hip)
 // and not in windows.

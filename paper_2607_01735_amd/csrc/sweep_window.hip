@@ -76,20 +76,55 @@ Shape shape(int n, size_t elem_bytes) {
 
 }  // namespace
 
-// Where the windows are the choice (against the plain, resident and blocked
-// kernels, MI355X): always up to 2300 (FP64; from 1600 and nine sweeps the row
-// pipeline is the faster one) / 10000 (FP32), the figures above; beyond, calls of
-// few sweeps, where the persistent kernel's ramp or two launches a sweep cost
-// more (FP64 4095^2: 7 sweeps 341 us against 683; 8191^2: 8 sweeps 1341 against
-// 1436; FP32 12287^2: 24 sweeps 2463 against 2788); not for one sweep of a
-// large grid, which the half-sweeps do in fewer bytes (FP64 4095^2 243 against
-// 223; FP32 12287^2 1248 against 1127).
-bool window_takes(int n, size_t elem_bytes, int nsweeps) {
-    if (pipeline_takes(n, elem_bytes, nsweeps)) return true;
+// Whether the windows (or, pipeline_takes, the row pipeline) are the choice
+// against the plain, resident and blocked kernels.  in_place: the sweeps have to
+// end in the buffer they start from, which makes an odd number of passes one more,
+// and shallower.  MI355X, us, here against the others:
+//   one sweep of a large grid, which the half-sweeps do in fewer bytes, or in
+//     place: FP64 4095^2 243 / 223; FP32 12287^2 1248 / 1127
+//   two in place, as two passes: FP64 7001^2 0.93 of it, 8191^2 581 / 573, 12287^2
+//     1266 / 1231; FP32 5001^2 0.95, 7001^2 1.06, 12287^2 703 / 636; SOR, whose
+//     passes move red too, 1800^2 0.98, 4095^2 1.12
+//   up to seven: all sizes (FP64 24575^2 x 7 11019 / 22153, FP32 32767^2 0.76)
+//   FP64 up to 8000: always; beyond, up to 30 sweeps, until the ramp of the
+//     persistent kernel no longer counts: x 9 8191^2 1250 / 1443, 12287^2 2764 /
+//     2897, 15001^2 1.00, 16383^2 5144 / 4934, 24575^2 11446 / 10585; with a pass
+//     more: x 16 12287^2 2716 / 3270, x 20 14001^2 1.03, x 30 8191^2 1759 / 2045,
+//     12287^2 4006 / 3936, 14001^2 1.11
+//   FP32: always up to 9200 (x 100 8191^2 3622 / 4076); above, passes of four
+//     sweeps, which have short windows, cost too much (x 8 10001^2 1454 / 1360,
+//     12287^2 2176 / 1890), and above 10000 so do more passes than the persistent
+//     kernel takes (x 18 12287^2 2066 / 2405, x 20 2690 / 2504); 16383^2 x 12 3347
+//     / 3098, x 24 5114 / 4265.  With a pass more: x 14, down to four and three
+//     sweeps a pass, 4095^2 281 / 316, 5001^2 1.14, 12287^2 2363 / 1255; x 16
+//     6001^2 1.03, 7001^2 0.79, 8191^2 1201 / 966; x 26 5001^2 0.99, 6001^2 1.07;
+//     x 38 7001^2 0.79, 9001^2 1.16
+bool window_takes(int n, size_t elem_bytes, int nsweeps, bool in_place, bool sor) {
     const bool f64 = elem_bytes == 8;
-    if (nsweeps == 1) return n <= (f64 ? 3000 : 4500);
-    if (n <= (f64 ? 2300 : 10000)) return true;
-    return nsweeps <= (f64 ? 8 : 24);
+    if (nsweeps == 1) return !in_place && n <= (f64 ? 3000 : 4500);
+    if (nsweeps == 2 && in_place) return n <= (sor ? 1900 : f64 ? 7500 : 5500);
+    if (nsweeps < 8) return true;
+    const int passes = window_passes(n, elem_bytes, nsweeps, in_place);
+    const bool more = passes > window_passes(n, elem_bytes, nsweeps, false);
+    if (f64) {
+        const int most = !more ? 15500 : nsweeps <= 20 ? 13000 : 12000;
+        return n <= 8000 || (nsweeps <= 30 && n <= most);
+    }
+    const int depth = nsweeps / passes;  // of the shallower passes
+    if (more) {
+        if (depth < 4) return n <= 4300;
+        if (2 * int64_t(nsweeps) < 9 * int64_t(passes)) return n <= (passes <= 4 ? 7100 : 5500);
+        return n <= 8200;
+    }
+    if (n <= 9200) return true;
+    if (n <= 10000) return depth >= 5;
+    return n <= 12500 && nsweeps <= 24 && depth >= 5 && passes <= (nsweeps + 6) / 7;
+}
+
+int window_passes(int n, size_t elem_bytes, int nsweeps, bool in_place) {
+    const int k = window_fuse(n, elem_bytes, nsweeps);
+    const int passes = nsweeps / k + (nsweeps % k ? 1 : 0);
+    return in_place && (passes & 1) && nsweeps > passes ? passes + 1 : passes;
 }
 
 int window_fuse(int n, size_t elem_bytes, int nsweeps) {
