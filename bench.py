@@ -471,11 +471,11 @@ def rb3_throughput(torch, rb, n=767, sweeps=40, tol_sizes=(63, 127), tol=1e-8):
     """Red-black Gauss-Seidel in 3D (the higher-dimension extension): n^3
     FP64 with f ~ U[-1, 1) drawn on the device (seeded), time per sweep from
     the difference of a (sweeps + 1)-sweep and a 1-sweep call, GLUP/s and
-    model bytes (24 B per point per sweep, as in 2D), for the plain kernel
-    (one launch per half-sweep) and the flag-driven form (one launch, a
-    counter per block).  Then, per size in tol_sizes, the solve from u = 0 to
-    rel <= tol with each (residual every 500 sweeps; the plain solve's
-    rounds are graph-captured)."""
+    model bytes, for the automatic kernel (passes of two sweeps), the plain
+    one (one launch per half-sweep, 24 B per point per sweep as in 2D) and the
+    flag-driven form (one launch, a counter per block).  Then, per size in
+    tol_sizes, the solve from u = 0 to rel <= tol with each (residual every 500
+    sweeps; the rounds of the first two are graph-captured)."""
     h = 1.0 / (n + 1)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(0)
@@ -506,13 +506,14 @@ def rb3_throughput(torch, rb, n=767, sweeps=40, tol_sizes=(63, 127), tol=1e-8):
                 "model_GBs": round(glups * model_bytes, 1),
                 "frac_of_8TBs": round(glups * model_bytes / HBM_PEAK_GBS, 4)}
 
-    plain = per_sweep_of("plain")
-    flags = per_sweep_of("resident")
+    auto, plain, flags = (per_sweep_of(k) for k in ("auto", "plain", "resident"))
     out = {"workload": f"{n}^3 FP64, f~U[-1,1) (device generator, seed 0), {sweeps} sweeps"}
-    out.update(figures(plain, RB3_PASS_BYTES_PER_LUP))
+    out.update(figures(auto, RB3_PASS_BYTES_PER_LUP))
+    out["plain"] = dict(figures(plain, BYTES_PER_LUP["f64"]))
+    out["speedup_vs_plain"] = round(plain / auto, 3)
     out["flag_driven"] = dict(figures(flags, BYTES_PER_LUP["f64"]), speedup_vs_plain=round(plain / flags, 3))
-    log(f"3D red-black {n}^3: plain {plain * 1e3:.3f} ms/sweep ({n ** 3 / plain / 1e9:.1f} GLUP/s), "
-        f"flag-driven {flags * 1e3:.3f} ms/sweep ({n ** 3 / flags / 1e9:.1f} GLUP/s)")
+    log(f"3D red-black {n}^3: auto {auto * 1e3:.3f} ms/sweep ({n ** 3 / auto / 1e9:.1f} GLUP/s), "
+        f"plain {plain * 1e3:.3f} ms/sweep, flag-driven {flags * 1e3:.3f} ms/sweep")
     del u, f, ws
     torch.cuda.empty_cache()
     for m in tol_sizes:
@@ -523,7 +524,7 @@ def rb3_throughput(torch, rb, n=767, sweeps=40, tol_sizes=(63, 127), tol=1e-8):
                                           generator=gen) * 2.0 - 1.0
         row = {"problem": f"{m}^3 FP64, f~U[-1,1) (device generator, seed 1), u0=0, "
                           f"rel<={tol:g}, residual every 500 sweeps"}
-        for kernel in ("plain", "resident"):
+        for kernel in ("auto", "plain", "resident"):
             um = torch.zeros_like(fm)
             rb.rbgs_rb3_solve(um, fm, 1000, tol, check_every=500, h=hm, kernel=kernel)  # warm-up
             um.zero_()
@@ -531,9 +532,10 @@ def rb3_throughput(torch, rb, n=767, sweeps=40, tol_sizes=(63, 127), tol=1e-8):
             t0 = time.perf_counter()
             info = rb.rbgs_rb3_solve(um, fm, 2_000_000, tol, check_every=500, h=hm, kernel=kernel)
             torch.cuda.synchronize()
-            row["plain" if kernel == "plain" else "flag_driven"] = {
+            row["flag_driven" if kernel == "resident" else kernel] = {
                 "seconds": round(time.perf_counter() - t0, 4), "sweeps": info["sweeps"],
                 "rel_residual": info["rel_residual"], "status": info["status"]}
+        row["speedup_auto_vs_plain"] = round(row["plain"]["seconds"] / row["auto"]["seconds"], 3)
         row["speedup_flag_driven_vs_plain"] = round(row["plain"]["seconds"] /
                                                     row["flag_driven"]["seconds"], 3)
         out[f"time_to_{tol:g}_{m}"] = row

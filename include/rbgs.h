@@ -682,10 +682,11 @@ int rbgs_rb3_solve(const rbgs_grid *g, double *u, const double *f,
                    size_t workspace_bytes, void *stream);
 
 /* Kernel choice for the 3D calls (zero-initialise; NULL = all zero).
- * kernel: RBGS_KERNEL_AUTO or RBGS_KERNEL_PLAIN = passes of up to two sweeps,
- * one launch each (a device-wide barrier between passes); a launch per
- * half-sweep (Algorithm 1's structure) where there is no room for the passes'
- * second black array, and for a round of a single sweep; the same bits.
+ * kernel: RBGS_KERNEL_AUTO = passes of up to two sweeps, one launch each (a
+ * device-wide barrier between passes); as PLAIN where there is no room for the
+ * passes' second black array, and for a round of a single sweep.
+ * RBGS_KERNEL_PLAIN = one launch per half-sweep (Algorithm 1's structure).  The
+ * same bits.
  * RBGS_KERNEL_RESIDENT = the flag-driven form, the dependency rule of
  * Algorithm 2 (Section 2.3) carried to 3D: all half-sweeps of a call in one
  * cooperative launch of co-resident one-wave workgroups, the interior cut

@@ -973,7 +973,10 @@ Rb3Workspace plan_rb3(const rbgs_grid* g, char* base) {
     return w;
 }
 
-int rb3_prepare(const rbgs_grid* g, const void* u, const void* f, void* ws, size_t ws_bytes,
+// opts (optional): only AUTO takes the fused passes; without the second black array
+// every sweep is a launch per half-sweep, Algorithm 1's structure.
+int rb3_prepare(const rbgs_grid* g, const void* u, const void* f, const rbgs_rb3_opts* opts,
+                void* ws, size_t ws_bytes,
                 Rb3Workspace* w) {
     std::string why;
     if (!valid_grid3(g, &why)) return fail(RBGS_EINVAL, why);
@@ -986,7 +989,7 @@ int rb3_prepare(const rbgs_grid* g, const void* u, const void* f, void* ws, size
     if ((rc = check_device_range(u, grid3_bytes(g), "u"))) return rc;
     if ((rc = check_device_range(f, grid3_bytes(g), "f"))) return rc;
     *w = plan_rb3(g, static_cast<char*>(ws));
-    if (!second) w->u2_black = nullptr;
+    if (!second || (opts && opts->kernel != RBGS_KERNEL_AUTO)) w->u2_black = nullptr;
     return RBGS_OK;
 }
 
@@ -1894,13 +1897,13 @@ int rbgs_rb3_sweep_ex(const rbgs_grid* g, double* u, const double* f, int32_t ns
     int rc = rb3_check_opts(opts);
     if (rc) return rc;
     Rb3Workspace w;
-    if ((rc = rb3_prepare(g, u, f, workspace, workspace_bytes, &w))) return rc;
+    if ((rc = rb3_prepare(g, u, f, opts, workspace, workspace_bytes, &w))) return rc;
     if (nsweeps == 0) return RBGS_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool flags = rb3_flag_driven(opts);
     int capacity = 0;
     if (flags && (rc = rb3_flags_setup(g, opts, w, s, &capacity))) return rc;
-    const bool fused = !flags && w.u2_black;
+    const bool fused = w.u2_black != nullptr;
     const int passes = rb3_passes(nsweeps, false), start = fused ? passes & 1 : 0;
     if ((rc = rb3_pack_both(g, w, u, f, s, start))) return rc;
     if (flags)
@@ -1917,7 +1920,7 @@ int rbgs_rb3_sweep_ex(const rbgs_grid* g, double* u, const double* f, int32_t ns
 int rbgs_rb3_residual(const rbgs_grid* g, const double* u, const double* f, double* abs_norm,
                       double* rel_norm, void* workspace, size_t workspace_bytes, void* stream) {
     Rb3Workspace w;
-    int rc = rb3_prepare(g, u, f, workspace, workspace_bytes, &w);
+    int rc = rb3_prepare(g, u, f, nullptr, workspace, workspace_bytes, &w);
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = rb3_pack_both(g, w, u, f, s))) return rc;
@@ -1947,7 +1950,7 @@ int rbgs_rb3_solve_ex(const rbgs_grid* g, double* u, const double* f, int32_t ma
     if (flags && (max_sweeps > (1 << 29)))
         return fail(RBGS_EINVAL, "the flag-driven form runs at most 2^29 sweeps per call");
     Rb3Workspace w;
-    if ((rc = rb3_prepare(g, u, f, workspace, workspace_bytes, &w))) return rc;
+    if ((rc = rb3_prepare(g, u, f, opts, workspace, workspace_bytes, &w))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     int capacity = 0;
     if (flags && (rc = rb3_flags_setup(g, opts, w, s, &capacity))) return rc;

@@ -513,7 +513,7 @@ def rbgs_rb3_workspace_size(grid):
     return int(_lib.rbgs_rb3_workspace_size(ctypes.byref(grid)))
 
 
-def _rb3_opts(kernel="plain", debug_delay=0, debug_spin_limit=0, debug_stall_block=0):
+def _rb3_opts(kernel="auto", debug_delay=0, debug_spin_limit=0, debug_stall_block=0):
     o = rbgs_rb3_opts()
     o.kernel = _KERNELS[kernel] if isinstance(kernel, str) else int(kernel)
     o.debug_delay, o.debug_spin_limit = int(debug_delay), int(debug_spin_limit)
@@ -521,10 +521,11 @@ def _rb3_opts(kernel="plain", debug_delay=0, debug_spin_limit=0, debug_stall_blo
     return o
 
 
-def rbgs_rb3_sweep(u, f, nsweeps, h=None, workspace=None, stream=None, kernel="plain", **debug):
+def rbgs_rb3_sweep(u, f, nsweeps, h=None, workspace=None, stream=None, kernel="auto", **debug):
     """nsweeps 3D red-black sweeps (7-point Laplacian), in place (FP64).
-    kernel "plain": launches of up to two sweeps each; "resident": the
-    flag-driven form (one launch, per-block progress counters; synchronises)."""
+    kernel "auto": launches of up to two sweeps each; "plain": one launch per
+    half-sweep; "resident": the flag-driven form (one launch, per-block progress
+    counters; synchronises)."""
     grid, ws = _rb3_args(u, f, h, workspace)
     o = _rb3_opts(kernel, **debug)
     _check(_lib.rbgs_rb3_sweep_ex(ctypes.byref(grid), _vp(u.data_ptr()), _vp(f.data_ptr()),
@@ -543,7 +544,7 @@ def rbgs_rb3_residual(u, f, h=None, workspace=None, stream=None):
 
 
 def rbgs_rb3_solve(u, f, max_sweeps, rel_tol, check_every=100, h=None, workspace=None,
-                   stream=None, raise_on_noconv=False, kernel="plain", **debug):
+                   stream=None, raise_on_noconv=False, kernel="auto", **debug):
     """3D red-black sweeps until rel <= rel_tol; returns a dict with sweeps,
     rel_residual, abs_residual and status.  kernel as in rbgs_rb3_sweep."""
     grid, ws = _rb3_args(u, f, h, workspace)
