@@ -684,7 +684,8 @@ int rbgs_rb3_solve(const rbgs_grid *g, double *u, const double *f,
 /* Kernel choice for the 3D calls (zero-initialise; NULL = all zero).
  * kernel: RBGS_KERNEL_AUTO = passes of up to two sweeps, one launch each (a
  * device-wide barrier between passes); as PLAIN where there is no room for the
- * passes' second black array, and for a round of a single sweep.
+ * passes' second black array, for a round of a single sweep, for 2 <= n <= 7 and
+ * for one sweep of n >= 700.
  * RBGS_KERNEL_PLAIN = one launch per half-sweep (Algorithm 1's structure).  The
  * same bits.
  * RBGS_KERNEL_RESIDENT = the flag-driven form, the dependency rule of

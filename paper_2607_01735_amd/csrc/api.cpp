@@ -973,6 +973,17 @@ Rb3Workspace plan_rb3(const rbgs_grid* g, char* base) {
     return w;
 }
 
+// Whether nsweeps sweeps run in passes.  Not on tiny grids, where a pass's steps take
+// longer than the launches it saves (MI355X, 20 sweeps: 2^3 1.15 times as long in
+// passes, 4^3 1.31, 6^3 1.24, 7^3 1.10, 8^3 1.01, 9^3 0.84; two sweeps: 4^3 0.95,
+// 6^3 1.05, 7^3 0.98; one point, 10 sweeps a round: 0.79).  Nor for a single sweep of
+// a large grid, which moves as much either way (255^3 1.01, 511^3 0.97, 767^3 1.01,
+// 1023^3 1.01 - 1.04).
+bool rb3_passes_pay(int n, int nsweeps) {
+    if (nsweeps == 1) return n < 700;
+    return n < 2 || n > 7 || nsweeps == 2;
+}
+
 // opts (optional): only AUTO takes the fused passes; without the second black array
 // every sweep is a launch per half-sweep, Algorithm 1's structure.
 int rb3_prepare(const rbgs_grid* g, const void* u, const void* f, const rbgs_rb3_opts* opts,
@@ -1027,12 +1038,12 @@ int rb3_sweeps_fused(const rbgs_grid* g, const Rb3Workspace& w, int nsweeps, int
     return RBGS_OK;
 }
 
-// An even number of fused passes, or (no second array, a single sweep) a
-// launch per half-sweep.
+// An even number of fused passes, or (no second array, a single sweep, a tiny
+// grid) a launch per half-sweep.
 int rb3_sweeps(const rbgs_grid* g, const Rb3Workspace& w, int nsweeps, hipStream_t s,
                const int* stop) {
     const int passes = rb3_passes(nsweeps, true);
-    if (w.u2_black && passes > 0 && passes % 2 == 0)
+    if (w.u2_black && passes > 0 && passes % 2 == 0 && rb3_passes_pay(g->n, nsweeps))
         return rb3_sweeps_fused(g, w, nsweeps, passes, 0, s, stop);
     const double h2 = g->h * g->h;
     for (int it = 0; it < nsweeps; ++it) {
@@ -1903,7 +1914,7 @@ int rbgs_rb3_sweep_ex(const rbgs_grid* g, double* u, const double* f, int32_t ns
     const bool flags = rb3_flag_driven(opts);
     int capacity = 0;
     if (flags && (rc = rb3_flags_setup(g, opts, w, s, &capacity))) return rc;
-    const bool fused = w.u2_black != nullptr;
+    const bool fused = w.u2_black != nullptr && rb3_passes_pay(g->n, nsweeps);
     const int passes = rb3_passes(nsweeps, false), start = fused ? passes & 1 : 0;
     if ((rc = rb3_pack_both(g, w, u, f, s, start))) return rc;
     if (flags)
