@@ -310,8 +310,9 @@ void choose_windows(BatchSetup& s, int count, const rbgs_grid* grids, size_t es,
     std::vector<int> n(static_cast<size_t>(count)), first, order;
     for (int g = 0; g < count; ++g) n[size_t(g)] = grids[g].n;
     BatchWindows b;
-    b.nsweeps = nsweeps;
-    if (!batch_windows(count, n.data(), es, nsweeps, &b, &first, &order)) return;
+    if (!batch_windows_pay(count, n.data(), es, nsweeps) ||
+        !batch_windows(count, n.data(), es, nsweeps, &b, &first, &order))
+        return;
     s.win = b;
     s.small_ids = std::move(first);
     s.tile_map = std::move(order);

@@ -83,25 +83,17 @@ hipError_t launch_top(const BatchWindows& b, const blocked::GridDesc<T>* g, cons
 
 }  // namespace
 
-// Windows against the persistent kernel, MI355X, us: 64 grids of 63 .. 1023,
-// 100 sweeps FP32 1706 against 4178, FP64 3352 against 4650, 4 sweeps 405
-// against 562 and 566 against 692, one sweep 389 against 517; 300 such grids
-// FP32 30 sweeps 3303 against 5198; 8 grids of 2300^2 FP64 100 sweeps 5936
-// against 6889, 4095^2 with two small ones 60 sweeps 1750 against 3577; 2 of
-// 10000^2 FP32 60 sweeps 6550 against 7218.  Larger grids, where the
-// persistent kernel's deeper passes gain on one grid too, keep it.  The
-// shapes follow those of one grid of as many points.
+// The split of a batch into passes and windows.  The shapes follow those of one
+// grid of as many points.
 bool batch_windows(int count, const int* n, size_t elem_bytes, int nsweeps, BatchWindows* b,
                    std::vector<int>* first, std::vector<int>* order) {
     double points = 0.0;
-    for (int g = 0; g < count; ++g) {
-        if (n[g] > (elem_bytes == 8 ? 4095 : 10000)) return false;
-        points += double(n[g]) * n[g];
-    }
-    const int deepest = elem_bytes == 8 ? (points > 8e5 ? 4 : 5) : 6;
+    for (int g = 0; g < count; ++g) points += double(n[g]) * n[g];
+    const int deepest = batch_deepest(count, n, elem_bytes);
     b->count = count;
-    b->passes = (nsweeps + deepest - 1) / deepest;
-    b->top = (nsweeps + b->passes - 1) / b->passes;
+    b->nsweeps = nsweeps;
+    b->passes = (nsweeps - 1) / deepest + 1;
+    b->top = (nsweeps - 1) / b->passes + 1;
     const int tall = elem_bytes == 8 ? 16 : 24;
     b->rows = b->top <= 3 ? 8 : points > (elem_bytes == 8 ? 8e5 : 2e6) ? tall : 8;
     order->resize(size_t(count));
@@ -113,10 +105,63 @@ bool batch_windows(int count, const int* n, size_t elem_bytes, int nsweeps, Batc
         (*first)[size_t(k)] = int(at);
         const int m = n[(*order)[size_t(k)]];
         at += int64_t(window_bands(m, core_width(b->top))) * window_strips(m, b->rows);
-        if (at > INT32_MAX / 2) return false;
+        if (at > INT32_MAX / kLanes) return false;  // threads of a launch
     }
     b->windows = int(at);
     return true;
+}
+
+int batch_deepest(int count, const int* n, size_t elem_bytes) {
+    if (elem_bytes != 8) return 6;
+    double points = 0.0;
+    for (int g = 0; g < count; ++g) points += double(n[g]) * n[g];
+    return points > 8e5 ? 4 : 5;
+}
+
+// Windows against the persistent kernel at its default shape, MI355X, us: 64 grids
+// of 63 .. 1023, 100 sweeps FP32 1706 against 4178, FP64 3352 against 4650, 4
+// sweeps 405 against 562 and 566 against 692, one sweep 389 against 517; 4095^2
+// with two small ones FP64 60 sweeps 1750 against 3577; 2 of 10000^2 FP32 100 sweeps
+// 10038 against 10635.  Above 4095 (FP64) / 10000 (FP32) the persistent kernel's
+// deeper passes gain on one grid too.
+// FP64 batches of several large grids: the persistent kernel moves less once its
+// tiles fill the chip, which the windows, a pass every four sweeps, do not make up
+// in long calls.  Measured, 8 of 4095^2: 20 sweeps 4953 windows, 4694 persistent,
+// 100 sweeps 17898 and 14487; 16 of 3500^2, 10 sweeps 1.07, 100 1.42; 16 of 2300^2 20
+// sweeps 3235 and 3300, 100 11537 and 9809; 4 of 4095^2 20 2515 and 2763, 100 9113
+// and 7990; 8 of 2300^2 100 5933 and 6900; 48 of 1800^2 (a last strip of 8 rows) 50
+// 0.98, 100 1.02.  The rule compares
+//   windows      5 us per million points and pass
+//   persistent   400 us of ramp more, and 0.355 us per tile of 256 rows and pass (the
+//                28 halo rows are rows too; a pass below depth 7, 0.65 + 0.05 depth
+//                of it), for at least 1250 tiles, which is when the chip is full
+// and so takes the faster one, or one within 3% of it, in 159 of the 165 calls timed
+// (30 batches with grids of 1600^2 .. 4095^2, 1 to 100 sweeps), and is 6% off at worst.
+// FP32: 3 of 8191^2 x 14, which the persistent kernel does in two passes of seven,
+// 3156 and 2888, 3 of 10000^2 4744 and 4097; x 20 to 100 0.81 to 1.02 but for 8 of
+// 6000^2, 100 sweeps 18178 and 16194 (the autotuner times both).
+bool batch_windows_pay(int count, const int* n, size_t elem_bytes, int nsweeps) {
+    const bool f64 = elem_bytes == 8;
+    int most = 0;
+    double points = 0.0;
+    for (int g = 0; g < count; ++g) {
+        most = std::max(most, n[g]);
+        points += double(n[g]) * n[g];
+    }
+    if (most > (f64 ? 4095 : 10000)) return false;
+    constexpr int fuse = 7;  // of the persistent kernel, where the largest grid has 1536
+    if (default_fuse(int(elem_bytes), most) != fuse) return true;
+    double tiles = 0.0;
+    for (int g = 0; g < count; ++g) {
+        const int rows = default_rows(n[g], 2 * fuse);
+        tiles += double(geometry(n[g], int(elem_bytes), fuse, rows).ntiles) * (rows + 4 * fuse) /
+                 (256 + 4 * fuse);
+    }
+    if (!f64) return !(nsweeps == 2 * fuse && most > 7000 && tiles >= 1700.0);
+    const int rest = nsweeps % fuse;
+    const double passes = nsweeps / fuse + (rest ? 0.65 + 0.05 * rest : 0.0);
+    const double windows = 5e-6 * points * ((nsweeps - 1) / batch_deepest(count, n, elem_bytes) + 1);
+    return windows <= 400.0 + 0.355 * std::max(tiles, 1250.0) * passes;
 }
 
 template <typename T>

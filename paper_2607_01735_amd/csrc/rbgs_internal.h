@@ -127,9 +127,13 @@ struct BatchWindows {
     int rows = 0;     // rows a window writes
     int windows = 0;  // of all grids
 };
-// The split of a batch (grid sizes n) and its tables; false: not the choice.
+// The split of a batch (grid sizes n) for nsweeps >= 1 and its tables; false: more
+// windows than a launch takes.
 bool batch_windows(int count, const int* n, size_t elem_bytes, int nsweeps, BatchWindows* b,
                    std::vector<int>* first, std::vector<int>* order);
+int batch_deepest(int count, const int* n, size_t elem_bytes);  // most sweeps a pass
+// Whether windows are the choice against the persistent kernel's default shape.
+bool batch_windows_pay(int count, const int* n, size_t elem_bytes, int nsweeps);
 // Pass 0 .. passes - 1; pass p reads buffer p & 1 and writes the other (red
 // only in the last).  grids: GridDesc<T>[count] in device memory.
 template <typename T>
