@@ -331,9 +331,11 @@ int rbgs_solve(const rbgs_grid *g, rbgs_dtype dt, void *u, const void *f,
  * Grid g has its own size grids[g], device arrays u[g] and f[g] (natural
  * layout, type dt; the HOST arrays u and f hold the device pointers).
  * count in [1, 65535].  opts: kernel must be AUTO or BLOCKED.
- * AUTO with every tuning and debug option 0, and no grid above 4095 (FP64) /
- * 10000 (FP32): launches of up to 4 - 6 sweeps over the register windows of
- * all grids.  Otherwise the persistent blocked kernel: work items (pass,
+ * AUTO with every tuning and debug option 0: the way that rbgs_autotune_batched
+ * found faster for this batch shape, else by measured time launches of up to 4 - 6
+ * sweeps over the register windows of all grids (not with a grid above 4095 (FP64)
+ * / 10000 (FP32), nor for long calls of several large FP64 grids).  Otherwise the
+ * persistent blocked kernel: work items (pass,
  * grid, tile), handed out pass by pass with the largest grids first; each
  * grid's tiles follow the same dependency rule as a single grid; small grids
  * (opts->lds_max_n) are instead swept entirely in one workgroup's LDS;
@@ -377,14 +379,16 @@ int rbgs_batch_plan_destroy(rbgs_batch_plan *plan);
  * {4, 5, 6, 7} and tile heights {64, 128, 256} (two passes each after a
  * warm-up pass; the workspace copies are swept, u and f are only read),
  * then, for the best of those, the LDS-resident threshold (lds_max_n: none,
- * or 127 FP32 / 63 FP64), and stores the fastest choice for the batch shape
- * (dtype, CU count and the
+ * or 127 FP32 / 63 FP64), then that choice against the register windows over eight
+ * of its passes, and stores the result for the batch shape (dtype, CU count and the
  * multiset of grid sizes) in a process-wide table, appends it to the file
  * named by the environment variable RBGS_TUNE_CACHE if set (and reads that
- * file on first use), and returns it in *best (HOST, may be NULL) with its
- * time per sweep in *best_ms_per_sweep (HOST, may be NULL).  The stored
- * choice serves calls that run the persistent kernel (kernel BLOCKED, or a
- * grid too large for the windows).  Synchronises. */
+ * file on first use).  Calls with kernel AUTO and all options 0 run the faster of
+ * the two; calls that run the persistent kernel take its best shape.  *best (HOST,
+ * may be NULL) receives that shape, with kernel AUTO if the windows were faster
+ * (leave the options at 0 for those), else BLOCKED; *best_ms_per_sweep (HOST, may
+ * be NULL) the faster one's time per sweep.  Entries that an earlier library wrote
+ * to the file hold the persistent kernel's shape alone.  Synchronises. */
 int rbgs_autotune_batched(int32_t count, const rbgs_grid *grids,
                           rbgs_dtype dt, void *const *u, const void *const *f,
                           void *workspace, size_t workspace_bytes,

@@ -1,8 +1,8 @@
 // Batched sweeps: many independent grids of uneven sizes, by register windows
 // (batched_window.hip) where the caller leaves the way open, else in one
 // launch of the tile pipeline (blocked_pipeline.h); plus the batched
-// pack/unpack kernels, the graph-captured plan and the autotuner (of the
-// pipeline).  Of the pipeline:
+// pack/unpack kernels, the graph-captured plan and the autotuner, which times
+// both.  Of the pipeline:
 //
 // Work items are (pass, grid, tile).  Tickets run pass-major, and inside a
 // pass the grids are ordered largest first (longest-processing-time first),
@@ -291,9 +291,16 @@ struct BatchSetup {
     std::vector<int> tile_map;
     std::vector<int> small_ids;  // grids swept LDS-resident by k_batch_lds
     size_t small_lds_bytes = 0;  // dynamic LDS for the largest of them
-    // Swept by windows (win.passes > 0): tile_map holds the grids' order and
-    // small_ids their first windows instead.
+    // Swept by windows (win.passes > 0) there are no tiles and no LDS-resident grids;
+    // in the workspace these tables take the place of tile_map and small_ids.
     BatchWindows win;
+    std::vector<int> win_order, win_first;
+};
+
+// How a batch is swept: the persistent kernel's shape, or (windows) not by it.
+struct BatchChoice {
+    int fuse = 0, rows = 0, lds_max_n = 0;
+    bool windows = false;
 };
 
 // Whether the caller leaves the way of sweeping a batch open.
@@ -303,23 +310,16 @@ bool batch_open(const rbgs_sweep_opts* o) {
                   o->debug_stall_tile == 0);
 }
 
-// Makes a batch's sweeps run by windows, where they are the choice.
-void choose_windows(BatchSetup& s, int count, const rbgs_grid* grids, size_t es, int nsweeps,
-                    const rbgs_sweep_opts* o) {
-    if (!batch_open(o) || nsweeps < 1) return;
-    std::vector<int> n(static_cast<size_t>(count)), first, order;
+// Splits a batch into windows for nsweeps sweeps; false: too many of them.
+bool split_windows(BatchSetup& s, int count, const rbgs_grid* grids, size_t es, int nsweeps) {
+    std::vector<int> n(static_cast<size_t>(count));
     for (int g = 0; g < count; ++g) n[size_t(g)] = grids[g].n;
     BatchWindows b;
-    if (!batch_windows_pay(count, n.data(), es, nsweeps) ||
-        !batch_windows(count, n.data(), es, nsweeps, &b, &first, &order))
-        return;
+    if (nsweeps < 1 || !batch_windows(count, n.data(), es, nsweeps, &b, &s.win_first, &s.win_order))
+        return false;
     s.win = b;
-    s.small_ids = std::move(first);
-    s.tile_map = std::move(order);
-    s.total_tiles = 0;
-    s.small_lds_bytes = 0;
+    return true;
 }
-
 
 // LDS-resident threshold the autotuner tries: the largest grid of the
 // benchmark's size mix that fits (127 in FP32: 133 KB; 63 in FP64: 68 KB).
@@ -330,9 +330,9 @@ inline int tuned_lds_candidate(size_t es) { return es == 4 ? 127 : 63; }
 
 template <typename T>
 BatchSetup build_setup(int count, const rbgs_grid* grids, void* const* u, const void* const* f,
-                       const BatchLayout& lay, char* ws, int fuse, int rows_opt, int nsweeps,
-                       int lds_max_n) {
+                       const BatchLayout& lay, char* ws, const BatchChoice& how, int nsweeps) {
     BatchSetup s;
+    const int fuse = how.fuse, rows_opt = how.rows, lds_max_n = how.lds_max_n;
     const size_t lds_limit = lds_max_n > 0 ? lds_limit_bytes() : 0;
     s.fuse = fuse;
     s.passes = nsweeps / fuse;
@@ -390,7 +390,8 @@ BatchSetup build_setup(int count, const rbgs_grid* grids, void* const* u, const 
         row += n + 2;
     }
     s.total_rows = row;
-    for (int k = 0; k < count; ++k) {
+    const bool windows = how.windows && split_windows(s, count, grids, es, nsweeps);
+    for (int k = 0; k < count && !windows; ++k) {
         const int g = order[k];
         const size_t lds = lds_grid_bytes(grids[g].n, es);
         if (grids[g].n <= lds_max_n && lds <= lds_limit) {
@@ -488,7 +489,7 @@ hipError_t enqueue_batch(const BatchSetup& su, const BatchLayout& lay, char* ws,
     if ((e = launch_zero(ws + lay.header, 256, s)) != hipSuccess) return e;
     if (su.win.passes > 0) {
         const int* first = reinterpret_cast<const int*>(ws + lay.small);
-        for (int p = 0; p < su.win.passes; ++p)
+        for (int p = 0; p < su.win.passes; ++p)  // map: the grids' order
             if ((e = launch_batch_pass<T>(su.win, gd, first, map, p, s)) != hipSuccess) return e;
         if (do_unpack) {
             hipLaunchKernelGGL((k_batch_unpack<typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type>),
@@ -587,8 +588,10 @@ int check_ws(void* ws, size_t bytes, size_t need) {
 
 
 // --- autotuner cache --------------------------------------------------------
+// The persistent kernel's best shape for a batch, and whether the windows were
+// faster still (way 1) or not (0); -1: a choice that was made without timing them.
 struct Tuned {
-    int fuse, rows, lds_max_n;
+    int fuse, rows, lds_max_n, way;
 };
 std::mutex g_tune_mu;
 std::map<std::string, Tuned> g_tune;  // batch shape -> tuned parameters
@@ -599,7 +602,7 @@ std::string tune_key(int count, const rbgs_grid* grids, int dt) {
     int dev = 0, cus = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    std::string k = std::string(dt == RBGS_F64 ? "v2/f64" : "v2/f32") + "/cu" + std::to_string(cus);
+    std::string k = std::string(dt == RBGS_F64 ? "/f64" : "/f32") + "/cu" + std::to_string(cus);
     for (auto& kv : hist) k += "/" + std::to_string(kv.first) + "x" + std::to_string(kv.second);
     return k;
 }
@@ -612,14 +615,19 @@ void load_tune_file() {
     if (!path) return;
     FILE* fp = std::fopen(path, "r");
     if (!fp) return;
-    // one entry per line: key fuse rows lds_max_n ms (other lines are skipped)
+    // one entry per line, "v3" and the key, fuse rows lds_max_n ms way; "v2" entries
+    // have no way and give way to a "v3" one (other lines are skipped)
     char line[4352], key[4096];
     while (std::fgets(line, sizeof line, fp)) {
-        int fuse = 0, rows = 0, lds = 0;
+        int fuse = 0, rows = 0, lds = 0, way = -1;
         float ms = 0.f;
-        if (std::sscanf(line, "%4095s %d %d %d %f", key, &fuse, &rows, &lds, &ms) == 5 &&
-            fuse >= 1 && fuse <= kMaxFuse && rows >= kMinRows && lds >= -1)
-            g_tune[key] = Tuned{fuse, rows, lds};
+        const int got = std::sscanf(line, "%4095s %d %d %d %f %d", key, &fuse, &rows, &lds, &ms, &way);
+        if (got < 5 || fuse < 1 || fuse > kMaxFuse || rows < kMinRows || lds < -1) continue;
+        const bool v3 = std::strncmp(key, "v3/", 3) == 0;
+        if (v3 ? got != 6 || way < 0 || way > 1 : std::strncmp(key, "v2/", 3) != 0) continue;
+        const auto it = g_tune.find(key + 2);
+        if (!v3 && it != g_tune.end() && it->second.way >= 0) continue;
+        g_tune[key + 2] = Tuned{fuse, rows, lds, v3 ? way : -1};
     }
     std::fclose(fp);
 }
@@ -630,34 +638,47 @@ void store_tune(const std::string& key, const Tuned& t, float ms) {
     if (!path) return;
     FILE* fp = std::fopen(path, "a");
     if (!fp) return;
-    std::fprintf(fp, "%s %d %d %d %.6f\n", key.c_str(), t.fuse, t.rows, t.lds_max_n, double(ms));
+    std::fprintf(fp, "v3%s %d %d %d %.6f %d\n", key.c_str(), t.fuse, t.rows, t.lds_max_n, double(ms),
+                 t.way);
     std::fclose(fp);
 }
 
-// (fuse, rows, lds_max_n) for a batch: explicit options first, then the
-// tuned choice, then the defaults (default_fuse, per-grid default tile
+// How nsweeps sweeps of a batch run: explicit options first, then the tuned
+// choice, then the defaults (batch_windows_pay, default_fuse, per-grid default tile
 // height, no LDS-resident grids).
-void choose_params(int count, const rbgs_grid* grids, int dt, const rbgs_sweep_opts* o,
-                   int* fuse, int* rows, int* lds_max_n) {
-    *fuse = (o && o->fuse > 0) ? o->fuse : 0;
-    *rows = (o && o->tile_rows > 0) ? o->tile_rows : 0;
-    *lds_max_n = o ? o->lds_max_n : 0;
-    if (*fuse == 0 || *rows == 0 || *lds_max_n == 0) {
+BatchChoice choose(int count, const rbgs_grid* grids, int dt, const rbgs_sweep_opts* o,
+                   int nsweeps) {
+    BatchChoice c;
+    c.fuse = (o && o->fuse > 0) ? o->fuse : 0;
+    c.rows = (o && o->tile_rows > 0) ? o->tile_rows : 0;
+    c.lds_max_n = o ? o->lds_max_n : 0;
+    int way = -1;
+    if (c.fuse == 0 || c.rows == 0 || c.lds_max_n == 0) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_tune_file();
         auto it = g_tune.find(tune_key(count, grids, dt));
         if (it != g_tune.end()) {
-            if (*fuse == 0) *fuse = it->second.fuse;
-            if (*rows == 0) *rows = it->second.rows;
-            if (*lds_max_n == 0) *lds_max_n = it->second.lds_max_n;
+            if (c.fuse == 0) c.fuse = it->second.fuse;
+            if (c.rows == 0) c.rows = it->second.rows;
+            if (c.lds_max_n == 0) c.lds_max_n = it->second.lds_max_n;
+            way = it->second.way;
         }
     }
-    if (*fuse == 0) {
-        int nmax = 1;
-        for (int g = 0; g < count; ++g) nmax = grids[g].n > nmax ? grids[g].n : nmax;
-        *fuse = default_fuse(dt == RBGS_F64 ? 8 : 4, nmax);
+    int nmax = 1;
+    for (int g = 0; g < count; ++g) nmax = grids[g].n > nmax ? grids[g].n : nmax;
+    const int es = dt == RBGS_F64 ? 8 : 4;
+    if (c.fuse == 0) c.fuse = default_fuse(es, nmax);
+    if (c.lds_max_n == 0) c.lds_max_n = -1;
+    if (batch_open(o) && nsweeps > 0) {
+        if (way >= 0) {
+            c.windows = way == 1;
+        } else {
+            std::vector<int> n(static_cast<size_t>(count));
+            for (int g = 0; g < count; ++g) n[size_t(g)] = grids[g].n;
+            c.windows = batch_windows_pay(count, n.data(), size_t(es), nsweeps);
+        }
     }
-    if (*lds_max_n == 0) *lds_max_n = -1;
+    return c;
 }
 
 template <typename T>
@@ -668,11 +689,14 @@ int upload_setup(const BatchSetup& su, const BatchLayout& lay, char* ws, int cou
     if (e == hipSuccess)
         e = hipMemcpyAsync(ws + lay.pdesc, su.pdesc.data(), sizeof(PackDesc) * count,
                            hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && !su.tile_map.empty())
-        e = hipMemcpyAsync(ws + lay.tile_map, su.tile_map.data(), sizeof(int) * su.tile_map.size(),
+    const bool windows = su.win.passes > 0;
+    const std::vector<int>& map = windows ? su.win_order : su.tile_map;
+    const std::vector<int>& small = windows ? su.win_first : su.small_ids;
+    if (e == hipSuccess && !map.empty())
+        e = hipMemcpyAsync(ws + lay.tile_map, map.data(), sizeof(int) * map.size(),
                            hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && !su.small_ids.empty())
-        e = hipMemcpyAsync(ws + lay.small, su.small_ids.data(), sizeof(int) * su.small_ids.size(),
+    if (e == hipSuccess && !small.empty())
+        e = hipMemcpyAsync(ws + lay.small, small.data(), sizeof(int) * small.size(),
                            hipMemcpyHostToDevice, s);
     // the host tables are freed when the caller returns: wait for the copies
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -694,10 +718,8 @@ int sweep_batched_t(int32_t count, const rbgs_grid* grids, void* const* u, const
                     int32_t nsweeps, const rbgs_sweep_opts* o, char* ws, hipStream_t s) {
     const rbgs_dtype dt = sizeof(T) == 8 ? RBGS_F64 : RBGS_F32;
     const BatchLayout lay = batch_layout(count, grids, dt);
-    int fuse = 0, rows = 0, lds = 0;
-    choose_params(count, grids, dt, o, &fuse, &rows, &lds);
-    BatchSetup su = build_setup<T>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
-    choose_windows(su, count, grids, sizeof(T), nsweeps, o);
+    const BatchSetup su = build_setup<T>(count, grids, u, f, lay, ws,
+                                         choose(count, grids, dt, o, nsweeps), nsweeps);
     int rc = upload_setup<T>(su, lay, ws, count, s);
     if (rc) return rc;
     EventPair ev;
@@ -869,11 +891,9 @@ int solve_batched_ir(int32_t count, const rbgs_grid* grids, double* const* u,
                 sub.pitch[a] = L.inner.pitch[act[a]];
                 sg[a] = grids[act[a]];
             }
-            int fuse = 0, rows = 0, lds = 0;
-            choose_params(na, sg.data(), RBGS_F32, &o->sweep, &fuse, &rows, &lds);
-            BatchSetup su =
-                build_setup<float>(na, sg.data(), nu.data(), nf.data(), sub, ws, fuse, rows, k, lds);
-            choose_windows(su, na, sg.data(), 4, k, &o->sweep);
+            const BatchSetup su =
+                build_setup<float>(na, sg.data(), nu.data(), nf.data(), sub, ws,
+                                   choose(na, sg.data(), RBGS_F32, &o->sweep, k), k);
             if ((rc = upload_setup<float>(su, sub, ws, na, s))) return rc;
             e = enqueue_batch<float>(su, sub, ws, na, &o->sweep, false, false, s);
             if (e != hipSuccess)
@@ -966,7 +986,7 @@ int solve_batched_f64(int32_t count, const rbgs_grid* grids, double* const* u,
     {
         const BatchSetup su = build_setup<double>(count, grids, reinterpret_cast<void* const*>(u),
                                                   reinterpret_cast<const void* const*>(f), L.batch,
-                                                  ws, 1, 0, 0, -1);
+                                                  ws, BatchChoice{1, 0, -1}, 0);
         int rc = upload_setup<double>(su, L.batch, ws, count, s);
         if (rc) return rc;
         hipError_t e = enqueue_batch<double>(su, L.batch, ws, count, nullptr, true, false, s);
@@ -1027,12 +1047,12 @@ int solve_batched_f64(int32_t count, const rbgs_grid* grids, double* const* u,
                 sub.pitch[a] = L.batch.pitch[act[a]];
                 sg[a] = grids[act[a]];
             }
-            int fuse = 0, rows = 0, lds = 0;
-            choose_params(na, sg.data(), RBGS_F64, &o->sweep, &fuse, &rows, &lds);
-            if (sor) lds = -1;  // the LDS-resident sweep is Gauss-Seidel only
-            BatchSetup su =
-                build_setup<double>(na, sg.data(), nu.data(), nf.data(), sub, ws, fuse, rows, k, lds);
-            if (!sor) choose_windows(su, na, sg.data(), 8, k, &o->sweep);
+            BatchChoice how = choose(na, sg.data(), RBGS_F64, &o->sweep, k);
+            if (sor) {  // the LDS-resident sweep and the windows are Gauss-Seidel only
+                how.lds_max_n = -1;
+                how.windows = false;
+            }
+            BatchSetup su = build_setup<double>(na, sg.data(), nu.data(), nf.data(), sub, ws, how, k);
             // a grid whose iterate sits in buffer 1 runs with its buffers
             // swapped, so that every launch starts from "buffer 0"
             GridDesc<double>* gd = reinterpret_cast<GridDesc<double>*>(su.gdesc.data());
@@ -1127,16 +1147,13 @@ int rbgs_batch_plan_create(rbgs_batch_plan** plan, int32_t count, const rbgs_gri
     hipStream_t cs = nullptr;
     if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess)
         return bfail(RBGS_EHIP, "stream create");
-    int fuse = 0, rows = 0, lds = 0;
-    choose_params(count, grids, dt, opts, &fuse, &rows, &lds);
+    const BatchChoice how = choose(count, grids, dt, opts, nsweeps);
     BatchSetup su;
     if (dt == RBGS_F64) {
-        su = build_setup<double>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
-        choose_windows(su, count, grids, 8, nsweeps, opts);
+        su = build_setup<double>(count, grids, u, f, lay, ws, how, nsweeps);
         rc = upload_setup<double>(su, lay, ws, count, cs);
     } else {
-        su = build_setup<float>(count, grids, u, f, lay, ws, fuse, rows, nsweeps, lds);
-        choose_windows(su, count, grids, 4, nsweeps, opts);
+        su = build_setup<float>(count, grids, u, f, lay, ws, how, nsweeps);
         rc = upload_setup<float>(su, lay, ws, count, cs);
     }
     if (rc) {
@@ -1147,7 +1164,7 @@ int rbgs_batch_plan_create(rbgs_batch_plan** plan, int32_t count, const rbgs_gri
     p->lay = lay;
     p->ws = ws;
     p->passes = su.passes;
-    p->fuse = fuse;
+    p->fuse = how.fuse;
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         hipError_t e2 = dt == RBGS_F64 ? enqueue_batch<double>(su, lay, ws, count, opts, true, true, cs)
@@ -1202,53 +1219,76 @@ int rbgs_autotune_batched(int32_t count, const rbgs_grid* grids, rbgs_dtype dt, 
     const int rowsv[] = {64, 128, 256};
     const int lds_candidate = tuned_lds_candidate(dt == RBGS_F64 ? 8 : 4);
     bool packed = false;
-    // time per sweep of one candidate: two passes, timed after one untimed
-    // warm-up pass
-    auto time_one = [&](int fu, int ro, int lds, float* per_sweep) -> int {
-        BatchSetup su = dt == RBGS_F64
-                            ? build_setup<double>(count, grids, u, f, lay, ws, fu, ro, 2 * fu, lds)
-                            : build_setup<float>(count, grids, u, f, lay, ws, fu, ro, 2 * fu, lds);
-        int r = dt == RBGS_F64 ? upload_setup<double>(su, lay, ws, count, s)
-                               : upload_setup<float>(su, lay, ws, count, s);
-        if (r) return r;
-        BatchSetup warm = su;
-        warm.passes = 1;
-        hipError_t e = dt == RBGS_F64
-                           ? enqueue_batch<double>(warm, lay, ws, count, nullptr, !packed, false, s)
-                           : enqueue_batch<float>(warm, lay, ws, count, nullptr, !packed, false, s);
+    const size_t es = dt == RBGS_F64 ? 8 : 4;
+    auto enqueue = [&](const BatchSetup& su) {
+        const hipError_t e =
+            dt == RBGS_F64 ? enqueue_batch<double>(su, lay, ws, count, nullptr, !packed, false, s)
+                           : enqueue_batch<float>(su, lay, ws, count, nullptr, !packed, false, s);
         packed = true;
-        if (e == hipSuccess) e = hipEventRecord(a, s);
-        if (e == hipSuccess)
-            e = dt == RBGS_F64 ? enqueue_batch<double>(su, lay, ws, count, nullptr, false, false, s)
-                               : enqueue_batch<float>(su, lay, ws, count, nullptr, false, false, s);
-        if (e == hipSuccess) e = hipEventRecord(b, s);
-        if (e == hipSuccess) e = hipEventSynchronize(b);
+        return e;
+    };
+    // time per sweep of one candidate over nsweeps sweeps, after an untimed run of
+    // warm sweeps
+    auto time_one = [&](const BatchChoice& how, int warm, int nsweeps, float* per_sweep) -> int {
+        auto setup = [&](int k) {
+            return dt == RBGS_F64 ? build_setup<double>(count, grids, u, f, lay, ws, how, k)
+                                  : build_setup<float>(count, grids, u, f, lay, ws, how, k);
+        };
+        hipError_t e = hipSuccess;
+        for (int k : {warm, nsweeps}) {
+            const BatchSetup su = setup(k);
+            int r = dt == RBGS_F64 ? upload_setup<double>(su, lay, ws, count, s)
+                                   : upload_setup<float>(su, lay, ws, count, s);
+            if (r) return r;
+            if (e == hipSuccess) e = hipEventRecord(a, s);
+            if (e == hipSuccess) e = enqueue(su);
+            if (e == hipSuccess) e = hipEventRecord(b, s);
+            if (e == hipSuccess) e = hipEventSynchronize(b);
+            if (e != hipSuccess)
+                return bfail(RBGS_EHIP, std::string("autotune: ") + hipGetErrorString(e));
+        }
         float ms = 0.f;
-        if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
-        if (e != hipSuccess) return bfail(RBGS_EHIP, std::string("autotune: ") + hipGetErrorString(e));
-        if ((r = read_error_word(lay, ws, s))) return r;
-        *per_sweep = ms / float(2 * fu);
+        if ((e = hipEventElapsedTime(&ms, a, b)) != hipSuccess)
+            return bfail(RBGS_EHIP, std::string("autotune: ") + hipGetErrorString(e));
+        int r = read_error_word(lay, ws, s);
+        if (r) return r;
+        *per_sweep = ms / float(nsweeps);
         return RBGS_OK;
     };
     float best_ms = 1e30f;
-    Tuned bt{kMaxFuse, 0, -1};
+    BatchChoice bt{kMaxFuse, 0, -1};
     for (int fu : fuses) {
         for (int ro : rowsv) {
             float per_sweep = 0.f;
-            if ((rc = time_one(fu, ro, -1, &per_sweep))) break;
+            if ((rc = time_one({fu, ro, -1}, fu, 2 * fu, &per_sweep))) break;
             if (per_sweep < best_ms) {
                 best_ms = per_sweep;
-                bt = Tuned{fu, ro, -1};
+                bt = BatchChoice{fu, ro, -1};
             }
         }
         if (rc) break;
     }
     if (!rc) {  // then the small grids LDS-resident instead
         float per_sweep = 0.f;
-        rc = time_one(bt.fuse, bt.rows, lds_candidate, &per_sweep);
+        rc = time_one({bt.fuse, bt.rows, lds_candidate}, bt.fuse, 2 * bt.fuse, &per_sweep);
         if (!rc && per_sweep < best_ms) {
             best_ms = per_sweep;
             bt.lds_max_n = lds_candidate;
+        }
+    }
+    if (!rc) {  // the windows against the best of these, over as many sweeps
+        BatchChoice wi = bt;
+        wi.windows = true;
+        float persistent = 0.f, windows = 0.f;
+        rc = time_one(bt, bt.fuse, 8 * bt.fuse, &persistent);
+        if (!rc) best_ms = persistent;
+        BatchSetup probe;
+        if (!rc && split_windows(probe, count, grids, es, 8 * bt.fuse)) {
+            rc = time_one(wi, bt.fuse, 8 * bt.fuse, &windows);
+            if (!rc && windows < persistent) {
+                best_ms = windows;
+                bt.windows = true;
+            }
         }
     }
     (void)hipEventDestroy(a);
@@ -1257,11 +1297,12 @@ int rbgs_autotune_batched(int32_t count, const rbgs_grid* grids, rbgs_dtype dt, 
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_tune_file();
-        store_tune(tune_key(count, grids, dt), bt, best_ms);
+        store_tune(tune_key(count, grids, dt),
+                   Tuned{bt.fuse, bt.rows, bt.lds_max_n, bt.windows ? 1 : 0}, best_ms);
     }
     if (best) {
         std::memset(best, 0, sizeof *best);
-        best->kernel = RBGS_KERNEL_BLOCKED;
+        best->kernel = bt.windows ? RBGS_KERNEL_AUTO : RBGS_KERNEL_BLOCKED;
         best->fuse = bt.fuse;
         best->tile_rows = bt.rows;
         best->lds_max_n = bt.lds_max_n;

@@ -774,7 +774,10 @@ def rbgs_solve_batched(us, fs, max_sweeps, rel_tol, inner_sweeps, precision="f32
 
 
 def rbgs_autotune_batched(us, fs, hs=None, workspace=None, stream=None):
-    """Tune (fuse, tile_rows, lds_max_n) for this batch shape; returns the choice."""
+    """Times the ways to sweep this batch shape, which calls without options then
+    follow; returns the persistent kernel's best (fuse, tile_rows, lds_max_n), "kernel":
+    "blocked", or "auto" where the register windows were faster, and the faster
+    one's time."""
     b = _Batch(us, fs, hs)
     ws = b.workspace(workspace)
     best = rbgs_sweep_opts()
@@ -782,8 +785,8 @@ def rbgs_autotune_batched(us, fs, hs=None, workspace=None, stream=None):
     _bcheck(_lib.rbgs_autotune_batched(b.count, b.grids, b.code, b.u, b.f, _vp(ws.data_ptr()),
                                        ws.numel(), _stream_ptr(stream, b.device),
                                        ctypes.byref(best), ctypes.byref(ms)))
-    return {"fuse": best.fuse, "tile_rows": best.tile_rows, "lds_max_n": best.lds_max_n,
-            "ms_per_sweep": ms.value}
+    return {"kernel": "auto" if best.kernel == _KERNELS["auto"] else "blocked", "fuse": best.fuse,
+            "tile_rows": best.tile_rows, "lds_max_n": best.lds_max_n, "ms_per_sweep": ms.value}
 
 
 # ---------------------------------------------------------------------------
