@@ -1176,9 +1176,8 @@ WgradSplit wgrad_split(int batch, int n, int cin_p, int cout) {
     return p;
 }
 
-// Floats of partial sums the largest fixed-order reduction needs: all layers'
-// gradients (a slot of cout x cin x 9 and cout per workgroup, for the batch
-// that has most), the head (blocks of 17), the loss and the rms row sums.
+// Floats of partial sums a layer's gradients need: a slot of cout x cin x 9 and
+// cout per workgroup, for the batch that has most.
 size_t wgrad_floats(const Net& net, const Layer& l) {
     size_t most = 0;
     for (int b = 1; b <= net.batch; ++b) {
@@ -1188,13 +1187,21 @@ size_t wgrad_floats(const Net& net, const Layer& l) {
     return most * (size_t(l.cout) * size_t(l.cin) * 9 + size_t(l.cout));
 }
 
-size_t parts_floats(const Net& net) {
-    size_t most = 0, sum = 0;
+// Floats of partial sums the fixed-order reductions need: the layers' gradients, the
+// head (blocks of 17), the loss and the rms row sums.  The layers' stay until one
+// launch adds them all, where that takes at most an eighth of what the rest of the
+// workspace does (`others` bytes); else two and a half times the largest layer's,
+// with a launch whenever they are full (grad_reduce).  511^2 x 8 with factor 4, 75 MB:
+// one launch; 127^2 x 1024, whose layers need 2.1 GB together, 1.5 GB and two.
+size_t parts_floats(const Net& net, size_t others) {
+    size_t largest = 0, all = 0;
     const size_t B = size_t(net.batch);
     for (const auto& l : net.layers) {
-        sum += wgrad_floats(net, l);
+        const size_t f = wgrad_floats(net, l);
+        largest = std::max(largest, f);
+        all += f;
     }
-    most = sum;
+    size_t most = std::min(all, std::max(largest * 5 / 2, others / 8 / sizeof(float)));
     const size_t px0 = B * size_t(net.n[0]) * size_t(net.n[0]);
     most = std::max(most, (px0 + 255) / 256 * 17);
     most = std::max(most, 2 * B * size_t(net.n[0]));  // the rms row sums (doubles)
@@ -1223,8 +1230,6 @@ size_t carve(Net& net, char* base) {
     const int64_t px0 = int64_t(net.n[0]) * net.n[0];
     net.y = reinterpret_cast<float*>(take(B * px0 * 4));
     net.dy = reinterpret_cast<float*>(take(B * px0 * 4));
-    net.parts_floats = parts_floats(net);
-    net.parts = reinterpret_cast<float*>(take(net.parts_floats * 4));
     net.guess = reinterpret_cast<double*>(take(size_t(net.n[0] + 2) * (net.n[0] + 2) * 8));
     for (int l = 0; l < kLevels; ++l) {
         const int64_t px = B * net.n[l] * net.n[l];
@@ -1244,6 +1249,8 @@ size_t carve(Net& net, char* base) {
             net.gd[l] = act(kC[l]);
         }
     }
+    net.parts_floats = parts_floats(net, off);
+    net.parts = reinterpret_cast<float*>(take(net.parts_floats * 4));
     return off;
 }
 
@@ -1416,6 +1423,15 @@ struct Partials {
     int blocks = 0;
 };
 
+// Adds the layers' partial sums so far; their room is free for the next ones.
+hipError_t grad_reduce(Partials& parts, hipStream_t s) {
+    if (parts.args.layers == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_reduce_slots, dim3(unsigned(parts.blocks)), dim3(64 * kReduceWaves), 0, s,
+                       parts.args);
+    parts = Partials();
+    return hipGetLastError();
+}
+
 hipError_t wgrad(const Net& net, Partials& parts, const Layer& L, In x, const bf16* dy, const bf16* y,
                  int batch, hipStream_t s) {
     const int64_t dys = L.cout, ys = L.cout;
@@ -1433,13 +1449,17 @@ hipError_t wgrad(const Net& net, Partials& parts, const Layer& L, In x, const bf
     a.cin = L.cin_p;
     a.cout = L.cout;
     a.cin_w = L.cin;  // the first layer's padded input channels feed no weight
-    a.part = net.parts + parts.used;
     const bool one = L.cin == 1;  // one channel in memory
     const WgradSplit p = wgrad_split(batch, a.h, a.cin, a.cout);
     a.rows = p.rows;
     const int64_t slots = int64_t(batch) * p.strips * p.groups;
     const int64_t blocks = slots * (a.cin / (16 * p.ti)) * (a.cout / (16 * p.to));
     const int64_t count = int64_t(L.cout) * L.cin * 9 + L.cout;  // the bias follows the weights
+    if (parts.used + size_t(slots * count) > net.parts_floats) {
+        const hipError_t e = grad_reduce(parts, s);
+        if (e != hipSuccess) return e;
+    }
+    a.part = net.parts + parts.used;
     if (parts.used + size_t(slots * count) > net.parts_floats || parts.args.layers == kMaxLayers ||
         blocks > (int64_t(1) << 31) - 1 ||
         L.b_off != L.w_off + size_t(count - L.cout) || ((one ? 0 : x.ca) | x.cb | a.cout) % 16 != 0 ||
@@ -1635,9 +1655,7 @@ hipError_t backward(Net& net, int batch, hipStream_t s) {
                               net.n[l], in_channels(l), 1.f / float(net.factor * net.factor), 1, s));
         }
     }
-    hipLaunchKernelGGL(k_reduce_slots, dim3(unsigned(parts.blocks)), dim3(64 * kReduceWaves), 0, s,
-                       parts.args);
-    return hipGetLastError();
+    return grad_reduce(parts, s);
 }
 
 hipError_t adam(Net& net, float lr, hipStream_t s) {
