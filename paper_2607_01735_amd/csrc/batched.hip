@@ -32,6 +32,7 @@
 #include <vector>
 
 #include "blocked_pipeline.h"
+#include "lds_limit.h"
 #include "rbgs.h"
 #include "rbgs_blocked.h"
 #include "rbgs_internal.h"

@@ -19,6 +19,7 @@
 //   even), (e[I][J] + e[I+1][J]) * 0.5 (i odd), (e[I][J] + e[I][J+1]) * 0.5
 //   (j odd), ((e[I][J] + e[I][J+1]) + (e[I+1][J] + e[I+1][J+1])) * 0.25
 //   (both odd); then u + v.
+#include "lds_limit.h"
 #include "rbgs_internal.h"
 
 namespace rbgs {
