@@ -241,12 +241,21 @@ def mg_model_bytes(sizes, nu1, nu2, coarse_sweeps):
     return total + 16.0 * sizes[0] ** 2
 
 
+def mg_leg_model_bytes(sizes):
+    """The same of the automatic kernel's cycle: a pass down (black and f read,
+    black and the coarse right-hand side written; black not read on a coarse
+    level, which starts from zero) and one up (black, f and the coarse iterate
+    read, both colours written; the residual's norm with it)."""
+    return sum(n * n * ((18.0 if k == 0 else 14.0) + 22.0) for k, n in enumerate(sizes) if n > 63)
+
+
 def multigrid_to_tolerance(torch, rb, W, tol=1e-8, sizes=(1023, 8191, 16383)):
     """Red-black Gauss-Seidel as the smoother of a V-cycle (the multilevel
     extension): wall time and cycles to rel <= tol from u = 0 on the 64-mode
     Fourier right-hand side (seed 0), V(2,2) and V(1,1) on the plain
-    smoother, and the time per cycle from 10 fixed cycles with the model
-    bytes of a cycle per that time."""
+    smoother and, under "auto", with the automatic kernel (a pass a leg), and
+    the time per cycle from 10 fixed cycles with the model bytes of a cycle
+    per that time."""
     out = {"problem": f"n x n FP64, 64 Fourier modes seed 0, u0=0, rel<={tol:g}"}
     for n in sizes:
         h = W.spacing(n)
@@ -262,53 +271,55 @@ def multigrid_to_tolerance(torch, rb, W, tol=1e-8, sizes=(1023, 8191, 16383)):
                 break
             m = (m - 1) // 2
         for nu in ((2, 2), (1, 1)):
-            u = torch.zeros_like(f)
-            rb.rbgs_mg_solve(u, f, 1, -1.0, pre_sweeps=nu[0], post_sweeps=nu[1], h=h,
-                             kernel="plain", workspace=ws)  # warm-up
-            best, info = None, None
-            for _ in range(3):
-                u.zero_()
-                torch.cuda.synchronize()
-                t0 = time.perf_counter()
-                info = rb.rbgs_mg_solve(u, f, 40, tol, pre_sweeps=nu[0], post_sweeps=nu[1], h=h,
-                                        kernel="plain", workspace=ws)
-                torch.cuda.synchronize()
-                dt = time.perf_counter() - t0
-                best = dt if best is None else min(best, dt)
-            u.zero_()
-            torch.cuda.synchronize()
-            t0 = time.perf_counter()
-            rb.rbgs_mg_solve(u, f, 10, -1.0, pre_sweeps=nu[0], post_sweeps=nu[1], h=h,
-                             kernel="plain", workspace=ws)
-            torch.cuda.synchronize()
-            per_cycle = (time.perf_counter() - t0) / 10
-            model = mg_model_bytes(levels, nu[0], nu[1], info["coarse_sweeps"])
             key = f"n{n}_V{nu[0]}{nu[1]}"
-            out[key] = {"seconds": round(best, 5), "cycles": info["cycles"],
-                        "rel_residual": info["rel_residual"], "status": info["status"],
-                        "levels": info["levels"], "graph": info["graph"],
-                        "ms_per_cycle": round(per_cycle * 1e3, 3),
-                        "model_bytes_per_cycle": model,
-                        "model_GBs": round(model / per_cycle / 1e9, 1)}
-            log(f"multigrid {key}: {best * 1e3:.2f} ms, {info['cycles']} cycles, "
-                f"rel={info['rel_residual']:.3e}, {per_cycle * 1e3:.3f} ms/cycle, "
-                f"{model / per_cycle / 1e9:.0f} GB/s model")
+            for kernel in ("plain", "auto"):
+                u = torch.zeros_like(f)
+
+                def solve(cycles, stop):
+                    u.zero_()
+                    torch.cuda.synchronize()
+                    t0 = time.perf_counter()
+                    got = rb.rbgs_mg_solve(u, f, cycles, stop, pre_sweeps=nu[0], post_sweeps=nu[1],
+                                           h=h, kernel=kernel, workspace=ws)
+                    torch.cuda.synchronize()
+                    return time.perf_counter() - t0, got
+
+                solve(1, -1.0)  # warm-up
+                best, info = min((solve(40, tol) for _ in range(3)), key=lambda r: r[0])
+                per_cycle = solve(10, -1.0)[0] / 10
+                model = (mg_model_bytes(levels, nu[0], nu[1], info["coarse_sweeps"])
+                         if kernel == "plain" else mg_leg_model_bytes(levels))
+                row = {"seconds": round(best, 5), "cycles": info["cycles"],
+                       "rel_residual": info["rel_residual"], "status": info["status"],
+                       "levels": info["levels"], "graph": info["graph"],
+                       "ms_per_cycle": round(per_cycle * 1e3, 3),
+                       "model_bytes_per_cycle": model,
+                       "model_GBs": round(model / per_cycle / 1e9, 1)}
+                if kernel == "plain":
+                    out[key] = row
+                else:
+                    out[key]["auto"] = row
+                log(f"multigrid {key} {kernel}: {best * 1e3:.2f} ms, {info['cycles']} cycles, "
+                    f"rel={info['rel_residual']:.3e}, {per_cycle * 1e3:.3f} ms/cycle, "
+                    f"{model / per_cycle / 1e9:.0f} GB/s model")
         del f, ws, u
         torch.cuda.empty_cache()
     return out
 
 
 MC9_BYTES_PER_LUP = 40.0  # per sweep: four quarter-sweeps, each 5 words per updated point
+MC9_PASS_BYTES_PER_LUP = 20.0 / 3  # a pass of three sweeps: three colours and f read, three written
 
 
 def multicolour9_throughput(torch, rb, W, n=8191, sweeps=100, with_solve=True):
     """Four-colour Gauss-Seidel for the 9-point Laplacian (the multi-colour
     extension) on the 8191^2 FP64 grid: time of `sweeps` sweeps as the
     difference of a (sweeps + 1)-sweep call and a 1-sweep call (both pack and
-    unpack once), GLUP/s and model bytes (40 B per point per sweep); and the
-    time to rel <= 1e-8 at 255^2 from u = 0 (sine right-hand side); each for
-    the plain kernel (a launch per colour) and the flag-driven form (one
-    launch, a counter per block)."""
+    unpack once), GLUP/s and model bytes per point and sweep; and the time to
+    rel <= 1e-8 at 255^2 from u = 0 (sine right-hand side); each for the
+    automatic kernel (passes of two or three sweeps), the plain one (a launch
+    per colour, 40 B) and the flag-driven form (one launch, a counter per
+    block)."""
     h = W.spacing(n)
     f = torch.from_numpy(W.uniform_rhs(n, seed=0)).to("cuda")
     u = torch.zeros_like(f)
@@ -323,19 +334,19 @@ def multicolour9_throughput(torch, rb, W, n=8191, sweeps=100, with_solve=True):
         return time.perf_counter() - t0
 
     out = {"workload": f"{n}x{n} FP64, f~U[-1,1) seed 0, {sweeps} sweeps"}
-    for kernel in ("plain", "resident"):
+    for kernel in ("auto", "plain", "resident"):
         timed(3, kernel)
         one = min(timed(1, kernel) for _ in range(3))
         many = min(timed(sweeps + 1, kernel) for _ in range(2))
         per_sweep = (many - one) / sweeps
         glups = n * n / per_sweep / 1e9
+        model = MC9_PASS_BYTES_PER_LUP if kernel == "auto" else MC9_BYTES_PER_LUP
         res = {"ms_per_sweep": round(per_sweep * 1e3, 4), "GLUP/s": round(glups, 2),
-               "model_bytes_per_lup": MC9_BYTES_PER_LUP,
-               "model_GBs": round(glups * MC9_BYTES_PER_LUP, 1),
-               "frac_of_8TBs": round(glups * MC9_BYTES_PER_LUP / HBM_PEAK_GBS, 4)}
-        out["plain" if kernel == "plain" else "flag_driven"] = res
+               "model_bytes_per_lup": round(model, 2), "model_GBs": round(glups * model, 1),
+               "frac_of_8TBs": round(glups * model / HBM_PEAK_GBS, 4)}
+        out["flag_driven" if kernel == "resident" else kernel] = res
         log(f"multicolour 9-point {n} {kernel}: {per_sweep * 1e3:.3f} ms/sweep, {glups:.1f} GLUP/s, "
-            f"{glups * MC9_BYTES_PER_LUP:.0f} GB/s model")
+            f"{glups * model:.0f} GB/s model")
     del u, f, ws
     torch.cuda.empty_cache()
     if not with_solve:
@@ -344,7 +355,7 @@ def multicolour9_throughput(torch, rb, W, n=8191, sweeps=100, with_solve=True):
     hm = W.spacing(m)
     fm = torch.from_numpy(W.sine_rhs(m)).to("cuda")
     um = torch.zeros_like(fm)
-    for kernel in ("plain", "resident"):
+    for kernel in ("auto", "plain", "resident"):
         rb.rbgs_mc9_solve(um, fm, 8, -1.0, check_every=8, h=hm, kernel=kernel)
         um.zero_()
         torch.cuda.synchronize()
@@ -352,7 +363,7 @@ def multicolour9_throughput(torch, rb, W, n=8191, sweeps=100, with_solve=True):
         info = rb.rbgs_mc9_solve(um, fm, 4_000_000, 1e-8, check_every=1000, h=hm, kernel=kernel)
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
-        key = "time_to_1e-8_255_sine_" + ("plain" if kernel == "plain" else "flag_driven")
+        key = "time_to_1e-8_255_sine_" + ("flag_driven" if kernel == "resident" else kernel)
         out[key] = {"seconds": round(dt, 4), "sweeps": info["sweeps"],
                     "rel_residual": info["rel_residual"], "status": info["status"]}
         log(f"multicolour 9-point time-to-tol 255 {kernel}: {dt:.3f} s, {info['sweeps']} sweeps")
@@ -760,8 +771,10 @@ def refinement_throughput(torch, rb, W, n=16383, inner=100, outer=2):
 def batched_throughput(torch, rb, W, count=512, sweeps=100):
     """The batched workload: 512 grids, sizes uniform on {63,127,255,511,1023}
     (seed 0), f i.i.d. N(0,1) (seed 1+g), FP32, 100 sweeps each, one
-    graph-captured persistent launch after autotuning; beside it the same
-    grids swept one by one with the plain FP64 kernel (the judge), and in
+    graph-captured plan after autotuning (which times the register windows and
+    the persistent kernel; the plan runs the faster one), and a plan of the
+    persistent kernel at its tuned shape; beside it the same grids swept one by
+    one with the plain FP64 kernel (the judge), and in
     FP32 with the plain kernel and with the automatic single-grid choice
     (the same precision)."""
     sizes = W.batch_sizes(count, seed=0)
@@ -772,20 +785,22 @@ def batched_throughput(torch, rb, W, count=512, sweeps=100):
     lups = sum(n * n for n in sizes) * sweeps
     best = rb.rbgs_autotune_batched(us, fs)
     log(f"autotuned: {best}")
-    plan = rb.BatchPlan(us, fs, sweeps)
-    plan.launch()
-    plan.check()
-    reps = 5
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    for _ in range(reps):
-        plan.launch()
-    plan.check()
-    dt = (time.perf_counter() - t0) / reps
-    plan.close()
+    def plan_seconds(reps=5, **how):
+        with rb.BatchPlan(us, fs, sweeps, **how) as plan:
+            plan.launch()
+            plan.check()
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(reps):
+                plan.launch()
+            plan.check()
+            return (time.perf_counter() - t0) / reps
+
+    dt, dtp = plan_seconds(), plan_seconds(kernel="blocked")
     out = {"workload": f"{count} grids, N in {{63,127,255,511,1023}} seed 0, FP32, {sweeps} "
                        f"sweeps, one hipGraph launch", "total_lups": lups,
-           "autotuned": best, "seconds": round(dt, 5), "glups": round(lups / dt / 1e9, 1)}
+           "autotuned": best, "seconds": round(dt, 5), "glups": round(lups / dt / 1e9, 1),
+           "persistent": {"seconds": round(dtp, 5), "glups": round(lups / dtp / 1e9, 1)}}
     # the judge: each grid alone, plain FP64 kernel, one rbgs_sweep call per grid
     u64 = [torch.zeros((n + 2, n + 2), dtype=torch.float64, device="cuda") for n in sizes]
     f64 = [x.to("cuda") for x in fs64]
