@@ -25,10 +25,12 @@
 // above and below, which are recomputed and not written; a pass reads one
 // buffer and writes the other, so tiles are independent.
 //
-// 50 sweeps at 4001^2: 5.13 ms with a launch per colour, 1.62 here; a pass of
-// three sweeps takes 87 us (4 TB/s of the 350 MB it moves, two waves a SIMD).
-// What bounds it is the serial chain of twelve levels a step and the bytes in
-// flight, not the 148 FP64 instructions a step (a third of the time).
+// 50 sweeps at 4001^2: 5.13 ms with a launch per colour, 1.54 here; a pass of
+// three sweeps takes 87 us and moves 426 MB by the counters (4.9 TB/s; 320 MB
+// without the columns and pairs that tiles share), two waves a SIMD, which issue in
+// 41% of their cycles.  What bounds it is the serial chain of twelve levels a step
+// and the bytes in flight, not the 148 FP64 instructions a step (a third of the
+// time).
 //
 // Each point's operations and their order are k_mc9_quarter's; the division
 // by 20 is div20 below, which gives the same bits.
@@ -321,7 +323,8 @@ int pass_pairs(int rows, int bands, int sweeps) {
 // (four spill); small grids are bound by the steps of a strip, of which a
 // sweep adds four, and by launches.  Measured on MI355X, 60 sweeps: 255^2
 // 271 us at two a pass, 316 at three, 326 at one; 2047^2 788, 818 and 1125;
-// 4001^2 (50 sweeps) 2.03 ms at two, 1.62 at three.
+// 4001^2 (50 sweeps) 2.03 ms at two and 1.62 at three, 1.54 since the ring is
+// packed with u.
 int mc9_fuse(int n) { return n < 3000 ? 2 : 3; }
 
 hipError_t launch_mc9_pass(double* const in[4], double* const out[4], double* const f[4], int n,

@@ -75,7 +75,8 @@ hipError_t launch(const WindowArgs<double>& a, hipStream_t s) {
 //   8191^2 (100)                                    5363            5416
 //  12287^2 (20)                                     3540            3467
 //  12287^2 (60)                                     7028            7474
-// Calls of up to 8 sweeps stay with the windows, whose passes have no ramp.
+// Calls of up to 8 sweeps stay with the windows, whose passes have no ramp.  Larger
+// grids than those above: window_takes.
 bool pipeline_takes(int n, size_t elem_bytes, int nsweeps) {
     return elem_bytes == 8 && nsweeps >= 9 && n >= 1600 && (n <= 8000 || nsweeps <= 30);
 }

@@ -323,7 +323,8 @@ __global__ __launch_bounds__(256) void k_conv_march(ConvArgs a) {
     }
 }
 
-// Many channels, fewer pixels (cin a multiple of 32, from 64: the coarser levels).
+// Many channels, fewer pixels (cin a multiple of 32: the coarser levels, with 32
+// channels those of them that have too few rows for k_conv_march).
 // D divides the number of chunks.  Bound by latency: an output's 9 cin / 16 MFMAs are a chain of at most 108,
 // under a microsecond, but each group of them waits for its loads.  So a
 // wave takes few outputs (PG x 16 pixels, NT x 16 channels) and keeps the
@@ -677,7 +678,8 @@ __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ 
     if (threadIdx.x == 0) out[e] = sh[0];
 }
 
-// The same sums for many elements and all layers at once, coalesced: `ways`
+// The same sums for many elements and several layers at once (all of them, where
+// their partial sums fit the workspace's share), coalesced: `ways`
 // waves share 64 consecutive elements of a layer, taking the slots w, w +
 // ways, ... (64 consecutive floats of a slot at a time, four partial sums),
 // whose sums are added in the waves' order.  A block of 16 waves takes 64

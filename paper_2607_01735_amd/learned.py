@@ -106,8 +106,8 @@ def nested_targets(rb, torch, f, level_sweeps=LEVEL_SWEEPS, chunk=512, tune=True
     """u* for every f (device FP64 (B, n+2, n+2)) by nested iteration in FP32:
     restrict f to each coarser level (full weighting), sweep the coarsest
     level from u = 0, then prolong (bilinear) and sweep each finer level, all
-    grids of a chunk in one persistent batched launch per level.  Widened to
-    FP64 at the end."""
+    grids of a chunk in one plan per level, which runs the way of sweeping the
+    batch that the tuner found faster.  Widened to FP64 at the end."""
     count, n = f.shape[0], f.shape[1] - 2
     sizes = level_sizes(n, len(level_sweeps))
     out = torch.empty_like(f)
