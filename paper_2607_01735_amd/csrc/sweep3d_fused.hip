@@ -22,10 +22,11 @@
 // (black's are in both arrays; red's are loaded where they are needed).
 //
 // 40 sweeps at 383^3: 12.6 ms with a launch per half-sweep, 5.8 here; a pass of
-// two sweeps takes 265 us, of which 220 remain when every load hits a cache:
+// two sweeps takes 270 us, of which 220 remain when every load hits a cache:
 // it is bound by instruction issue (283 vector instructions per wave and step,
 // 168 of them the update's FP64; two waves a SIMD, which the registers allow)
-// and by the halo's share of them, then by memory (1.2 GB a pass, 4.5 TB/s).
+// and by the halo's share of them, then by memory (1.44 GB a pass by the
+// counters, 5.3 TB/s).
 //
 // Each point's operations and their order are k_rb3_half's; the division by 6
 // is div6 below, which gives the same bits.
